@@ -112,26 +112,41 @@ __device__ __forceinline__ uint32_t reach_quadrants(uint32_t m, const float4& q0
   return out;
 }
 
-// Returns the entry's quadrant mask.  qmask (optional): the forward's per-entry mask of quadrants with a
-// contributing pixel, ANDed in; without it the quadrants the surfel cannot reach are dropped by
-// reach_quadrants.
-__device__ __forceinline__ uint32_t stage_record(Stage& s, int lane, const float* rec, int64_t vn, int64_t n,
-                                                 uint32_t id, int ox, int oy, const uint8_t* qmask, uint32_t idx) {
-  // an entry no pixel of the forward took reaches no quadrant here: its record is not read at all
-  const uint32_t qm = qmask ? qmask[idx] : 0xfu;
-  if (qm == 0u) return 0u;
+// A list entry on its way to LDS: its record, as loaded.  qm: the quadrants the entry may reach (0: its
+// record is not read).
+struct StageIn {
+  float4 r[6];
+  uint32_t id, qm;
+  bool valid;
+};
+
+__device__ __forceinline__ void stage_load(StageIn& in, const float* rec, int64_t vn, int64_t n, uint32_t id,
+                                           uint32_t qm) {
   // an id outside [0, n) (never produced by the binning) stages a record that reaches no quadrant
-  const bool valid = (int64_t)id < n;
-  const float4* r = (const float4*)(rec + (size_t)(vn + (valid ? id : 0u)) * kRec);
-  const float4 r0 = r[0], r1 = r[1], r2 = r[2], r3 = r[3], r4 = r[4], r5 = r[5];
+  in.valid = (int64_t)id < n;
+  in.id = in.valid ? id : 0u;
+  in.qm = qm;
+  if (qm == 0u) return;
+  const float4* r = (const float4*)(rec + (size_t)(vn + in.id) * kRec);
+#pragma unroll
+  for (int k = 0; k < 6; ++k) in.r[k] = r[k];
+}
+
+// Writes the entry's LDS record and returns its mask among the quadrants in.qm: those its pixel rect
+// meets and, with 'reach', that some pixel sample of the surfel can reach (reach_quadrants; without it
+// in.qm is the forward's mask of the quadrants with a contributing pixel).
+__device__ __forceinline__ uint32_t stage_put(Stage& s, int lane, const StageIn& in, int ox, int oy, bool reach) {
+  // an entry no pixel takes reaches no quadrant here
+  if (in.qm == 0u) return 0u;
+  const float4 r0 = in.r[0], r1 = in.r[1], r2 = in.r[2], r3 = in.r[3], r4 = in.r[4], r5 = in.r[5];
   const float fox = (float)ox, foy = (float)oy;
   const float4 q0 = make_float4((r0.x - fox) + r0.z, (r0.y - foy) + r0.w, r1.x * kInvSqrt2, r1.y * kInvSqrt2);
   const float4 q1 = make_float4(r1.z * kInvSqrt2, r1.w * kInvSqrt2, r2.x, r2.y);
   s.q[lane][0] = q0;
   s.q[lane][1] = q1;
-  s.q[lane][2] = make_float4(r2.z, valid ? log2f(r3.x) : -INFINITY, r2.w, r2.w * r2.x);
-  s.q[lane][3] = make_float4(r3.y, r3.z, r3.w, __uint_as_float(valid ? id : 0u));
-  s.q[lane][4] = make_float4(r4.x, r4.y, r4.z, valid ? 1.f / r3.x : 0.f);
+  s.q[lane][2] = make_float4(r2.z, in.valid ? log2f(r3.x) : -INFINITY, r2.w, r2.w * r2.x);
+  s.q[lane][3] = make_float4(r3.y, r3.z, r3.w, __uint_as_float(in.id));
+  s.q[lane][4] = make_float4(r4.x, r4.y, r4.z, in.valid ? 1.f / r3.x : 0.f);
   // pixel rect relative to the tile origin
   const uint32_t px = __float_as_uint(r5.x), py = __float_as_uint(r5.y);
   const int i0 = (int)(px & 0xffffu) - ox, i1 = (int)(px >> 16) - ox;
@@ -142,9 +157,18 @@ __device__ __forceinline__ uint32_t stage_record(Stage& s, int lane, const float
     const int x0 = 8 * (k & 1), y0 = 8 * (k >> 1);
     if (i0 <= x0 + 7 && i1 >= x0 && j0 <= y0 + 7 && j1 >= y0) m |= 1u << k;
   }
-  if (qmask) m &= qm;
-  else if (m) m = reach_quadrants(m, q0, q1, r2.z, r4.w);
-  return valid ? m : 0u;
+  m &= in.qm;
+  if (reach && m) m = reach_quadrants(m, q0, q1, r2.z, r4.w);
+  return in.valid ? m : 0u;
+}
+
+__device__ __forceinline__ uint32_t stage_record(Stage& s, int lane, const float* rec, int64_t vn, int64_t n,
+                                                 uint32_t id, uint32_t qm, int ox, int oy, bool reach) {
+  // an entry no pixel of the forward took reaches no quadrant here: its record is not read at all
+  if (qm == 0u) return 0u;
+  StageIn in;
+  stage_load(in, rec, vn, n, id, qm);
+  return stage_put(s, lane, in, ox, oy, reach);
 }
 
 // Per-surfel terms of a lane at its quadrant-0 pixel; pixel k sits at (xr0 + 8 (k & 1), yr0 + 8 (k >> 1))
@@ -303,6 +327,7 @@ __device__ __forceinline__ void render_fwd_tile(const RenderArgs& a, Stage& s, u
   const int ox = tx * kTile, oy = ty * kTile;
   const uint32_t start = a.ranges[(int64_t)v * a.tiles + t], end = a.ranges[(int64_t)v * a.tiles + t + 1];
   const int64_t vn = (int64_t)v * a.n;
+  constexpr bool kOne = (kSub & (kSub - 1u)) == 0u;  // a single quadrant
 
   FwdState f[4];
   unsigned long long n_eval = 0, n_con = 0;
@@ -323,63 +348,92 @@ __device__ __forceinline__ void render_fwd_tile(const RenderArgs& a, Stage& s, u
   // the list ids of the next chunk are loaded one chunk ahead: staging then waits on one load round trip
   // (the records) instead of two
   uint32_t nid = start + lane < end ? a.ids[start + lane] : 0u;
+  [[maybe_unused]] StageIn in;
+  if constexpr (kOne) {
+    stage_load(in, a.rec, vn, a.n, nid, start + lane < end ? kSub : 0u);
+    nid = start + 64u + lane < end ? a.ids[start + 64u + lane] : 0u;
+  }
   for (uint32_t base = start; base < end && qlive != 0; base += 64) {
     const uint32_t idx = base + lane;
-    const uint32_t id = nid;
-    QuadBits qb;
-    qb.from_lanes(idx < end ? stage_record(s, lane, a.rec, vn, a.n, id, ox, oy, nullptr, 0) : 0u);
-    nid = idx + 64u < end ? a.ids[idx + 64u] : 0u;
+    uint32_t m4;
+    if constexpr (!kOne) {
+      m4 = stage_record(s, lane, a.rec, vn, a.n, nid, idx < end ? kSub : 0u, ox, oy, true);
+      nid = idx + 64u < end ? a.ids[idx + 64u] : 0u;
+    } else {
+      m4 = stage_put(s, lane, in, ox, oy, true);
+      // a quadrant block holds one pixel's state per lane, so there are registers for the next chunk's
+      // records too: their round trip runs under this chunk's entries
+      stage_load(in, a.rec, vn, a.n, nid, idx + 64u < end ? kSub : 0u);
+      nid = idx + 128u < end ? a.ids[idx + 128u] : 0u;
+    }
     __syncthreads();
     const int cnt = (int)min(64u, end - base);
     int reached = cnt;  // entries of this chunk the wave evaluated
     // bit j of cq[k]: quadrant k had a taking pixel at entry base + j (scalar registers)
     uint64_t cq[4] = {0, 0, 0, 0};
-    uint64_t cur = qb.w[0];  // entry j's nibble in bits 0-3
-    for (int j = 0; j < cnt; ++j) {
-      if (kCount) {
+    auto entry = [&](int j, uint32_t m) {
+      const float4 q0 = s.q[j][0], q1 = s.q[j][1], q2 = s.q[j][2], q3 = s.q[j][3], q4 = s.q[j][4];
+      LaneTerms lt;
+      lane_terms(lx0, ly0, q0, q1, q2, lt);
+      const uint32_t e_idx = lane_copy(base + (uint32_t)j);
+      float csum = 0.f, ccnt = 0.f;
+      bool took = false;
+      Px e[4];
 #pragma unroll
-        for (int k = 0; k < 4; ++k)
-          if ((kSub >> k) & 1u) n_eval += f[k].T > 0.f ? 1u : 0u;
-      }
-      const uint32_t m = (uint32_t)cur & 0xfu & qlive;
-      cur >>= 4;
-      if (m != 0) {
-        const float4 q0 = s.q[j][0], q1 = s.q[j][1], q2 = s.q[j][2], q3 = s.q[j][3], q4 = s.q[j][4];
-        LaneTerms lt;
-        lane_terms(lx0, ly0, q0, q1, q2, lt);
-        const uint32_t e_idx = lane_copy(base + (uint32_t)j);
-        float csum = 0.f, ccnt = 0.f;
-        bool took = false;
-        Px e[4];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          if (!((kSub >> k) & 1u)) continue;
-          // (evaluated where it is used: the compiler sinks each pixel's evaluation into its branch)
-          if (k == 0) eval_px<0>(lt, q2.y, e[0]);
-          if (k == 1) eval_px<1>(lt, q2.y, e[1]);
-          if (k == 2) eval_px<2>(lt, q2.y, e[2]);
-          if (k == 3) eval_px<3>(lt, q2.y, e[3]);
-          if (((m >> k) & 1u) && fwd_px<kContrib>(e[k], q2, q3, q4, e_idx, f[k], n_con, a.gamma, csum, ccnt)) {
-            took = true;
-            if (kMask) cq[k] |= 1ull << j;
-          }
-        }
-        if (kContrib && took) {
-          const float ts = wave_sum_lane63(csum), tc = wave_sum_lane63(ccnt);
-          if (lane == 63 && tc > 0.f) {
-            float* w = a.cws + 2 * (vn + (int64_t)__float_as_uint(q3.w));
-            atomicAdd(w, ts);
-            atomicAdd(w + 1, tc);
-          }
+      for (int k = 0; k < 4; ++k) {
+        if (!((kSub >> k) & 1u)) continue;
+        // (evaluated where it is used: the compiler sinks each pixel's evaluation into its branch)
+        if (k == 0) eval_px<0>(lt, q2.y, e[0]);
+        if (k == 1) eval_px<1>(lt, q2.y, e[1]);
+        if (k == 2) eval_px<2>(lt, q2.y, e[2]);
+        if (k == 3) eval_px<3>(lt, q2.y, e[3]);
+        if (((m >> k) & 1u) && fwd_px<kContrib>(e[k], q2, q3, q4, e_idx, f[k], n_con, a.gamma, csum, ccnt)) {
+          took = true;
+          if (kMask) cq[k] |= 1ull << j;
         }
       }
-      if ((j & 15) == 15) {
-        qlive = live_quadrants<kSub>(f);
-        if (qlive == 0) {
+      if (kContrib && took) {
+        const float ts = wave_sum_lane63(csum), tc = wave_sum_lane63(ccnt);
+        if (lane == 63 && tc > 0.f) {
+          float* w = a.cws + 2 * (vn + (int64_t)__float_as_uint(q3.w));
+          atomicAdd(w, ts);
+          atomicAdd(w + 1, tc);
+        }
+      }
+    };
+    if constexpr (kOne && !kCount) {
+      // one quadrant: walk the set bits of its ballot
+      uint64_t todo = __ballot((m4 & kSub) != 0u);
+      for (int seen = 1; todo != 0; ++seen) {
+        const int j = __builtin_ctzll(todo);
+        todo &= todo - 1;
+        entry(j, kSub);
+        if ((seen & 15) == 0 && live_quadrants<kSub>(f) == 0) {
           reached = j + 1;
           break;
         }
-        cur = qb.word((j + 1) >> 4);
+      }
+    } else {
+      QuadBits qb;
+      qb.from_lanes(m4);
+      uint64_t cur = qb.w[0];  // entry j's nibble in bits 0-3
+      for (int j = 0; j < cnt; ++j) {
+        if (kCount) {
+#pragma unroll
+          for (int k = 0; k < 4; ++k)
+            if ((kSub >> k) & 1u) n_eval += f[k].T > 0.f ? 1u : 0u;
+        }
+        const uint32_t m = (uint32_t)cur & 0xfu & qlive;
+        cur >>= 4;
+        if (m != 0) entry(j, m);
+        if ((j & 15) == 15) {
+          qlive = live_quadrants<kSub>(f);
+          if (qlive == 0) {
+            reached = j + 1;
+            break;
+          }
+          cur = qb.word((j + 1) >> 4);
+        }
       }
     }
     // entries past 'reached' lie beyond every pixel's 'last': the reverse pass never reads them
@@ -663,48 +717,95 @@ __device__ __forceinline__ void render_bwd_tile(const BwdArgs& A, Stage& s, uint
   const int slot = reduce16_index(lane);
   const float sc = slot_scale(slot);
 
-  // the list ids of the next (lower) chunk are loaded one chunk ahead, as in the forward
-  uint32_t nlo = hi - start > 64u ? hi - 64u : start;
-  uint32_t nid = nlo + lane < hi ? a.ids[nlo + lane] : 0u;
-  for (uint32_t top = hi; top > start;) {
-    const uint32_t lo = nlo;
-    const uint32_t idx = lo + lane;
-    const uint32_t id = nid;
-    QuadBits qb;
+  constexpr bool kOne = (kSub & (kSub - 1u)) == 0u;  // a single quadrant
+  // quadrants of the subset in which list entry idx of the chunk below 'top' may contribute: each only
+  // below its walk bound, and where the forward found a contributing pixel
+  auto wanted = [&](uint32_t idx, uint32_t top) -> uint32_t {
+    uint32_t allow = 0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) allow |= (((kSub >> k) & 1u) && idx < qhi[k] ? 1u : 0u) << k;
+    if (idx >= top) allow = 0u;
+    return allow && a.img.qmask ? a.img.qmask[idx] & allow : allow;
+  };
+  auto below = [&](uint32_t x) { return x - start > 64u ? x - 64u : start; };
+  uint32_t nlo = below(hi);
+  if constexpr (kOne) {
+    // as the forward: the next chunk's records are loaded under this chunk's entries, and only the set
+    // bits of the quadrant's ballot are walked
+    StageIn in;
+    uint32_t nid, nqm;
     {
-      // the subset's quadrants, each only below its walk bound
-      uint32_t allow = 0;
-#pragma unroll
-      for (int k = 0; k < 4; ++k) allow |= (((kSub >> k) & 1u) && idx < qhi[k] ? 1u : 0u) << k;
-      qb.from_lanes(idx < top ? stage_record(s, lane, a.rec, vn, a.n, id, ox, oy, a.img.qmask, idx) & allow : 0u);
+      const uint32_t idx = nlo + lane;
+      stage_load(in, a.rec, vn, a.n, idx < hi ? a.ids[idx] : 0u, wanted(idx, hi));
+      const uint32_t l2 = below(nlo);
+      nid = l2 + lane < nlo ? a.ids[l2 + lane] : 0u;
+      nqm = wanted(l2 + lane, nlo);
     }
-    nlo = lo - start > 64u ? lo - 64u : start;
-    nid = nlo + lane < lo ? a.ids[nlo + lane] : 0u;
-    __syncthreads();
-    const int j0 = (int)(top - lo) - 1;
-    uint64_t cur = qb.word(j0 >> 4) << (4 * (15 - (j0 & 15)));  // entry j's nibble in bits 60-63
-    for (int j = (int)(top - lo) - 1; j >= 0; --j) {
-      const uint32_t e_idx = lo + (uint32_t)j;
-      if ((j & 15) == 15) cur = qb.word(j >> 4);
-      const uint32_t m = (uint32_t)(cur >> 60);  // quadrant bits, kSub and the quadrants' walk bounds applied
-      cur <<= 4;
-      if (m == 0) continue;
-      const float4 q0 = s.q[j][0], q1 = s.q[j][1], q2 = s.q[j][2], q3 = s.q[j][3], q4 = s.q[j][4];
-      LaneTerms lt;
-      lane_terms(lx0, ly0, q0, q1, q2, lt);
-      float acc[kGradFields];
+    for (uint32_t top = hi; top > start;) {
+      const uint32_t lo = nlo;
+      uint64_t todo = __ballot(stage_put(s, lane, in, ox, oy, !a.img.qmask) != 0u);
+      nlo = below(lo);
+      stage_load(in, a.rec, vn, a.n, nid, nqm);
+      const uint32_t l2 = below(nlo);
+      nid = l2 + lane < nlo ? a.ids[l2 + lane] : 0u;
+      nqm = wanted(l2 + lane, nlo);
+      __syncthreads();
+      while (todo != 0) {
+        const int j = 63 - __builtin_clzll(todo);
+        todo &= ~(1ull << j);
+        const uint32_t e_idx = lo + (uint32_t)j;
+        const float4 q0 = s.q[j][0], q1 = s.q[j][1], q2 = s.q[j][2], q3 = s.q[j][3], q4 = s.q[j][4];
+        LaneTerms lt;
+        lane_terms(lx0, ly0, q0, q1, q2, lt);
+        float acc[kGradFields];
 #pragma unroll
-      for (int f = 0; f < kGradFields; ++f) acc[f] = 0.f;
-      bool any = false;
-      if ((kSub & 1u) && (m & 1u)) bwd_px<0, kGeom>(lt, q0, q1, q2, q3, q4, e_idx, p[0], acc, any);
-      if ((kSub & 2u) && (m & 2u)) bwd_px<1, kGeom>(lt, q0, q1, q2, q3, q4, e_idx, p[1], acc, any);
-      if ((kSub & 4u) && (m & 4u)) bwd_px<2, kGeom>(lt, q0, q1, q2, q3, q4, e_idx, p[2], acc, any);
-      if ((kSub & 8u) && (m & 8u)) bwd_px<3, kGeom>(lt, q0, q1, q2, q3, q4, e_idx, p[3], acc, any);
-      if (!any) continue;
-      bwd_commit<kGeom>(acc, lane, slot, sc, q4.w, rgv, rgn, __float_as_uint(q3.w));
+        for (int f = 0; f < kGradFields; ++f) acc[f] = 0.f;
+        bool any = false;
+        if (kSub == 1u) bwd_px<0, kGeom>(lt, q0, q1, q2, q3, q4, e_idx, p[0], acc, any);
+        if (kSub == 2u) bwd_px<1, kGeom>(lt, q0, q1, q2, q3, q4, e_idx, p[1], acc, any);
+        if (kSub == 4u) bwd_px<2, kGeom>(lt, q0, q1, q2, q3, q4, e_idx, p[2], acc, any);
+        if (kSub == 8u) bwd_px<3, kGeom>(lt, q0, q1, q2, q3, q4, e_idx, p[3], acc, any);
+        if (any) bwd_commit<kGeom>(acc, lane, slot, sc, q4.w, rgv, rgn, __float_as_uint(q3.w));
+      }
+      __syncthreads();
+      top = lo;
     }
-    __syncthreads();
-    top = lo;
+  } else {
+    // the list ids of the next (lower) chunk are loaded one chunk ahead, as in the forward
+    uint32_t nid = nlo + lane < hi ? a.ids[nlo + lane] : 0u;
+    for (uint32_t top = hi; top > start;) {
+      const uint32_t lo = nlo;
+      const uint32_t id = nid;
+      QuadBits qb;
+      qb.from_lanes(stage_record(s, lane, a.rec, vn, a.n, id, wanted(lo + lane, top), ox, oy, !a.img.qmask));
+      nlo = below(lo);
+      nid = nlo + lane < lo ? a.ids[nlo + lane] : 0u;
+      __syncthreads();
+      const int j0 = (int)(top - lo) - 1;
+      uint64_t cur = qb.word(j0 >> 4) << (4 * (15 - (j0 & 15)));  // entry j's nibble in bits 60-63
+      for (int j = (int)(top - lo) - 1; j >= 0; --j) {
+        const uint32_t e_idx = lo + (uint32_t)j;
+        if ((j & 15) == 15) cur = qb.word(j >> 4);
+        const uint32_t m = (uint32_t)(cur >> 60);  // quadrant bits, kSub and the quadrants' walk bounds applied
+        cur <<= 4;
+        if (m == 0) continue;
+        const float4 q0 = s.q[j][0], q1 = s.q[j][1], q2 = s.q[j][2], q3 = s.q[j][3], q4 = s.q[j][4];
+        LaneTerms lt;
+        lane_terms(lx0, ly0, q0, q1, q2, lt);
+        float acc[kGradFields];
+#pragma unroll
+        for (int f = 0; f < kGradFields; ++f) acc[f] = 0.f;
+        bool any = false;
+        if ((kSub & 1u) && (m & 1u)) bwd_px<0, kGeom>(lt, q0, q1, q2, q3, q4, e_idx, p[0], acc, any);
+        if ((kSub & 2u) && (m & 2u)) bwd_px<1, kGeom>(lt, q0, q1, q2, q3, q4, e_idx, p[1], acc, any);
+        if ((kSub & 4u) && (m & 4u)) bwd_px<2, kGeom>(lt, q0, q1, q2, q3, q4, e_idx, p[2], acc, any);
+        if ((kSub & 8u) && (m & 8u)) bwd_px<3, kGeom>(lt, q0, q1, q2, q3, q4, e_idx, p[3], acc, any);
+        if (!any) continue;
+        bwd_commit<kGeom>(acc, lane, slot, sc, q4.w, rgv, rgn, __float_as_uint(q3.w));
+      }
+      __syncthreads();
+      top = lo;
+    }
   }
 }
 
@@ -745,7 +846,17 @@ __global__ __launch_bounds__(256) void k_zero_visible(const uint32_t* __restrict
 
 // Heavy tiles split over several waves: the 1 / kSplitDiv heaviest of a launch's tiles (at most
 // kSplitMax) into four quadrant blocks, the next 1 / kHalfDiv (at most kSplitMax; none for 0) into two
-// halves.
+// halves.  A launch with fewer tiles than the chip holds waves of the kernel ('resident': 1,024 SIMDs
+// times its waves per SIMD) is split further, because its time is then one wave's walk of one list:
+//   2 tiles <= 1.25 resident   every tile, into halves, and the heaviest into quadrants as far as 1.25
+//                              resident blocks go (all of them up to 0.31 resident tiles)
+//   up to 'fill_below' tiles   the heaviest into quadrants, up to 'resident' blocks
+// Measured (us, before -> after): 64 tiles (4,096 surfels, 128x128) forward 121 -> 47, reverse 181 -> 68;
+// 1,200 tiles (5 M surfels, 640x480) 4067 -> 1932 and 3232 -> 1702; 1,900 tiles (1 M, 800x600) 109 -> 83
+// and 160 -> 128; 2,304 tiles (2 M, 1024x576) 302 -> 222 and 440 -> 338; 3,072 tiles (2 M, 1024x768)
+// 302 -> 243 and 442 -> 386; 3,600 tiles (5 M, 1280x720) forward 1744 -> 1229, but the reverse 1604 ->
+// 1703 and 242 -> 262 (1 M), so the reverse stops at 3/4 resident.  At 6,700 tiles more splitting is
+// slower in both (forward 197 -> 201 and reverse 353 -> 358 with 5,120 to 8,192 blocks).
 #ifndef CGV2_SPLIT_DIV
 #define CGV2_SPLIT_DIV 48
 #endif
@@ -769,6 +880,24 @@ __global__ __launch_bounds__(256) void k_clear_split_qmask(RenderArgs a) {
 }
 }  // namespace cgv2
 
+static void split_tiles(cgv2::RenderArgs& a, int64_t resident, int64_t fill_below) {
+  a.n_q = a.n_h = 0;
+  if (!a.order) return;
+  const int64_t all = (int64_t)a.cams.count * a.tiles;
+  int64_t q = std::min<int64_t>(all / kSplitDiv, kSplitMax);
+  int64_t h = kHalfDiv > 0 ? std::min<int64_t>(all / std::max(kHalfDiv, 1), kSplitMax) : 0;
+  const int64_t most = resident + resident / 4;
+  if (2 * all <= most) {
+    q = std::max(q, (most - 2 * all) / 2);
+    h = all;
+  } else if (all < fill_below) {
+    q = std::max(q, (resident - all) / 3);
+  }
+  a.n_q = (uint32_t)std::min(q, all);
+  a.n_h = (uint32_t)std::min(h, all - (int64_t)a.n_q);
+}
+constexpr int64_t kSimds = 1024;
+
 static cgv2::RenderArgs make_args(const cgv2_proj& p, const cgv2_bins& b, const cgv2::CamPack& cams, int64_t n,
                                   int tiles_x, int tiles_y, const cgv2_image* img, unsigned long long* counters) {
   cgv2::RenderArgs a;
@@ -786,17 +915,21 @@ static cgv2::RenderArgs make_args(const cgv2_proj& p, const cgv2_bins& b, const 
   a.counters = counters;
   a.cws = nullptr;
   a.gamma = 0.f;
-  const int64_t all = (int64_t)cams.count * a.tiles;
-  a.n_q = a.order ? (uint32_t)std::min<int64_t>(all / kSplitDiv, kSplitMax) : 0u;
-  a.n_h = a.order && kHalfDiv > 0 ? (uint32_t)std::min<int64_t>({all / std::max(kHalfDiv, 1), (int64_t)kSplitMax,
-                                                                   all - (int64_t)a.n_q})
-                                  : 0u;
+  a.n_q = a.n_h = 0;
   return a;
+}
+
+// the forward kernels hold at least 4 waves per SIMD, the reverse 4 without and 3 with geometry terms
+static void split_fwd(cgv2::RenderArgs& a) { split_tiles(a, 4 * kSimds, 4 * kSimds); }
+static void split_bwd(cgv2::RenderArgs& a, bool geom) {
+  const int64_t resident = (geom ? 3 : 4) * kSimds;
+  split_tiles(a, resident, resident * 3 / 4 + 1);
 }
 
 hipError_t cgv2_launch_render_fwd(const cgv2_proj& p, const cgv2_bins& b, const cgv2::CamPack& cams, int64_t n,
                                   int tiles_x, int tiles_y, const cgv2_image& img, hipStream_t st) {
   cgv2::RenderArgs a = make_args(p, b, cams, n, tiles_x, tiles_y, &img, nullptr);
+  split_fwd(a);
   const unsigned grid = (unsigned)((int64_t)cams.count * a.tiles + 3 * a.n_q + a.n_h);
   if (img.qmask && a.n_q + a.n_h)
     hipLaunchKernelGGL(cgv2::k_clear_split_qmask, dim3(a.n_q + a.n_h), dim3(256), 0, st, a);
@@ -808,6 +941,7 @@ hipError_t cgv2_launch_render_fwd(const cgv2_proj& p, const cgv2_bins& b, const 
 hipError_t cgv2_launch_render_count(const cgv2_proj& p, const cgv2_bins& b, const cgv2::CamPack& cams, int64_t n,
                                     int tiles_x, int tiles_y, unsigned long long* counters, hipStream_t st) {
   cgv2::RenderArgs a = make_args(p, b, cams, n, tiles_x, tiles_y, nullptr, counters);
+  split_fwd(a);
   const unsigned grid = (unsigned)((int64_t)cams.count * a.tiles + 3 * a.n_q + a.n_h);
   hipLaunchKernelGGL((cgv2::k_render_fwd<true, false, false>), dim3(grid), dim3(64), 0, st, a);
   return hipGetLastError();
@@ -825,8 +959,9 @@ hipError_t cgv2_launch_render_bwd(const cgv2_proj& p, const cgv2_bins& b, const 
   A.r = make_args(p, b, cams, n, tiles_x, tiles_y, &img, nullptr);
   A.up = up;
   A.rg = rg;
-  const unsigned grid = (unsigned)((int64_t)cams.count * A.r.tiles + 3 * A.r.n_q + A.r.n_h);
   const bool geom = up.d_depth || up.d_depth_med || up.d_normal || up.d_alpha;
+  split_bwd(A.r, geom);
+  const unsigned grid = (unsigned)((int64_t)cams.count * A.r.tiles + 3 * A.r.n_q + A.r.n_h);
   if (geom) hipLaunchKernelGGL(cgv2::k_render_bwd<true>, dim3(grid), dim3(64), 0, st, A);
   else hipLaunchKernelGGL(cgv2::k_render_bwd<false>, dim3(grid), dim3(64), 0, st, A);
   return hipGetLastError();
@@ -835,6 +970,7 @@ hipError_t cgv2_launch_render_bwd(const cgv2_proj& p, const cgv2_bins& b, const 
 hipError_t cgv2_launch_contribution(const cgv2_proj& p, const cgv2_bins& b, const cgv2::CamPack& cams, int64_t n,
                                     int tiles_x, int tiles_y, float gamma, float* cws, hipStream_t st) {
   cgv2::RenderArgs a = make_args(p, b, cams, n, tiles_x, tiles_y, nullptr, nullptr);
+  split_fwd(a);
   a.cws = cws;
   a.gamma = gamma;
   const unsigned grid = (unsigned)((int64_t)cams.count * a.tiles + 3 * a.n_q + a.n_h);
