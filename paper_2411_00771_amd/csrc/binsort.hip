@@ -5,21 +5,20 @@
 //   surfel scan   one fused pass of three kernels (two up to kSurfLocal chunks) over every (view,
 //                 surfel): the exclusive prefix sum of its tile count (from its rect) and the compaction
 //                 of the visible ones into per-view lists, plus the capacity check
-//   k_stage       groups of lanes per visible surfel: for each tile of its rect that the surfel's
-//                 alpha >= 1/255 region reaches (reach_cell over the tile's pixel samples), a returning
-//                 atomic on the tile's counter gives the entry's rank within the tile; (tile, rank,
-//                 depth bits << 32 | id) goes to the surfel's own slice, a sentinel tile to the slots of
-//                 the rect tiles it cannot reach
-//   k_tile_scan   one workgroup: exclusive prefix sum of the V * tiles counters -> ranges; up to
-//                 kScanChunk tiles of at most kMaxViews views, k_tile_scan_order also computes the
-//                 launch order in the same workgroup (the multi-workgroup order kernels otherwise)
-//   k_place       one thread per staged slot: keys[ranges[tile] + rank] = key (no atomics)
+//   k_stage       a workgroup per run of consecutive visible surfels: for each tile of a surfel's rect that
+//                 its alpha >= 1/255 region reaches (reach_cell over the tile's pixel samples), a returning
+//                 atomic on the tile's counter gives the entry's rank within the tile; the run's entries
+//                 (counter, rank, depth bits << 32 | id) are packed at the start of the run's rect slots
+//   k_tile_scan_order   one workgroup up to kScanChunk tiles: exclusive prefix sum of the counters ->
+//                 ranges and each counter's first slot; for at most kMaxViews views also the launch order
+//                 (k_tile_sums / k_tile_apply and the multi-workgroup order kernels otherwise)
+//   k_place       a workgroup per run: keys[first slot of the counter + rank] = key (no atomics)
 //   k_sort_wave   one wave per tile: bitonic sort of lists up to kWaveSort entries in registers
 //   k_sort_big    longer lists, up to kBig entries in 128 KB of LDS; longer still are sorted in kBig
 //                 chunks and merged in global memory by rank (binary search)
 // (depth bits, id) is unique within a tile, so the order in which the atomics hand out ranks does not
 // matter: the result is deterministic and bit-exact.  HBM traffic is about 16 B staged + 16 B read +
-// 8 B placed + 8 B read + 4 B written per intersection.
+// 8 B placed + 8 B read + 4 B written per listed entry, nothing per rect tile out of reach.
 #include "cgv2r_device.h"
 #include "cgv2r_kernels.h"
 
@@ -192,16 +191,17 @@ __global__ __launch_bounds__(kSurfBlock) void k_surfel_sums(const uint16_t* __re
   }
 }
 
-// pass 3 of the surfel scan: soff[e] = first staged slot of (view, surfel) e, soff[m] = total;
-// visible[pos] = surfel id of every (view, surfel) with a non-empty rect in (view, id) order,
-// vstart[v] = first entry of view v, vstart[V] = total; the total is checked against the capacity.
+// pass 3 of the surfel scan: visible[pos] = surfel id of every (view, surfel) with a non-empty rect in
+// (view, id) order, voff[pos] = its first rect slot (for pos < max_vis; more are visible only when the
+// slots exceed the capacity too), vstart[v] = first entry of view v, vstart[V] = total; the total is
+// checked against the capacity.
 // local_nsb > 0 (at most kSurfLocal chunks): the sums are pass 1's raw chunk sums and each workgroup
 // adds up those before it (pass 2 is skipped); 0: the sums are pass 2's scanned ones, totals its totals.
 __global__ __launch_bounds__(kSurfBlock) void k_surfel_apply(
     const uint16_t* __restrict__ rect, int64_t m, int64_t n, const uint64_t* __restrict__ sums_cnt,
     const uint64_t* __restrict__ sums_vis, const uint64_t* __restrict__ totals, int local_nsb,
-    uint32_t* __restrict__ soff, uint32_t* __restrict__ visible, uint32_t* __restrict__ vstart, int V,
-    int64_t capacity, int32_t* __restrict__ status, int64_t* __restrict__ needed) {
+    uint32_t* __restrict__ voff, int64_t max_vis, uint32_t* __restrict__ visible, uint32_t* __restrict__ vstart,
+    int V, int64_t capacity, int32_t* __restrict__ status, int64_t* __restrict__ needed) {
   __shared__ uint64_t red[4][kSurfWaves];
   __shared__ uint32_t wt[2][kSurfWaves];
   __shared__ uint64_t carry[4];
@@ -269,204 +269,437 @@ __global__ __launch_bounds__(kSurfBlock) void k_surfel_apply(
   for (int r = 0; r < kSurfRows; ++r) {
     const int64_t e = wbase + 64 * r + lane;
     if (e >= m) continue;
-    const uint64_t cs = oc + ex[r];
-    soff[e] = (uint32_t)(cs > 0xffffffffull ? 0xffffffffull : cs);
     const uint32_t pos = (uint32_t)(ov + fx[r]);
     const int64_t i = e % n;
-    if (c[r] != 0u) visible[pos] = (uint32_t)i;
+    if (c[r] != 0u) {
+      visible[pos] = (uint32_t)i;
+      const uint64_t cs = oc + ex[r];
+      if (pos < max_vis) voff[pos] = (uint32_t)(cs > 0xffffffffull ? 0xffffffffull : cs);
+    }
     if (i == 0) vstart[e / n] = pos;
   }
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     const uint64_t K = carry[2];
-    soff[m] = (uint32_t)(K > 0xffffffffull ? 0xffffffffull : K);
     vstart[V] = (uint32_t)carry[3];
     *needed = (int64_t)K;
     if ((int64_t)K > capacity) *status = 1;
   }
 }
 
-// Groups of 32 lanes take one visible surfel of view blockIdx.y each and spread its rect tiles over the
-// group.  A group stages at most the first kFirstTiles tiles of a surfel itself; the rest of a larger rect
-// (a surfel near the camera, or a long thin one) goes to a queue of kChunkTiles-tile chunks that
-// k_stage_big spreads over all groups, so no group walks one rect for long while the others idle.
-// (Measured: 8 or 16 lanes per surfel are slower on the training views, 64 saves 7 us there but costs
-// 20 % of the served latency on the 5 M-surfel 4K views; batches of 64 surfels with their tiles
-// flattened over the lanes are slower; up to 8192 workgroups per view instead of 2048 saves 3 us.)
+// How a workgroup of k_stage takes the visible surfels of view blockIdx.y depends on the call's rects:
+//   large rects  runs of kGroups surfels, a group of 32 lanes spread over the rect tiles of each
+//   small rects  (on average at most kSmallRect tiles: distant surfels, one or two tiles each, and at least
+//                kLaneMin visible per view, so that the runs cover the chip) runs of a surfel per lane.  A
+//                lane stages its own surfel when the rect holds at most kLaneTiles tiles; the groups then
+//                take the run's others.  (With a group for each, a 640x480 view of 5 M surfels, 2.6 M
+//                visible with 1.6 rect tiles each, kept 5 % of the lanes busy.)
+// The tile counters lie row by row for large rects, whose rows then touch one cache line, and column by
+// column for small ones: atomics on one 128-byte line complete every 4 ns, and the horizon's row of long
+// lists would share few lines (5 M surfels at 1920x1080: 854 us row by row, 510 column by column; 1 M at
+// 1600x1066, 52 tiles per rect, 33 us column by column, 26 row by row).
+// A group stages at most the first kFirstTiles tiles of a surfel; the rest of a larger rect (a surfel near
+// the camera, or a long thin one) goes to a queue of kChunkTiles-tile chunks that k_stage_big spreads over
+// all groups, so no group walks one rect for long while the others idle.  (Measured: 8 or 16 lanes per
+// surfel are slower on the training views, 64 saves 7 us there but costs 20 % of the served latency on the
+// 5 M-surfel 4K views; up to 8192 workgroups per view instead of 2048 saves 3 us.)
 constexpr int kGroup = 32;
-constexpr uint32_t kNoTile = 0xffffffffu;  // staged slot of a rect tile the surfel cannot reach
+constexpr int kStageBlock = 256;
+constexpr uint32_t kGroups = kStageBlock / kGroup;
+constexpr uint32_t kLaneMin = 32768;
+constexpr uint32_t kSmallRect = 6;
+constexpr uint32_t kLaneTiles = 8;
+constexpr int kLaneStep = 4;             // tiles of a lane in flight
+constexpr uint32_t kRunBig = 0x8000u;    // a long run's count: of a surfel with slots of its own
 constexpr uint32_t kChunkTiles = 4 * kGroup;
 #ifndef CGV2_FIRST_CHUNKS
 #define CGV2_FIRST_CHUNKS 2
 #endif
 constexpr uint32_t kFirstTiles = CGV2_FIRST_CHUNKS * kChunkTiles;
+// Atomics on one address complete every 13 ns, whichever XCD they come from: a tile of 32,767 entries (the
+// horizon of a 640x480 view of 5 M surfels) alone takes 0.43 ms.  Launches of few tiles, whose lists can be
+// that long, count into kSets counters per tile (workgroup b into set b % kSets).
+constexpr int kSets = 8;
+constexpr int64_t kSetsMaxTiles = 4096;
 
-// One visible surfel of view v as the staging sees it.
+// Small-rect runs pack a surfel's index within its run into the top 8 bits of an entry's rank (a tile lists
+// each of a view's n surfels at most once).
+constexpr int kRankBits = 24;
+static_assert(kStageBlock == 256, "a run's index takes 8 bits of the rank");
+__device__ __forceinline__ bool small_rects(const uint32_t* vstart, const int64_t* needed, int V, int64_t n) {
+  const uint64_t vis = vstart[V];
+  return vis >= (uint64_t)kLaneMin * (uint32_t)V && (uint64_t)*needed <= kSmallRect * vis &&
+         n <= ((int64_t)1 << kRankBits);
+}
+
+// A view's tiles and their counters.
+struct TileMap {
+  uint32_t tiles_x, tiles_y, m;  // m: tiles of all views
+  int sets;
+  __device__ __forceinline__ uint32_t counter(uint32_t tx, uint32_t ty, bool small) const {
+    return small ? tx * tiles_y + ty : ty * tiles_x + tx;
+  }
+  // the counter of tile i of the call's views
+  __device__ __forceinline__ uint32_t counter_of(uint32_t i, bool small) const {
+    if (!small) return i;
+    const uint32_t tiles = tiles_x * tiles_y, v = i / tiles, t = i - v * tiles, ty = t / tiles_x;
+    return v * tiles + counter(t - ty * tiles_x, ty, true);
+  }
+  // the first counter of view v in the set of this workgroup
+  __device__ __forceinline__ uint32_t base(int v) const {
+    return (uint32_t)v * tiles_x * tiles_y + (sets > 1 ? blockIdx.x % kSets * m : 0u);
+  }
+};
+
+// One visible surfel as the staging sees it.
 struct StageSurfel {
-  uint32_t tx0, ty0, w, total, o;
+  uint32_t tx0, ty0, w, total;
   float4 r0;
-  uint64_t key;
+  float depth;
   Reach q;
 };
 
-__device__ __forceinline__ void stage_surfel(const uint16_t* rect, const float* rec, const uint32_t* soff, int64_t n,
-                                             int v, uint32_t i, StageSurfel& u) {
-  const int64_t vi = (int64_t)v * n + i;
+__device__ __forceinline__ void stage_rect(const uint16_t* rect, int64_t vi, StageSurfel& u) {
   uint32_t tx1, ty1;
   tile_rect(rect + 4 * vi, u.tx0, u.ty0, tx1, ty1);
   u.w = tx1 - u.tx0;
   u.total = u.w * (ty1 - u.ty0);
+}
+
+__device__ __forceinline__ void stage_surfel(const float* rec, int64_t vi, StageSurfel& u) {
   const float4* rp = (const float4*)(rec + vi * kRec);
   const float4 r1 = rp[1], r2 = rp[2], r4 = rp[4];
   u.r0 = rp[0];
-  u.key = ((uint64_t)__float_as_uint(r2.w) << 32) | i;
+  u.depth = r2.w;
   reach_setup(r1.x * kInvSqrt2, r1.y * kInvSqrt2, r1.z * kInvSqrt2, r1.w * kInvSqrt2, r2.x, r2.y, r2.z, r4.w, u.q);
-  u.o = soff[vi];
 }
 
-// Rect tiles [kb, ke) of surfel u, tile k on lane kb + g + 32 j of the group: for each tile the surfel's
-// alpha >= 1/255 region reaches, a returning atomic on the tile's counter gives the entry's rank; (tile,
-// rank) and the key go to the surfel's slot o + k, a sentinel tile to the slots of the tiles it cannot
-// reach.  Four independent returning atomics are in flight per lane before their results are used.
-__device__ __forceinline__ void stage_range(const StageSurfel& u, uint32_t tbase, int tiles_x, uint32_t kb, uint32_t ke,
-                                            uint32_t g, uint32_t* __restrict__ cnt, uint2* __restrict__ st_pos,
-                                            uint64_t* __restrict__ st_key) {
-  for (uint32_t k0 = kb + g; k0 < ke; k0 += 4 * kGroup) {
-    uint32_t t[4], r[4];
-    bool keep[4];
+// Does the surfel reach rect tile k (counter c of its view)?
+__device__ __forceinline__ bool stage_tile(const StageSurfel& u, uint32_t k, const TileMap& tm, bool small,
+                                           uint32_t& c) {
+  const uint32_t tx = u.tx0 + k % u.w, ty = u.ty0 + k / u.w;
+  c = tm.counter(tx, ty, small);
+  // the tile-relative centre exactly as the renderer stages it
+  const float fox = (float)(tx * kTile), foy = (float)(ty * kTile);
+  return reach_cell(u.q, (u.r0.x - fox) + u.r0.z, (u.r0.y - foy) + u.r0.w, 0, 0, kTile);
+}
+
+// A staged entry is (counter, rank there | tag).
+//
+// Stages up to N tiles per lane (keep[j]: tile counter c[j] is reached) of a run's lanes: the ranks by
+// returning atomics, all in flight before their results are used, and the entries packed from *slots (LDS) on.
+template <int N>
+__device__ __forceinline__ void stage_packed(const bool (&keep)[N], const uint32_t (&c)[N], uint32_t tag,
+                                             uint32_t* __restrict__ cnt, uint32_t* slots, uint2* __restrict__ out) {
+  const unsigned lane = threadIdx.x & 63u;
+  const unsigned long long lt = (1ull << lane) - 1ull;
+  uint32_t r[N];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const uint32_t k = k0 + (uint32_t)j * kGroup;
-      const uint32_t tx = u.tx0 + k % u.w, ty = u.ty0 + k / u.w;
-      t[j] = tbase + ty * tiles_x + tx;
-      // the tile-relative centre exactly as the renderer stages it
-      const float fox = (float)(tx * kTile), foy = (float)(ty * kTile);
-      keep[j] = k < ke && reach_cell(u.q, (u.r0.x - fox) + u.r0.z, (u.r0.y - foy) + u.r0.w, 0, 0, kTile);
-      r[j] = keep[j] ? atomicAdd(cnt + t[j], 1u) : 0u;
-    }
+  for (int j = 0; j < N; ++j) r[j] = keep[j] ? atomicAdd(cnt + c[j], 1u) : 0u;
+  uint32_t total = 0;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const uint32_t k = k0 + (uint32_t)j * kGroup;
-      if (k < ke) {
-        st_pos[u.o + k] = make_uint2(keep[j] ? t[j] : kNoTile, r[j]);
-        if (keep[j]) st_key[u.o + k] = u.key;
-      }
-    }
+  for (int j = 0; j < N; ++j) total += (uint32_t)__popcll(__ballot(keep[j]));
+  if (total == 0) return;
+  uint32_t base = 0;
+  if ((__ballot(true) & lt) == 0) base = atomicAdd(slots, total);
+  base = __builtin_amdgcn_readfirstlane(base);
+#pragma unroll
+  for (int j = 0; j < N; ++j) {
+    const unsigned long long b = __ballot(keep[j]);
+    if (keep[j]) out[base + (uint32_t)__popcll(b & lt)] = make_uint2(c[j], r[j] | tag);
+    base += (uint32_t)__popcll(b);
   }
 }
 
-// chunk queue entry: (index into 'visible', view << 16 | chunk); chunk c covers rect tiles
-// [kFirstTiles + c kChunkTiles, ... + kChunkTiles).  A surfel with T > kFirstTiles tiles queues
-// ceil((T - kFirstTiles) / kChunkTiles) < T / kChunkTiles chunks, so capacity / kChunkTiles + 1 entries
-// hold every queue whose rect slots fit the capacity (the staging does not run otherwise).
-__global__ __launch_bounds__(256) void k_stage(const uint16_t* __restrict__ rect, const float* __restrict__ rec,
-                                               int64_t n, int tiles_x, int tiles_per_view,
-                                               const uint32_t* __restrict__ visible,
-                                               const uint32_t* __restrict__ vstart,
-                                               const uint32_t* __restrict__ soff, uint32_t* __restrict__ cnt,
-                                               uint2* __restrict__ st_pos, uint64_t* __restrict__ st_key,
-                                               uint2* __restrict__ chunks, uint32_t* __restrict__ n_chunks,
-                                               uint32_t max_chunks, const int32_t* __restrict__ status) {
+// Rect tiles [kb, ke) of surfel u by the kGroup lanes of a group, tile kb + g + 32 j on lane g: the entries
+// packed from out[0] on; returns their number.  Four returning atomics are in flight per lane.
+__device__ __forceinline__ uint32_t stage_group(const StageSurfel& u, uint32_t kb, uint32_t ke, const TileMap& tm,
+                                                bool small, uint32_t tbase, uint32_t tag, uint32_t* __restrict__ cnt,
+                                                uint2* __restrict__ out) {
+  uint32_t at = 0;
+  const uint32_t g = threadIdx.x % kGroup;
+  const uint32_t shift = threadIdx.x & 63u & ~(uint32_t)(kGroup - 1);  // the group's lanes in its wave
+  for (uint32_t k0 = kb; k0 < ke; k0 += 4 * kGroup) {
+    uint32_t c[4] = {0, 0, 0, 0}, r[4];
+    bool keep[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const uint32_t k = k0 + g + (uint32_t)j * kGroup;
+      keep[j] = k < ke && stage_tile(u, k, tm, small, c[j]);
+      c[j] += tbase;
+      r[j] = keep[j] ? atomicAdd(cnt + c[j], 1u) : 0u;
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const uint32_t b = (uint32_t)(__ballot(keep[j]) >> shift);
+      if (keep[j]) out[at + (uint32_t)__popc(b & ((1u << g) - 1u))] = make_uint2(c[j], r[j] | tag);
+      at += (uint32_t)__popc(b);
+    }
+  }
+  return at;
+}
+
+// chunk queue entry: (index into 'visible', view << 16 | chunk, first staged slot, entries staged there by
+// k_stage_big); chunk c covers rect tiles [kFirstTiles + c kChunkTiles, ... + kChunkTiles).  A surfel with
+// T > kFirstTiles tiles queues ceil((T - kFirstTiles) / kChunkTiles) < T / kChunkTiles chunks, so
+// capacity / kChunkTiles + 1 entries hold every queue whose rect slots fit the capacity (the staging does
+// not run otherwise).  Called by the lanes of one group together.
+__device__ __forceinline__ void queue_chunks(uint32_t vis, int v, uint32_t total, uint32_t at,
+                                             uint4* __restrict__ chunks, uint32_t* __restrict__ n_chunks,
+                                             uint32_t max_chunks) {
+  const uint32_t g = threadIdx.x % kGroup;
+  const uint32_t nc = (total - kFirstTiles + kChunkTiles - 1) / kChunkTiles;
+  uint32_t base = 0;
+  if (g == 0) base = atomicAdd(n_chunks, nc);
+  base = __shfl(base, (int)(threadIdx.x & 63u & ~(uint32_t)(kGroup - 1)), 64);
+  for (uint32_t c = g; c < nc; c += kGroup)
+    if (base + c < max_chunks) chunks[base + c] = make_uint4(vis, ((uint32_t)v << 16) | c, at + c * kChunkTiles, 0u);
+}
+
+// Every visible entry's depth goes to depth[].  A short run's surfels each pack their entries at the start
+// of their own rect slots (count[entry]).  A long run's rect slots hold the lanes' entries, packed, then the
+// slots of each surfel for the groups; of its b such surfels, number k has its entries at voff[first + k]
+// and kRunBig | their count in count[first + k], and the lanes' follow at index b (when b is not all of them).
+__global__ __launch_bounds__(kStageBlock, 5) void k_stage(const uint16_t* __restrict__ rect,
+                                                       const float* __restrict__ rec, int64_t n, TileMap tm, int V,
+                                                       const int64_t* __restrict__ needed,
+                                                       const uint32_t* __restrict__ visible,
+                                                       const uint32_t* __restrict__ vstart, uint32_t* voff,
+                                                       uint32_t* __restrict__ cnt,
+                                                       uint2* __restrict__ st, uint16_t* __restrict__ count,
+                                                       float* __restrict__ depth, uint4* __restrict__ chunks,
+                                                       uint32_t* __restrict__ n_chunks, uint32_t max_chunks,
+                                                       const int32_t* __restrict__ status) {
+  __shared__ uint32_t big[kStageBlock];  // a long run's surfels for the groups
+  __shared__ uint32_t n_big, slots, own;
   const int v = blockIdx.y;
   if (*status != 0) return;
-  const uint32_t nv = vstart[v + 1] - vstart[v];
-  const uint32_t* list = visible + vstart[v];
-  const uint32_t g = threadIdx.x % kGroup;
-  const uint32_t tbase = (uint32_t)v * (uint32_t)tiles_per_view;
-  for (uint32_t e = (blockIdx.x * blockDim.x + threadIdx.x) / kGroup; e < nv;
-       e += gridDim.x * blockDim.x / kGroup) {
-    StageSurfel u;
-    stage_surfel(rect, rec, soff, n, v, list[e], u);
-    stage_range(u, tbase, tiles_x, 0u, min(u.total, kFirstTiles), g, cnt, st_pos, st_key);
-    if (u.total > kFirstTiles) {
-      const uint32_t nc = (u.total - kFirstTiles + kChunkTiles - 1) / kChunkTiles;
-      uint32_t base = 0;
-      if (g == 0) base = atomicAdd(n_chunks, nc);
-      base = __shfl(base, (int)(threadIdx.x & 63u & ~(uint32_t)(kGroup - 1)), 64);
-      for (uint32_t c = g; c < nc; c += kGroup)
-        if (base + c < max_chunks) chunks[base + c] = make_uint2(vstart[v] + e, ((uint32_t)v << 16) | c);
+  const uint32_t vs = vstart[v], nv = vstart[v + 1] - vs;
+  const uint32_t* list = visible + vs;
+  const uint32_t g = threadIdx.x % kGroup, grp = threadIdx.x / kGroup;
+  const uint32_t tbase = tm.base(v);
+  if (!small_rects(vstart, needed, V, n)) {
+    for (uint32_t e = blockIdx.x * kGroups + grp; e < nv; e += gridDim.x * kGroups) {
+      const uint32_t at = voff[vs + e];
+      const int64_t vi = (int64_t)v * n + list[e];
+      StageSurfel u;
+      stage_rect(rect, vi, u);
+      stage_surfel(rec, vi, u);
+      const uint32_t k = stage_group(u, 0u, min(u.total, kFirstTiles), tm, false, tbase, 0u, cnt, st + at);
+      if (g == 0) {
+        count[vs + e] = (uint16_t)k;
+        depth[vs + e] = u.depth;
+      }
+      if (u.total > kFirstTiles) queue_chunks(vs + e, v, u.total, at + kFirstTiles, chunks, n_chunks, max_chunks);
     }
+    return;
+  }
+  for (uint32_t e0 = blockIdx.x * kStageBlock; e0 < nv; e0 += gridDim.x * kStageBlock) {
+    const uint32_t e = e0 + threadIdx.x;
+    const bool live = e < nv;
+    if (threadIdx.x == 0) n_big = slots = own = 0u;
+    __syncthreads();
+    const int64_t vi = (int64_t)v * n + (live ? list[e] : 0u);
+    const uint32_t at = voff[vs + e0];
+    StageSurfel u;
+    u.total = 0;
+    if (live) stage_rect(rect, vi, u);
+    const bool mine = live && u.total <= kLaneTiles;
+    if (mine) {
+      stage_surfel(rec, vi, u);
+      depth[vs + e] = u.depth;
+      atomicAdd(&own, u.total);
+    } else if (live) {
+      big[atomicAdd(&n_big, 1u)] = threadIdx.x;
+    }
+    for (uint32_t k0 = 0; __ballot(mine && k0 < u.total) != 0; k0 += kLaneStep) {
+      bool keep[kLaneStep];
+      uint32_t c[kLaneStep] = {};
+#pragma unroll
+      for (int j = 0; j < kLaneStep; ++j) {
+        keep[j] = mine && k0 + j < u.total && stage_tile(u, k0 + j, tm, true, c[j]);
+        c[j] += tbase;
+      }
+      stage_packed<kLaneStep>(keep, c, threadIdx.x << kRankBits, cnt, &slots, st + at);
+    }
+    __syncthreads();
+    const uint32_t nb = n_big;
+    if (live && threadIdx.x >= nb) count[vs + e] = (uint16_t)(threadIdx.x == nb ? slots : 0u);
+    if (live && threadIdx.x == nb) voff[vs + e] = at;
+    for (uint32_t b = grp; b < nb; b += kGroups) {
+      const uint32_t eb = e0 + big[b];
+      const int64_t vb = (int64_t)v * n + list[eb];
+      stage_rect(rect, vb, u);
+      stage_surfel(rec, vb, u);
+      uint32_t to = 0;
+      if (g == 0) to = atomicAdd(&own, u.total);
+      to = at + __shfl(to, (int)(threadIdx.x & 63u & ~(uint32_t)(kGroup - 1)), 64);
+      const uint32_t k = stage_group(u, 0u, min(u.total, kFirstTiles), tm, true, tbase, big[b] << kRankBits,
+                                     cnt, st + to);
+      if (g == 0) {
+        voff[vs + e0 + b] = to;
+        count[vs + e0 + b] = (uint16_t)(kRunBig | k);
+        depth[vs + eb] = u.depth;
+      }
+      if (u.total > kFirstTiles) queue_chunks(vs + eb, v, u.total, to + kFirstTiles, chunks, n_chunks, max_chunks);
+    }
+    __syncthreads();  // the list and the counters are rewritten by the next run
   }
 }
 
 // The queued chunks of the large rects, one chunk per group.
-__global__ __launch_bounds__(256) void k_stage_big(const uint16_t* __restrict__ rect, const float* __restrict__ rec,
-                                                   int64_t n, int tiles_x, int tiles_per_view,
-                                                   const uint32_t* __restrict__ visible,
-                                                   const uint32_t* __restrict__ soff, uint32_t* __restrict__ cnt,
-                                                   uint2* __restrict__ st_pos, uint64_t* __restrict__ st_key,
-                                                   const uint2* __restrict__ chunks,
-                                                   const uint32_t* __restrict__ n_chunks, uint32_t max_chunks,
-                                                   const int32_t* __restrict__ status) {
+__global__ __launch_bounds__(kStageBlock) void k_stage_big(const uint16_t* __restrict__ rect,
+                                                           const float* __restrict__ rec, int64_t n, TileMap tm, int V,
+                                                           const int64_t* __restrict__ needed,
+                                                           const uint32_t* __restrict__ visible,
+                                                           const uint32_t* __restrict__ vstart,
+                                                           uint32_t* __restrict__ cnt,
+                                                           uint2* __restrict__ st, uint4* __restrict__ chunks,
+                                                           const uint32_t* __restrict__ n_chunks, uint32_t max_chunks,
+                                                           const int32_t* __restrict__ status) {
   if (*status != 0) return;
   const uint32_t nc = min(*n_chunks, max_chunks);
-  const uint32_t g = threadIdx.x % kGroup;
+  const bool small = small_rects(vstart, needed, V, n);
   for (uint32_t it = (blockIdx.x * blockDim.x + threadIdx.x) / kGroup; it < nc;
        it += gridDim.x * blockDim.x / kGroup) {
-    const uint2 c = chunks[it];
-    const int v = (int)(c.y >> 16);
+    const uint4 q = chunks[it];
+    const int v = (int)(q.y >> 16);
+    const int64_t vi = (int64_t)v * n + visible[q.x];
     StageSurfel u;
-    stage_surfel(rect, rec, soff, n, v, visible[c.x], u);
-    const uint32_t kb = kFirstTiles + (c.y & 0xffffu) * kChunkTiles;
-    stage_range(u, (uint32_t)v * (uint32_t)tiles_per_view, tiles_x, kb, min(u.total, kb + kChunkTiles), g, cnt,
-                st_pos, st_key);
+    stage_rect(rect, vi, u);
+    stage_surfel(rec, vi, u);
+    const uint32_t kb = kFirstTiles + (q.y & 0xffffu) * kChunkTiles;
+    const uint32_t k = stage_group(u, kb, min(u.total, kb + kChunkTiles), tm, small, tm.base(v), 0u, cnt, st + q.z);
+    if (threadIdx.x % kGroup == 0) chunks[it].w = k;
   }
 }
 
-__global__ __launch_bounds__(kScanBlock) void k_tile_scan(const uint32_t* __restrict__ cnt, int64_t m,
-                                                          uint32_t* __restrict__ ranges) {
-  __shared__ uint64_t lds[2 * kScanWaves];
-  uint64_t carry = 0;
-  for (int64_t base = 0; base < m; base += kScanChunk) {
-    const int64_t b0 = base + (int64_t)threadIdx.x * kScanItems;
-    uint64_t vals[kScanItems];
-    for (int k = 0; k < kScanItems; ++k) vals[k] = b0 + k < m ? cnt[b0 + k] : 0;
-    const uint64_t tot = block_scan(vals, lds);
-    for (int k = 0; k < kScanItems; ++k)
-      if (b0 + k < m) ranges[b0 + k] = (uint32_t)(vals[k] + carry);
-    carry += tot;
-  }
-  if (threadIdx.x == 0) ranges[m] = (uint32_t)carry;
-}
-
-// Multi-workgroup form of the tile scan for many tiles: chunk sums, then (after k_scan_top) each chunk
-// scanned with its carry.
-__global__ __launch_bounds__(kScanBlock) void k_u32_sums(const uint32_t* __restrict__ a, int64_t m,
-                                                         uint64_t* __restrict__ sums) {
+// Multi-workgroup form of the tile scan for more than kScanChunk tiles: chunk sums, then each chunk scanned
+// with the sum of those before it (us, two launches against one workgroup: 32,400 tiles 31 -> 10, 53,600
+// tiles 50 -> 10).
+__global__ __launch_bounds__(kScanBlock) void k_tile_sums(const uint32_t* __restrict__ cnt, TileMap tm, int V,
+                                                          int64_t n, const uint32_t* __restrict__ vstart,
+                                                          const int64_t* __restrict__ needed,
+                                                          uint64_t* __restrict__ sums) {
   __shared__ uint64_t lds[2 * kScanWaves];
   const int64_t base = (int64_t)blockIdx.x * kScanChunk;
+  const bool small = small_rects(vstart, needed, V, n);
   uint64_t c = 0;
   for (int k = 0; k < kScanItems; ++k) {
     const int64_t idx = base + (int64_t)k * kScanBlock + threadIdx.x;
-    if (idx < m) c += a[idx];
+    if (idx < tm.m) c += cnt[tm.counter_of((uint32_t)idx, small)];
   }
   const uint64_t t = block_sum(c, lds);
   if (threadIdx.x == 0) sums[blockIdx.x] = t;
 }
 
-__global__ __launch_bounds__(kScanBlock) void k_u32_apply(const uint32_t* __restrict__ a, int64_t m,
-                                                          const uint64_t* __restrict__ sums,
-                                                          const uint64_t* __restrict__ total,
-                                                          uint32_t* __restrict__ out) {
-  __shared__ uint64_t lds[2 * kScanWaves];
-  const uint64_t carry = sums[blockIdx.x];
+// (column-major counters become their first slots; row-major ones have them in ranges)
+__global__ __launch_bounds__(kScanBlock) void k_tile_apply(uint32_t* __restrict__ cnt, TileMap tm, int V, int64_t n,
+                                                           const uint32_t* __restrict__ vstart,
+                                                           const int64_t* __restrict__ needed,
+                                                           const uint64_t* __restrict__ sums,
+                                                           uint32_t* __restrict__ ranges) {
+  __shared__ uint64_t lds[2 * kScanWaves], red[2][kScanWaves], tot[2];
+  {
+    // the totals of the chunks before this one, and of all
+    uint64_t before = 0, all = 0;
+    for (uint32_t j = threadIdx.x; j < gridDim.x; j += kScanBlock) {
+      const uint64_t x = sums[j];
+      before += j < blockIdx.x ? x : 0;
+      all += x;
+    }
+    before = block_sum(before, red[0]);
+    all = block_sum(all, red[1]);
+    if (threadIdx.x == 0) {
+      tot[0] = before;
+      tot[1] = all;
+    }
+    __syncthreads();
+  }
+  const uint64_t carry = tot[0];
   const int64_t base = (int64_t)blockIdx.x * kScanChunk + (int64_t)threadIdx.x * kScanItems;
   uint64_t vals[kScanItems];
-  for (int k = 0; k < kScanItems; ++k) vals[k] = base + k < m ? a[base + k] : 0;
+  const bool small = small_rects(vstart, needed, V, n);
+  uint32_t at[kScanItems];
+  for (int k = 0; k < kScanItems; ++k) {
+    at[k] = base + k < tm.m ? tm.counter_of((uint32_t)(base + k), small) : 0u;
+    vals[k] = base + k < tm.m ? cnt[at[k]] : 0;
+  }
   block_scan(vals, lds);
   for (int k = 0; k < kScanItems; ++k)
-    if (base + k < m) out[base + k] = (uint32_t)(vals[k] + carry);
-  if (blockIdx.x == 0 && threadIdx.x == 0) out[m] = (uint32_t)*total;
+    if (base + k < tm.m) {
+      ranges[base + k] = (uint32_t)(vals[k] + carry);
+      if (small) cnt[at[k]] = (uint32_t)(vals[k] + carry);
+    }
+  if (blockIdx.x == 0 && threadIdx.x == 0) ranges[tm.m] = (uint32_t)tot[1];
 }
 
-__global__ __launch_bounds__(256) void k_place(const uint32_t* __restrict__ soff_total,
-                                               const uint2* __restrict__ st_pos, const uint64_t* __restrict__ st_key,
-                                               const uint32_t* __restrict__ ranges, uint64_t* __restrict__ keys,
-                                               const int32_t* __restrict__ status) {
+// Staged entries to their tiles: a group per surfel of short runs, a workgroup per long run, then a group
+// per queued chunk.
+__global__ __launch_bounds__(kStageBlock) void k_place(const uint32_t* __restrict__ visible,
+                                                       const uint32_t* __restrict__ vstart, int V, int64_t n,
+                                                       const int64_t* __restrict__ needed,
+                                                       const uint32_t* __restrict__ voff,
+                                                       const uint16_t* __restrict__ count,
+                                                       const float* __restrict__ depth, const uint2* __restrict__ st,
+                                                       const uint32_t* __restrict__ cnt, int sets,
+                                                       const uint32_t* __restrict__ ranges,
+                                                       const uint4* __restrict__ chunks,
+                                                       const uint32_t* __restrict__ n_chunks, uint32_t max_chunks,
+                                                       uint64_t* __restrict__ keys, const int32_t* __restrict__ status) {
+  __shared__ uint64_t key[kStageBlock];
+  __shared__ uint32_t at_s[kStageBlock], cnt_s[kStageBlock];
+  __shared__ uint32_t n_big;
   if (*status != 0) return;
-  const uint32_t K = *soff_total;
-  for (uint32_t e = blockIdx.x * blockDim.x + threadIdx.x; e < K; e += gridDim.x * blockDim.x) {
-    const uint2 tp = st_pos[e];
-    if (tp.x != kNoTile) keys[ranges[tp.x] + tp.y] = st_key[e];
+  const int v = blockIdx.y;
+  const uint32_t vs = vstart[v], nv = vstart[v + 1] - vs;
+  const uint32_t g = threadIdx.x % kGroup, grp = threadIdx.x / kGroup;
+  const bool small = small_rects(vstart, needed, V, n);
+  const uint32_t* __restrict__ first = sets == 1 && !small ? ranges : cnt;  // first slot of each counter
+  auto key_of = [&](uint32_t e) { return (uint64_t)__float_as_uint(depth[e]) << 32 | visible[e]; };
+  if (!small) {
+    for (uint32_t e = blockIdx.x * kGroups + grp; e < nv; e += gridDim.x * kGroups) {
+      const uint32_t k = count[vs + e];
+      const uint2* p = st + voff[vs + e];
+      const uint64_t x = key_of(vs + e);
+      for (uint32_t j = g; j < k; j += kGroup) keys[first[p[j].x] + p[j].y] = x;
+    }
+  } else {
+    auto put = [&](const uint2& q) {
+      keys[first[q.x] + (q.y & ((1u << kRankBits) - 1u))] = key[q.y >> kRankBits];
+    };
+    for (uint32_t e0 = blockIdx.x * kStageBlock; e0 < nv; e0 += gridDim.x * kStageBlock) {
+      const uint32_t e = vs + e0 + threadIdx.x;
+      const bool live = e0 + threadIdx.x < nv;
+      if (threadIdx.x == 0) n_big = 0u;
+      __syncthreads();
+      if (live) {
+        key[threadIdx.x] = key_of(e);
+        at_s[threadIdx.x] = voff[e];
+        cnt_s[threadIdx.x] = count[e];
+      }
+      const unsigned long long flagged = __ballot(live && (cnt_s[threadIdx.x] & kRunBig) != 0u);
+      if ((threadIdx.x & 63u) == 0u && flagged) atomicAdd(&n_big, (uint32_t)__popcll(flagged));
+      __syncthreads();
+      const uint32_t nb = n_big;
+      if (e0 + nb < nv && nb < kStageBlock) {
+        const uint2* p = st + at_s[nb];
+        const uint32_t k = cnt_s[nb];
+        for (uint32_t j = threadIdx.x; j < k; j += kStageBlock) put(p[j]);
+      }
+      for (uint32_t b = grp; b < nb; b += kGroups) {
+        const uint2* p = st + at_s[b];
+        const uint32_t k = cnt_s[b] & (kRunBig - 1u);
+        for (uint32_t j = g; j < k; j += kGroup) put(p[j]);
+      }
+      __syncthreads();
+    }
+  }
+  const uint32_t nc = min(*n_chunks, max_chunks);
+  for (uint32_t it = ((blockIdx.y * gridDim.x + blockIdx.x) * kStageBlock + threadIdx.x) / kGroup; it < nc;
+       it += gridDim.y * gridDim.x * kGroups) {
+    const uint4 q = chunks[it];
+    const uint64_t x = key_of(q.x);
+    for (uint32_t j = g; j < q.w; j += kGroup) keys[first[st[q.z + j].x] + st[q.z + j].y] = x;
   }
 }
 
@@ -716,6 +949,7 @@ __global__ __launch_bounds__(kOrdChunk) void k_order_hist(const uint32_t* __rest
 __global__ __launch_bounds__(64) void k_order_scan(uint32_t* __restrict__ hist, int nc) {
   const int k = threadIdx.x;  // bucket
   uint32_t tot = 0;
+#pragma unroll 16
   for (int c = 0; c < nc; ++c) tot += hist[(int64_t)c * kOrdBuckets + k];
   // inclusive suffix sum over the buckets k and above, then exclusive
   uint32_t x = tot;
@@ -725,6 +959,7 @@ __global__ __launch_bounds__(64) void k_order_scan(uint32_t* __restrict__ hist, 
     if (k + d < 64) x += y;
   }
   uint32_t run = x - tot;
+#pragma unroll 16
   for (int c = 0; c < nc; ++c) {
     const uint32_t v = hist[(int64_t)c * kOrdBuckets + k];
     hist[(int64_t)c * kOrdBuckets + k] = run;
@@ -760,16 +995,22 @@ __global__ __launch_bounds__(kOrdChunk) void k_order_place(const uint32_t* __res
 }
 
 // One workgroup for up to kScanChunk tiles of at most kMaxViews views (the common single-view case):
-// the tile scan of k_tile_scan and the launch order of k_order_hist / k_order_scan / k_order_place in
+// the tile scan and the launch order of k_order_hist / k_order_scan / k_order_place in
 // one launch, the same results.  Wave w owns the contiguous tiles [w per, (w + 1) per) and loads their
 // counts once, all at the same time (lane l holds tiles w per + 64 k + l); the scan runs over those
 // registers (wave scans in k order, one LDS exchange of the 16 wave totals); the order takes LDS counts
 // per (wave, bucket), one exchange of the 16 x 64 counts into first slots, and a placing pass with
 // stable ranks from the lanes that share a bucket (same_bucket).
 
-__global__ __launch_bounds__(kScanBlock) void k_tile_scan_order(const uint32_t* __restrict__ cnt, int m,
+// A tile's count is the sum over its counters (one per set), which become their first slots (unless they are
+// one set in row order: ranges holds those).  order may be null.
+__global__ __launch_bounds__(kScanBlock) void k_tile_scan_order(uint32_t* __restrict__ cnt, TileMap tm, int V,
+                                                                int64_t n, const uint32_t* __restrict__ vstart,
+                                                                const int64_t* __restrict__ needed,
                                                                 uint32_t* __restrict__ ranges,
                                                                 uint32_t* __restrict__ order) {
+  const int m = (int)tm.m;
+  const bool small = small_rects(vstart, needed, V, n);
   __shared__ uint32_t wtot[kScanWaves];
   __shared__ uint32_t wc[kScanWaves][kOrdBuckets];
   const int t = threadIdx.x;
@@ -777,11 +1018,22 @@ __global__ __launch_bounds__(kScanBlock) void k_tile_scan_order(const uint32_t* 
   // kScanWaves * per >= m, per a multiple of 64 and at most 64 kScanItems (m <= kScanChunk)
   const int per = ((m + kScanBlock - 1) / kScanBlock) * 64;
   const int i0 = w * per, i1 = min(m, i0 + per);
-  uint32_t c[kScanItems];
+  uint32_t c[kScanItems], at[kScanItems];
 #pragma unroll
   for (int k = 0; k < kScanItems; ++k) {
     const int i = i0 + 64 * k + lane;
-    c[k] = 64 * k < per && i < i1 ? cnt[i] : 0u;
+    const bool in = 64 * k < per && i < i1;
+    at[k] = in ? tm.counter_of((uint32_t)i, small) : 0u;
+    c[k] = in ? cnt[at[k]] : 0u;
+  }
+  if (tm.sets > 1) {
+    // (at most kSetsMaxTiles tiles)
+#pragma unroll
+    for (int k = 0; k < kSetsMaxTiles / kScanBlock; ++k) {
+      if (64 * k >= per || i0 + 64 * k + lane >= i1) continue;
+#pragma unroll
+      for (int q = 1; q < kSets; ++q) c[k] += cnt[q * m + at[k]];
+    }
   }
   // tile scan: exclusive prefix sums within the wave's tiles, then the wave offsets
   uint32_t ex[kScanItems];
@@ -805,9 +1057,26 @@ __global__ __launch_bounds__(kScanBlock) void k_tile_scan_order(const uint32_t* 
 #pragma unroll
   for (int k = 0; k < kScanItems; ++k) {
     const int i = i0 + 64 * k + lane;
-    if (64 * k < per && i < i1) ranges[i] = off + ex[k];
+    if (64 * k >= per || i >= i1) continue;
+    ranges[i] = off + ex[k];
+    if (tm.sets == 1 && small) cnt[at[k]] = off + ex[k];
+  }
+  if (tm.sets > 1) {
+#pragma unroll
+    for (int k = 0; k < kSetsMaxTiles / kScanBlock; ++k) {
+      if (64 * k >= per || i0 + 64 * k + lane >= i1) continue;
+      uint32_t x[kSets], first = off + ex[k];
+#pragma unroll
+      for (int q = 0; q < kSets; ++q) x[q] = cnt[q * m + at[k]];
+#pragma unroll
+      for (int q = 0; q < kSets; ++q) {
+        cnt[q * m + at[k]] = first;
+        first += x[q];
+      }
+    }
   }
   if (t == 0) ranges[m] = total;
+  if (!order) return;
   // counts per (wave, bucket), by LDS atomics that return nothing (no wait between the rows)
 #pragma unroll
   for (int k = 0; k < kScanItems; ++k) {
@@ -849,30 +1118,35 @@ __global__ __launch_bounds__(kScanBlock) void k_tile_scan_order(const uint32_t* 
 static int64_t scan_blocks(int64_t m) { return (m + cgv2::kScanChunk - 1) / cgv2::kScanChunk; }
 static int64_t surf_blocks(int64_t m) { return (m + cgv2::kSurfChunk - 1) / cgv2::kSurfChunk; }
 
+static int counter_sets(int64_t m) { return m <= cgv2::kSetsMaxTiles ? cgv2::kSets : 1; }
+
 size_t cgv2_binsort_ws_layout(int64_t capacity, int V, int tiles, int64_t n, size_t* off) {
-  // off: [0] tile counters (u32, m) followed by the big-list and chunk-queue counts, [1] chunk sums of the surfel
-  //      scan (2 x u64 arrays), [2] big_list (u32, m), [3] scan totals (u64 x 2), [4] keys (u64,
-  //      capacity), [5] staged keys / merge scratch (u64, capacity), [6] staged (tile, rank) (u32 x 2,
-  //      capacity), [7] surfel offsets (u32, V n + 1), [8] chunk sums of the tile scan (u64)
+  // off: [0] tile counters (u32, m, kSets times for few tiles) followed by the big-list and chunk-queue
+  //      counts, [1] chunk sums of the surfel scan (2 x u64 arrays), [2] big_list (u32, m), [3] scan totals
+  //      (u64 x 2), [4] keys (u64, capacity), [5] staged entries (8 B, capacity; afterwards the merge
+  //      scratch), [6], [7], [11] per visible entry: staged count (u16), first slot (u32), depth (f32),
+  //      [8] chunk sums of the tile scan (u64)
   const int64_t m = (int64_t)V * tiles;
   const int64_t vn = (int64_t)V * n;
   const int64_t nsb = surf_blocks(vn > 0 ? vn : 1);
+  const int64_t vis = std::min(vn, capacity);  // most visible surfels that are staged
   size_t o = 0;
   auto take = [&](size_t bytes) { size_t r = o; o += (bytes + 255) & ~(size_t)255; return r; };
-  off[0] = take(4 * (size_t)(m + 2));
+  off[0] = take(4 * (size_t)(m * counter_sets(m) + 2));
   off[1] = take(16 * (size_t)(nsb + 1));
   off[2] = take(4 * (size_t)m);
   off[3] = take(64);
   off[4] = take(8 * (size_t)capacity);
   off[5] = take(8 * (size_t)capacity);
-  off[6] = take(8 * (size_t)capacity);
-  off[7] = take(4 * (size_t)(vn + 1));
+  off[6] = take(2 * (size_t)vis);
+  off[7] = take(4 * (size_t)(vis + 1));
   off[8] = take(8 * (size_t)(scan_blocks(m) + 1));
   // [9] per-chunk bucket counts of the launch order (one view chunk at a time)
   const int64_t per = (int64_t)std::min(V, cgv2::kMaxViews) * tiles;
   off[9] = take(4 * (size_t)cgv2::kOrdBuckets * (size_t)((per + cgv2::kOrdChunk - 1) / cgv2::kOrdChunk + 1));
   // [10] the chunk queue of the large rects (see k_stage)
-  off[10] = take(8 * (size_t)(capacity / cgv2::kChunkTiles + 1));
+  off[10] = take(16 * (size_t)(capacity / cgv2::kChunkTiles + 1));
+  off[11] = take(4 * (size_t)vis);
   return o;
 }
 
@@ -882,67 +1156,76 @@ hipError_t cgv2_launch_bin_sort(const cgv2_proj& p, int64_t n, int V, int tiles_
   const int tiles = tiles_x * tiles_y;
   const int64_t m = (int64_t)V * tiles;
   const int64_t vn = (int64_t)V * n;
+  const int sets = counter_sets(m);
   size_t off[kBinsortOffs];
   cgv2_binsort_ws_layout(b.capacity, V, tiles, n, off);
   char* w = (char*)ws;
   uint32_t* cnt = (uint32_t*)(w + off[0]);
-  uint32_t* big_count = cnt + m;
+  uint32_t* big_count = cnt + m * sets;
   const int64_t nsb = surf_blocks(vn > 0 ? vn : 1);
   uint64_t* sums_cnt = (uint64_t*)(w + off[1]);
   uint64_t* sums_vis = sums_cnt + nsb + 1;
   uint32_t* big_list = (uint32_t*)(w + off[2]);
   uint64_t* totals = (uint64_t*)(w + off[3]);
   uint64_t* keys = (uint64_t*)(w + off[4]);
-  uint64_t* stk = (uint64_t*)(w + off[5]);
-  uint2* stp = (uint2*)(w + off[6]);
-  uint32_t* soff = (uint32_t*)(w + off[7]);
-  uint32_t* n_chunks = cnt + m + 1;
-  uint2* chunks = (uint2*)(w + off[10]);
+  uint2* staged = (uint2*)(w + off[5]);
+  uint16_t* count = (uint16_t*)(w + off[6]);
+  float* depth = (float*)(w + off[11]);
+  uint32_t* voff = (uint32_t*)(w + off[7]);
+  uint32_t* n_chunks = big_count + 1;
+  uint4* chunks = (uint4*)(w + off[10]);
   const uint32_t max_chunks = (uint32_t)std::min<int64_t>(b.capacity / kChunkTiles + 1, 0xffffffffll);
+  TileMap tm;
+  tm.tiles_x = (uint32_t)tiles_x;
+  tm.tiles_y = (uint32_t)tiles_y;
+  tm.m = (uint32_t)m;
+  tm.sets = sets;
+  // workgroups per view of the staging and the placement: up to 8192, one run each (a multiple of kSets)
+  const unsigned runs =
+      (unsigned)std::min<int64_t>((std::max<int64_t>(n, 1) + kGroups * kSets - 1) / (kGroups * kSets) * kSets, 8192);
   if (n > 0) {
-    // surfel offsets, visible lists (consumed by the staging here and by the reverse pass), total and
+    // first rect slots and visible lists (consumed by the staging here and by the reverse pass), total and
     // overflow check; the tile counters and the big-list count are zeroed on the way
     hipLaunchKernelGGL(k_surfel_sums, dim3((unsigned)nsb), dim3(kSurfBlock), 0, st, p.rect, vn, sums_cnt, sums_vis,
-                       cnt, m + 2);
+                       cnt, m * sets + 2);
     // up to kSurfLocal chunks each apply workgroup adds up the chunk sums before it itself
     const int local_nsb = nsb <= kSurfLocal ? (int)nsb : 0;
     if (!local_nsb) hipLaunchKernelGGL(k_scan_top, dim3(2), dim3(kScanBlock), 0, st, sums_cnt, sums_vis, nsb, totals);
     hipLaunchKernelGGL(k_surfel_apply, dim3((unsigned)nsb), dim3(kSurfBlock), 0, st, p.rect, vn, n, sums_cnt,
-                       sums_vis, totals, local_nsb, soff, p.visible, p.visible_start, V, b.capacity, b.status,
-                       b.needed);
-    const unsigned blocks = (unsigned)std::min<int64_t>((n * kGroup + 255) / 256, 8192);
-    hipLaunchKernelGGL(k_stage, dim3(blocks, (unsigned)V), dim3(256), 0, st, p.rect, p.rec, n, tiles_x, tiles,
-                       p.visible, p.visible_start, soff, cnt, stp, stk, chunks, n_chunks, max_chunks, b.status);
-    hipLaunchKernelGGL(k_stage_big, dim3(1024), dim3(256), 0, st, p.rect, p.rec, n, tiles_x, tiles, p.visible, soff,
-                       cnt, stp, stk, chunks, n_chunks, max_chunks, b.status);
+                       sums_vis, totals, local_nsb, voff, std::min(vn, b.capacity), p.visible, p.visible_start, V,
+                       b.capacity, b.status, b.needed);
+    hipLaunchKernelGGL(k_stage, dim3(runs, (unsigned)V), dim3(kStageBlock), 0, st, p.rect, p.rec, n, tm, V, b.needed,
+                       p.visible, p.visible_start, voff, cnt, staged, count, depth, chunks, n_chunks,
+                       max_chunks, b.status);
+    hipLaunchKernelGGL(k_stage_big, dim3(1024), dim3(kStageBlock), 0, st, p.rect, p.rec, n, tm, V, b.needed,
+                       p.visible, p.visible_start, cnt, staged, chunks, n_chunks, max_chunks, b.status);
   } else {
     // no surfels: empty lists, zero intersections
-    hipLaunchKernelGGL(k_fill<uint32_t>, dim3((unsigned)std::min<int64_t>((m + 257) / 256, 65535)), dim3(256), 0, st,
-                       cnt, m + 2, 0u);
+    hipLaunchKernelGGL(k_fill<uint32_t>, dim3((unsigned)std::min<int64_t>((m * sets + 257) / 256, 65535)), dim3(256),
+                       0, st, cnt, m * sets + 2, 0u);
     hipLaunchKernelGGL(k_fill<uint32_t>, dim3(1), dim3(256), 0, st, p.visible_start, (int64_t)V + 1, 0u);
-    hipLaunchKernelGGL(k_fill<uint32_t>, dim3(1), dim3(256), 0, st, soff, (int64_t)1, 0u);
     hipLaunchKernelGGL(k_fill<int64_t>, dim3(1), dim3(256), 0, st, b.needed, (int64_t)1, (int64_t)0);
   }
   const int64_t nbt = scan_blocks(m);
   const bool fused_order = b.order && m <= kScanChunk && V <= kMaxViews;
-  if (fused_order) {
-    hipLaunchKernelGGL(k_tile_scan_order, dim3(1), dim3(kScanBlock), 0, st, cnt, (int)m, b.ranges, b.order);
-  } else if (nbt <= 16) {
-    hipLaunchKernelGGL(k_tile_scan, dim3(1), dim3(kScanBlock), 0, st, cnt, m, b.ranges);
+  if (nbt <= 1) {
+    hipLaunchKernelGGL(k_tile_scan_order, dim3(1), dim3(kScanBlock), 0, st, cnt, tm, V, n, p.visible_start,
+                       b.needed, b.ranges,
+                       fused_order ? b.order : nullptr);
   } else {
     uint64_t* ts = (uint64_t*)(w + off[8]);
-    hipLaunchKernelGGL(k_u32_sums, dim3((unsigned)nbt), dim3(kScanBlock), 0, st, cnt, m, ts);
-    hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(kScanBlock), 0, st, ts, ts, nbt, totals + 2);
-    hipLaunchKernelGGL(k_u32_apply, dim3((unsigned)nbt), dim3(kScanBlock), 0, st, cnt, m, ts, totals + 2, b.ranges);
+    hipLaunchKernelGGL(k_tile_sums, dim3((unsigned)nbt), dim3(kScanBlock), 0, st, cnt, tm, V, n,
+                       p.visible_start, b.needed, ts);
+    hipLaunchKernelGGL(k_tile_apply, dim3((unsigned)nbt), dim3(kScanBlock), 0, st, cnt, tm, V, n,
+                       p.visible_start, b.needed, ts, b.ranges);
   }
-  // one staged slot per thread up to 4 M slots (each slot is a chain of dependent loads); the total is
-  // only known on the device, so the grid follows the capacity and the surplus threads exit at once
-  const unsigned place_blocks = (unsigned)std::min<int64_t>(std::max<int64_t>((b.capacity + 255) / 256, 1), 16384);
-  hipLaunchKernelGGL(k_place, dim3(place_blocks), dim3(256), 0, st, soff + vn, stp, stk, b.ranges, keys, b.status);
+  hipLaunchKernelGGL(k_place, dim3(runs, (unsigned)V), dim3(kStageBlock), 0, st, p.visible, p.visible_start, V, n,
+                     b.needed, voff,
+                     count, depth, staged, cnt, sets, b.ranges, chunks, n_chunks, max_chunks, keys, b.status);
   hipLaunchKernelGGL(k_sort_wave, dim3((unsigned)((m + 3) / 4)), dim3(256), 0, st, b.ranges, (int)m, keys, b.ids,
                      big_list, big_count, b.status);
-  hipLaunchKernelGGL(k_sort_big, dim3(256), dim3(1024), 0, st, b.ranges, keys, stk, b.ids, big_list, big_count,
-                     b.status);
+  hipLaunchKernelGGL(k_sort_big, dim3(256), dim3(1024), 0, st, b.ranges, keys, (uint64_t*)staged, b.ids, big_list,
+                     big_count, b.status);
   if (b.order && !fused_order) {
     uint32_t* hist = (uint32_t*)(w + off[9]);
     for (int v0 = 0; v0 < V; v0 += kMaxViews) {
