@@ -13,9 +13,10 @@
 //                 ranges and each counter's first slot; for at most kMaxViews views also the launch order
 //                 (k_tile_sums / k_tile_apply and the multi-workgroup order kernels otherwise)
 //   k_place       a workgroup per run: keys[first slot of the counter + rank] = key (no atomics)
-//   k_sort_wave   one wave per tile: bitonic sort of lists up to kWaveSort entries in registers
-//   k_sort_big    longer lists, up to kBig entries in 128 KB of LDS; longer still are sorted in kBig
-//                 chunks and merged in global memory by rank (binary search)
+//   k_sort_wave   one wave per tile: bitonic sort of lists up to kWaveSort entries in registers; a longer
+//                 list is cut into equal chunks of at most kWaveSort, one wave each
+//   k_merge       one workgroup per chunk: each key's place among the other chunks of its list (binary
+//                 searches in LDS) gives its slot
 // (depth bits, id) is unique within a tile, so the order in which the atomics hand out ranks does not
 // matter: the result is deterministic and bit-exact.  HBM traffic is about 16 B staged + 16 B read +
 // 8 B placed + 8 B read + 4 B written per listed entry, nothing per rect tile out of reach.
@@ -26,7 +27,24 @@
 
 namespace cgv2 {
 
-constexpr int kBig = 16384;    // entries sorted in LDS by k_sort_big (128 KB)
+constexpr int kWaveSort = 1024;  // longest list one wave sorts in its registers (16 keys per lane)
+
+// The chunks of lists longer than kWaveSort, as (tile, chunk): a list of length len in chunks of equal size
+// (the last one shorter), as few as hold at most kWaveSort entries each.  Each such list holds more than
+// kWaveSort entries, so capacity / (kWaveSort / 2) + 1 items hold all chunks.
+struct SortItems {
+  uint2* item;
+  uint32_t* count;
+};
+__device__ __forceinline__ uint32_t chunk_size(uint32_t len) {
+  const uint32_t nc = (len + kWaveSort - 1) / kWaveSort;
+  return (len + nc - 1) / nc;
+}
+__device__ __forceinline__ uint32_t chunk_count(uint32_t len) {
+  const uint32_t cs = chunk_size(len);
+  return (len + cs - 1) / cs;
+}
+
 constexpr int kScanBlock = 1024;
 constexpr int kScanItems = 8;  // elements per thread per scan block
 constexpr int kScanChunk = kScanBlock * kScanItems;
@@ -80,6 +98,27 @@ __device__ __forceinline__ uint32_t wave_scan_u32(uint32_t x) {
   x += dpp_u32<0x142, 0xa>(x);  // row_bcast:15
   x += dpp_u32<0x143, 0xc>(x);  // row_bcast:31
   return x;
+}
+
+// Appends the chunks of the long lists among a lane's N tiles (tile[k] of length len[k]) with one atomic per
+// wave.  Every lane of the wave must call it.
+template <int N>
+__device__ __forceinline__ void list_items(const SortItems& it, const uint32_t (&tile)[N], const uint32_t (&len)[N]) {
+  uint32_t mine = 0;
+#pragma unroll
+  for (int k = 0; k < N; ++k) mine += len[k] > (uint32_t)kWaveSort ? chunk_count(len[k]) : 0u;
+  const uint32_t inc = wave_scan_u32(mine);
+  const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)inc, 63);
+  if (total == 0) return;
+  uint32_t base = 0;
+  if ((threadIdx.x & 63u) == 0u) base = atomicAdd(it.count, total);
+  uint2* out = it.item + (uint32_t)__builtin_amdgcn_readfirstlane((int)base) + inc - mine;
+#pragma unroll
+  for (int k = 0; k < N; ++k) {
+    if (len[k] <= (uint32_t)kWaveSort) continue;
+    const uint32_t nc = chunk_count(len[k]);
+    for (uint32_t c = 0; c < nc; ++c) *out++ = make_uint2(tile[k], c);
+  }
 }
 
 // the value of lane 63 (a wave total after wave_scan_u32)
@@ -595,7 +634,7 @@ __global__ __launch_bounds__(kScanBlock) void k_tile_sums(const uint32_t* __rest
 // (column-major counters become their first slots; row-major ones have them in ranges)
 __global__ __launch_bounds__(kScanBlock) void k_tile_apply(uint32_t* __restrict__ cnt, TileMap tm, int V, int64_t n,
                                                            const uint32_t* __restrict__ vstart,
-                                                           const int64_t* __restrict__ needed,
+                                                           const int64_t* __restrict__ needed, SortItems items,
                                                            const uint64_t* __restrict__ sums,
                                                            uint32_t* __restrict__ ranges) {
   __shared__ uint64_t lds[2 * kScanWaves], red[2][kScanWaves], tot[2];
@@ -624,6 +663,12 @@ __global__ __launch_bounds__(kScanBlock) void k_tile_apply(uint32_t* __restrict_
     at[k] = base + k < tm.m ? tm.counter_of((uint32_t)(base + k), small) : 0u;
     vals[k] = base + k < tm.m ? cnt[at[k]] : 0;
   }
+  uint32_t tile[kScanItems], len[kScanItems];
+  for (int k = 0; k < kScanItems; ++k) {
+    tile[k] = (uint32_t)(base + k);
+    len[k] = (uint32_t)vals[k];
+  }
+  list_items(items, tile, len);
   block_scan(vals, lds);
   for (int k = 0; k < kScanItems; ++k)
     if (base + k < tm.m) {
@@ -703,37 +748,12 @@ __global__ __launch_bounds__(kStageBlock) void k_place(const uint32_t* __restric
   }
 }
 
-// In-LDS bitonic sort of 'len' keys padded to the next power of two 'p' with UINT64_MAX.
-template <int NT>
-__device__ __forceinline__ void lds_bitonic(uint64_t* s, int p) {
-  for (int k = 2; k <= p; k <<= 1) {
-    for (int j = k >> 1; j > 0; j >>= 1) {
-      for (int t = threadIdx.x; t < (p >> 1); t += NT) {
-        // index of the lower element of pair t at distance j
-        const int i = ((t & ~(j - 1)) << 1) | (t & (j - 1));
-        const int l = i | j;
-        const bool up = (i & k) == 0;
-        const uint64_t a = s[i], b = s[l];
-        if ((a > b) == up) { s[i] = b; s[l] = a; }
-      }
-      __syncthreads();
-    }
-  }
-}
-
-__device__ __forceinline__ int next_pow2(int x) {
-  int p = 1;
-  while (p < x) p <<= 1;
-  return p;
-}
-
 // ---- per-tile sort of up to kWaveSort keys in one wave's registers ----------------------------------
 // A bitonic network over 64 E keys, E per lane in blocked order (key x = E lane + e).  Steps whose partner
 // distance j is below E pair two registers of a lane; the others pair register e of lanes l and l ^ j / E,
 // exchanged with DPP (distances 1, 2, 4, 8) or the gfx950 row-swap instructions (16, 32), so the sort
 // touches neither LDS nor a barrier.  A compare-exchange keeps the minimum where the lane holds the
 // lower index of an ascending pair or the upper one of a descending pair.
-constexpr int kWaveSort = 1024;  // longest list sorted in registers (E = 16)
 
 // value of lane l ^ D for D = 1, 2, 4, 8 (DPP within rows of 16)
 template <int D>
@@ -802,11 +822,11 @@ __device__ __forceinline__ void wave_bitonic(uint64_t (&v)[E], unsigned lane) {
   if constexpr (K < 64 * E) wave_bitonic<E, 2 * K>(v, lane);
 }
 
-// keys[a, a + len) sorted by one wave (len <= 64 E), ids written in order; the tail is padded with the
-// largest key
-template <int E>
-__device__ __forceinline__ void sort_list_wave(const uint64_t* __restrict__ keys, uint32_t* __restrict__ ids,
-                                               uint32_t a, int len, unsigned lane) {
+// keys[a, a + len) sorted by one wave (len <= 64 E): the ids written in order, or (kBack) the keys; the
+// tail is padded with the largest key
+template <int E, bool kBack>
+__device__ __forceinline__ void sort_list_wave(uint64_t* keys, uint32_t* __restrict__ ids, uint32_t a, int len,
+                                               unsigned lane) {
   uint64_t v[E];
 #pragma unroll
   for (int e = 0; e < E; ++e) {
@@ -817,91 +837,100 @@ __device__ __forceinline__ void sort_list_wave(const uint64_t* __restrict__ keys
 #pragma unroll
   for (int e = 0; e < E; ++e) {
     const int x = E * (int)lane + e;
-    if (x < len) ids[a + x] = (uint32_t)v[e];
+    if (x >= len) continue;
+    if (kBack) keys[a + x] = v[e];
+    else ids[a + x] = (uint32_t)v[e];
   }
 }
 
-// One wave per tile: lists up to kWaveSort entries are sorted in registers with the smallest E that
-// holds them; longer ones go to big_list for k_sort_big.
-__global__ __launch_bounds__(256) void k_sort_wave(const uint32_t* __restrict__ ranges, int num_tiles,
-                                                   const uint64_t* __restrict__ keys, uint32_t* __restrict__ ids,
-                                                   uint32_t* __restrict__ big_list, uint32_t* __restrict__ big_count,
-                                                   const int32_t* __restrict__ status) {
-  const int t = (int)(blockIdx.x * 4u + (threadIdx.x >> 6));
-  if (t >= num_tiles || *status != 0) return;
+// One wave per tile for lists up to kWaveSort entries, with the smallest E that holds them; the waves of
+// the workgroups past the tiles sort the chunks of the longer lists (the keys stay in place for k_merge).
+__global__ __launch_bounds__(256, 5) void k_sort_wave(const uint32_t* __restrict__ ranges, int num_tiles,
+                                                      SortItems items, uint64_t* keys, uint32_t* __restrict__ ids,
+                                                      const int32_t* __restrict__ status) {
+  if (*status != 0) return;
   const unsigned lane = threadIdx.x & 63u;
-  const uint32_t a = ranges[t], b = ranges[t + 1];
-  const int len = (int)(b - a);
-  if (len == 0) return;
-  if (len > kWaveSort) {
-    if (lane == 0) big_list[atomicAdd(big_count, 1u)] = (uint32_t)t;
+  const uint32_t t = blockIdx.x * 4u + (threadIdx.x >> 6);
+  const uint32_t first = ((uint32_t)num_tiles + 3u) / 4u * 4u;  // the tiles' waves
+  if (t < first) {
+    if (t >= (uint32_t)num_tiles) return;
+    const uint32_t a = ranges[t];
+    const int len = (int)(ranges[t + 1] - a);
+    if (len == 0 || len > kWaveSort) return;
+    if (len <= 64) sort_list_wave<1, false>(keys, ids, a, len, lane);
+    else if (len <= 128) sort_list_wave<2, false>(keys, ids, a, len, lane);
+    else if (len <= 256) sort_list_wave<4, false>(keys, ids, a, len, lane);
+    else if (len <= 512) sort_list_wave<8, false>(keys, ids, a, len, lane);
+    else sort_list_wave<16, false>(keys, ids, a, len, lane);
     return;
   }
-  if (len <= 64) sort_list_wave<1>(keys, ids, a, len, lane);
-  else if (len <= 128) sort_list_wave<2>(keys, ids, a, len, lane);
-  else if (len <= 256) sort_list_wave<4>(keys, ids, a, len, lane);
-  else if (len <= 512) sort_list_wave<8>(keys, ids, a, len, lane);
-  else sort_list_wave<16>(keys, ids, a, len, lane);
-}
-
-// rank of key x in sorted run r[0..len): number of elements < x
-__device__ __forceinline__ uint32_t lower_rank(const uint64_t* r, uint32_t len, uint64_t x) {
-  uint32_t lo = 0, hi = len;
-  while (lo < hi) {
-    const uint32_t mid = (lo + hi) >> 1;
-    if (r[mid] < x) lo = mid + 1; else hi = mid;
+  const uint32_t n = *items.count;
+  for (uint32_t k = t - first; k < n; k += gridDim.x * 4u - first) {
+    const uint2 it = items.item[k];
+    const uint32_t a = ranges[it.x], len = ranges[it.x + 1] - a, cs = chunk_size(len);
+    sort_list_wave<16, true>(keys, ids, a + it.y * cs, (int)min(cs, len - it.y * cs), lane);
   }
-  return lo;
 }
 
-__global__ __launch_bounds__(1024) void k_sort_big(const uint32_t* __restrict__ ranges,
-                                                   uint64_t* __restrict__ keys, uint64_t* __restrict__ scratch,
-                                                   uint32_t* __restrict__ ids, const uint32_t* __restrict__ big_list,
-                                                   const uint32_t* __restrict__ big_count,
-                                                   const int32_t* __restrict__ status) {
-  __shared__ uint64_t s[kBig];
+// Merge of a long list's sorted chunks, one workgroup per chunk: its keys (four per thread) are ranked in
+// every other chunk of the list, staged through LDS with the next one's loads in flight; a key's slot is
+// its index plus those ranks (the keys differ).  Long lists thus spread over as many workgroups as they have
+// chunks: for a 640x480 view of 5 M surfels (659 lists above 1,024, up to 32,767) both sorts take 173 us,
+// against 693 with one workgroup per list (LDS bitonic sort up to 16,384 entries, then pairwise merges);
+// 10 M surfels in 8 views (4,768 lists up to 3,810) 348 against 640.
+constexpr int kMergeBlock = 256;
+constexpr int kMergeKeys = kWaveSort / kMergeBlock;
+
+__global__ __launch_bounds__(kMergeBlock) void k_merge(const uint32_t* __restrict__ ranges, SortItems items,
+                                                       const uint64_t* __restrict__ keys, uint32_t* __restrict__ ids,
+                                                       const int32_t* __restrict__ status) {
+  __shared__ uint64_t s[2][kWaveSort];
   if (*status != 0) return;
-  const uint32_t nbig = *big_count;
-  for (uint32_t q = blockIdx.x; q < nbig; q += gridDim.x) {
-    const uint32_t t = big_list[q];
-    const uint32_t a = ranges[t], b = ranges[t + 1];
-    const uint32_t len = b - a;
-    // 1) sort chunks of kBig in LDS
-    for (uint32_t c0 = 0; c0 < len; c0 += kBig) {
-      const int cl = (int)min((uint32_t)kBig, len - c0);
-      const int p = next_pow2(cl);
-      for (int k = threadIdx.x; k < p; k += 1024) s[k] = k < cl ? keys[a + c0 + k] : ~0ull;
-      __syncthreads();
-      lds_bitonic<1024>(s, p);
-      if (len <= (uint32_t)kBig) {
-        for (int k = threadIdx.x; k < cl; k += 1024) ids[a + k] = (uint32_t)s[k];
-      } else {
-        for (int k = threadIdx.x; k < cl; k += 1024) keys[a + c0 + k] = s[k];
-      }
-      __syncthreads();
+  const uint32_t n = *items.count;
+  for (uint32_t k = blockIdx.x; k < n; k += gridDim.x) {
+    const uint2 it = items.item[k];
+    const uint32_t a = ranges[it.x], len = ranges[it.x + 1] - a, cs = chunk_size(len), nc = chunk_count(len);
+    const uint32_t own = it.y * cs, ol = min(cs, len - own);
+    uint64_t x[kMergeKeys], next[kMergeKeys];
+    uint32_t pos[kMergeKeys];
+#pragma unroll
+    for (int j = 0; j < kMergeKeys; ++j) {
+      const uint32_t e = threadIdx.x + (uint32_t)j * kMergeBlock;
+      x[j] = e < ol ? keys[a + own + e] : ~0ull;
+      pos[j] = e;
     }
-    if (len <= (uint32_t)kBig) continue;
-    // 2) merge sorted runs of width w pairwise, ping-ponging between keys and scratch
-    uint64_t* src = keys + a;
-    uint64_t* dst = scratch + a;
-    for (uint32_t w = kBig; w < len; w <<= 1) {
-      for (uint32_t k = threadIdx.x; k < len; k += 1024) {
-        const uint32_t run = k / w;
-        const uint32_t r0 = (run & ~1u) * w;  // start of the left run of this pair
-        const uint32_t llen = min(w, len - r0);
-        const uint32_t rlen = r0 + w < len ? min(w, len - r0 - w) : 0;
-        const uint64_t x = src[k];
-        uint32_t pos;
-        if ((run & 1u) == 0) pos = (k - r0) + lower_rank(src + r0 + w, rlen, x);
-        else pos = (k - r0 - w) + lower_rank(src + r0, llen, x);
-        dst[r0 + pos] = x;
+    // keys of chunk c (padded with the largest key: above every key)
+    auto load = [&](uint32_t c) {
+#pragma unroll
+      for (int j = 0; j < kMergeKeys; ++j) {
+        const uint32_t e = threadIdx.x + (uint32_t)j * kMergeBlock;
+        next[j] = c < nc && e < cs && c * cs + e < len ? keys[a + c * cs + e] : ~0ull;
       }
-      __syncthreads();
-      __threadfence_block();
-      uint64_t* tmp = src; src = dst; dst = tmp;
+    };
+    uint32_t c = it.y == 0 ? 1u : 0u;
+    load(c);
+    for (int buf = 0; c < nc; buf ^= 1) {
+#pragma unroll
+      for (int j = 0; j < kMergeKeys; ++j) s[buf][threadIdx.x + j * kMergeBlock] = next[j];
+      __syncthreads();  // (the other buffer's readers are behind the barrier before)
+      c += c + 1u == it.y ? 2u : 1u;
+      load(c);
+      // number of keys below x[j]: kWaveSort is a power of two and the chunk padded to it
+      uint32_t r[kMergeKeys] = {};
+#pragma unroll
+      for (int step = kWaveSort / 2; step > 0; step >>= 1) {
+#pragma unroll
+        for (int j = 0; j < kMergeKeys; ++j) r[j] += s[buf][r[j] + (uint32_t)step - 1u] < x[j] ? (uint32_t)step : 0u;
+      }
+#pragma unroll
+      for (int j = 0; j < kMergeKeys; ++j) pos[j] += r[j] + (s[buf][r[j]] < x[j] ? 1u : 0u);
     }
-    for (uint32_t k = threadIdx.x; k < len; k += 1024) ids[a + k] = (uint32_t)src[k];
-    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < kMergeKeys; ++j) {
+      const uint32_t e = threadIdx.x + (uint32_t)j * kMergeBlock;
+      if (e < ol) ids[a + pos[j]] = (uint32_t)x[j];
+    }
+    __syncthreads();  // the next item rewrites the buffers
   }
 }
 
@@ -1006,7 +1035,7 @@ __global__ __launch_bounds__(kOrdChunk) void k_order_place(const uint32_t* __res
 // one set in row order: ranges holds those).  order may be null.
 __global__ __launch_bounds__(kScanBlock) void k_tile_scan_order(uint32_t* __restrict__ cnt, TileMap tm, int V,
                                                                 int64_t n, const uint32_t* __restrict__ vstart,
-                                                                const int64_t* __restrict__ needed,
+                                                                const int64_t* __restrict__ needed, SortItems items,
                                                                 uint32_t* __restrict__ ranges,
                                                                 uint32_t* __restrict__ order) {
   const int m = (int)tm.m;
@@ -1076,6 +1105,10 @@ __global__ __launch_bounds__(kScanBlock) void k_tile_scan_order(uint32_t* __rest
     }
   }
   if (t == 0) ranges[m] = total;
+  uint32_t tile[kScanItems];
+#pragma unroll
+  for (int k = 0; k < kScanItems; ++k) tile[k] = (uint32_t)(i0 + 64 * k + lane);
+  list_items(items, tile, c);
   if (!order) return;
   // counts per (wave, bucket), by LDS atomics that return nothing (no wait between the rows)
 #pragma unroll
@@ -1121,10 +1154,9 @@ static int64_t surf_blocks(int64_t m) { return (m + cgv2::kSurfChunk - 1) / cgv2
 static int counter_sets(int64_t m) { return m <= cgv2::kSetsMaxTiles ? cgv2::kSets : 1; }
 
 size_t cgv2_binsort_ws_layout(int64_t capacity, int V, int tiles, int64_t n, size_t* off) {
-  // off: [0] tile counters (u32, m, kSets times for few tiles) followed by the big-list and chunk-queue
-  //      counts, [1] chunk sums of the surfel scan (2 x u64 arrays), [2] big_list (u32, m), [3] scan totals
-  //      (u64 x 2), [4] keys (u64, capacity), [5] staged entries (8 B, capacity; afterwards the merge
-  //      scratch), [6], [7], [11] per visible entry: staged count (u16), first slot (u32), depth (f32),
+  // off: [0] tile counters (u32, m, kSets times for few tiles) followed by the sort-item and chunk-queue
+  //      counts, [1] chunk sums of the surfel scan (2 x u64 arrays), [2] chunks of the long lists (uint2), [3] scan totals
+  //      (u64 x 2), [4] keys (u64, capacity), [5] staged entries (8 B, capacity), [6], [7], [11] per visible entry: staged count (u16), first slot (u32, capacity), depth (f32),
   //      [8] chunk sums of the tile scan (u64)
   const int64_t m = (int64_t)V * tiles;
   const int64_t vn = (int64_t)V * n;
@@ -1134,12 +1166,12 @@ size_t cgv2_binsort_ws_layout(int64_t capacity, int V, int tiles, int64_t n, siz
   auto take = [&](size_t bytes) { size_t r = o; o += (bytes + 255) & ~(size_t)255; return r; };
   off[0] = take(4 * (size_t)(m * counter_sets(m) + 2));
   off[1] = take(16 * (size_t)(nsb + 1));
-  off[2] = take(4 * (size_t)m);
+  off[2] = take(8 * (size_t)(capacity / (cgv2::kWaveSort / 2) + 1));
   off[3] = take(64);
   off[4] = take(8 * (size_t)capacity);
   off[5] = take(8 * (size_t)capacity);
   off[6] = take(2 * (size_t)vis);
-  off[7] = take(4 * (size_t)(vis + 1));
+  off[7] = take(4 * (size_t)(capacity + 1));
   off[8] = take(8 * (size_t)(scan_blocks(m) + 1));
   // [9] per-chunk bucket counts of the launch order (one view chunk at a time)
   const int64_t per = (int64_t)std::min(V, cgv2::kMaxViews) * tiles;
@@ -1161,18 +1193,19 @@ hipError_t cgv2_launch_bin_sort(const cgv2_proj& p, int64_t n, int V, int tiles_
   cgv2_binsort_ws_layout(b.capacity, V, tiles, n, off);
   char* w = (char*)ws;
   uint32_t* cnt = (uint32_t*)(w + off[0]);
-  uint32_t* big_count = cnt + m * sets;
+  SortItems items;
+  items.count = cnt + m * sets;
   const int64_t nsb = surf_blocks(vn > 0 ? vn : 1);
   uint64_t* sums_cnt = (uint64_t*)(w + off[1]);
   uint64_t* sums_vis = sums_cnt + nsb + 1;
-  uint32_t* big_list = (uint32_t*)(w + off[2]);
+  items.item = (uint2*)(w + off[2]);
   uint64_t* totals = (uint64_t*)(w + off[3]);
   uint64_t* keys = (uint64_t*)(w + off[4]);
   uint2* staged = (uint2*)(w + off[5]);
   uint16_t* count = (uint16_t*)(w + off[6]);
   float* depth = (float*)(w + off[11]);
   uint32_t* voff = (uint32_t*)(w + off[7]);
-  uint32_t* n_chunks = big_count + 1;
+  uint32_t* n_chunks = items.count + 1;
   uint4* chunks = (uint4*)(w + off[10]);
   const uint32_t max_chunks = (uint32_t)std::min<int64_t>(b.capacity / kChunkTiles + 1, 0xffffffffll);
   TileMap tm;
@@ -1185,7 +1218,7 @@ hipError_t cgv2_launch_bin_sort(const cgv2_proj& p, int64_t n, int V, int tiles_
       (unsigned)std::min<int64_t>((std::max<int64_t>(n, 1) + kGroups * kSets - 1) / (kGroups * kSets) * kSets, 8192);
   if (n > 0) {
     // first rect slots and visible lists (consumed by the staging here and by the reverse pass), total and
-    // overflow check; the tile counters and the big-list count are zeroed on the way
+    // overflow check; the tile counters and the two counts after them are zeroed on the way
     hipLaunchKernelGGL(k_surfel_sums, dim3((unsigned)nsb), dim3(kSurfBlock), 0, st, p.rect, vn, sums_cnt, sums_vis,
                        cnt, m * sets + 2);
     // up to kSurfLocal chunks each apply workgroup adds up the chunk sums before it itself
@@ -1210,22 +1243,22 @@ hipError_t cgv2_launch_bin_sort(const cgv2_proj& p, int64_t n, int V, int tiles_
   const bool fused_order = b.order && m <= kScanChunk && V <= kMaxViews;
   if (nbt <= 1) {
     hipLaunchKernelGGL(k_tile_scan_order, dim3(1), dim3(kScanBlock), 0, st, cnt, tm, V, n, p.visible_start,
-                       b.needed, b.ranges,
+                       b.needed, items, b.ranges,
                        fused_order ? b.order : nullptr);
   } else {
     uint64_t* ts = (uint64_t*)(w + off[8]);
     hipLaunchKernelGGL(k_tile_sums, dim3((unsigned)nbt), dim3(kScanBlock), 0, st, cnt, tm, V, n,
                        p.visible_start, b.needed, ts);
     hipLaunchKernelGGL(k_tile_apply, dim3((unsigned)nbt), dim3(kScanBlock), 0, st, cnt, tm, V, n,
-                       p.visible_start, b.needed, ts, b.ranges);
+                       p.visible_start, b.needed, items, ts, b.ranges);
   }
   hipLaunchKernelGGL(k_place, dim3(runs, (unsigned)V), dim3(kStageBlock), 0, st, p.visible, p.visible_start, V, n,
                      b.needed, voff,
                      count, depth, staged, cnt, sets, b.ranges, chunks, n_chunks, max_chunks, keys, b.status);
-  hipLaunchKernelGGL(k_sort_wave, dim3((unsigned)((m + 3) / 4)), dim3(256), 0, st, b.ranges, (int)m, keys, b.ids,
-                     big_list, big_count, b.status);
-  hipLaunchKernelGGL(k_sort_big, dim3(256), dim3(1024), 0, st, b.ranges, keys, (uint64_t*)staged, b.ids, big_list,
-                     big_count, b.status);
+  // (512 workgroups more than the tiles need, for the chunks of long lists)
+  hipLaunchKernelGGL(k_sort_wave, dim3((unsigned)((m + 3) / 4 + 512)), dim3(256), 0, st, b.ranges, (int)m, items, keys,
+                     b.ids, b.status);
+  hipLaunchKernelGGL(k_merge, dim3(1024), dim3(kMergeBlock), 0, st, b.ranges, items, keys, b.ids, b.status);
   if (b.order && !fused_order) {
     uint32_t* hist = (uint32_t*)(w + off[9]);
     for (int v0 = 0; v0 < V; v0 += kMaxViews) {
