@@ -73,42 +73,78 @@ __device__ __forceinline__ float wave_sum_lane63(float v) {
 }
 
 // Reduce-scatter of 16 per-lane values over a wave: on return every lane holds the wave total of
-// value index reduce16_index(lane).  Exchanges: xor 32 and xor 16 with the gfx950 row-swap
-// instructions (x' + y' after a swap is already the pairwise sum of the kept half), xor 1 and xor 2
-// with DPP quad permutations, then an all-reduce over lane bits 2-3 with two row rotations.
-// About 35 VALU operations for 16 values, against 96 for 16 separate reductions.
+// value index reduce16_index(lane).  Lane bits 3 and 2 go first, with DPP adds whose bank masks write only
+// the lanes that keep a value (two instructions per pair, no select); bits 5 and 4 with the row-swap
+// instructions (x' + y' after a swap is already the pairwise sum of the kept half), on the three pairs that
+// are left; the quads are summed last.  The row swaps issue slower than DPP adds: with bits 5 and 4 first
+// (twelve swaps, 35 instead of 33 instructions) k_render_bwd took 349 us against 334 (1 M surfels, 1600x1066)
+// and 4991 against 4718 (10 M, 8 views).  The DPP adds are one asm block because the compiler does not form
+// them under a bank mask; its first s_nop separates them from the writes of their sources, its last from the
+// swaps, and inside it no source is written less than two instructions before.
 __device__ __forceinline__ int reduce16_index(int lane) {
-  return ((lane >> 1) & 1) | ((lane & 1) << 1) | (((lane >> 4) & 1) << 2) | (((lane >> 5) & 1) << 3);
+  return ((lane >> 4) & 1) | (((lane >> 5) & 1) << 1) | (((lane >> 2) & 1) << 2) | (((lane >> 3) & 1) << 3);
 }
 
 __device__ __forceinline__ float reduce16_scatter(float (&v)[16]) {
-  const int lane = (int)(threadIdx.x & 63u);
-#pragma unroll
-  for (int j = 0; j < 8; ++j) {
-    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v[j]), __float_as_uint(v[j + 8]), false, false);
-    v[j] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
-  }
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v[j]), __float_as_uint(v[j + 4]), false, false);
-    v[j] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
-  }
-  const bool b0 = lane & 1, b1 = lane & 2;
+  asm("s_nop 1\n"
+      "v_add_f32_dpp %0, %0, %0 row_ror:8 row_mask:0xf bank_mask:0x3\n"
+      "v_add_f32_dpp %1, %1, %1 row_ror:8 row_mask:0xf bank_mask:0x3\n"
+      "v_add_f32_dpp %2, %2, %2 row_ror:8 row_mask:0xf bank_mask:0x3\n"
+      "v_add_f32_dpp %3, %3, %3 row_ror:8 row_mask:0xf bank_mask:0x3\n"
+      "v_add_f32_dpp %4, %4, %4 row_ror:8 row_mask:0xf bank_mask:0x3\n"
+      "v_add_f32_dpp %5, %5, %5 row_ror:8 row_mask:0xf bank_mask:0x3\n"
+      "v_add_f32_dpp %6, %6, %6 row_ror:8 row_mask:0xf bank_mask:0x3\n"
+      "v_add_f32_dpp %7, %7, %7 row_ror:8 row_mask:0xf bank_mask:0x3\n"
+      "v_add_f32_dpp %0, %8, %8 row_ror:8 row_mask:0xf bank_mask:0xc\n"
+      "v_add_f32_dpp %1, %9, %9 row_ror:8 row_mask:0xf bank_mask:0xc\n"
+      "v_add_f32_dpp %2, %10, %10 row_ror:8 row_mask:0xf bank_mask:0xc\n"
+      "v_add_f32_dpp %3, %11, %11 row_ror:8 row_mask:0xf bank_mask:0xc\n"
+      "v_add_f32_dpp %4, %12, %12 row_ror:8 row_mask:0xf bank_mask:0xc\n"
+      "v_add_f32_dpp %5, %13, %13 row_ror:8 row_mask:0xf bank_mask:0xc\n"
+      "v_add_f32_dpp %6, %14, %14 row_ror:8 row_mask:0xf bank_mask:0xc\n"
+      "v_add_f32_dpp %7, %15, %15 row_ror:8 row_mask:0xf bank_mask:0xc\n"
+      "v_add_f32_dpp %0, %0, %0 row_half_mirror row_mask:0xf bank_mask:0x5\n"
+      "v_add_f32_dpp %1, %1, %1 row_half_mirror row_mask:0xf bank_mask:0x5\n"
+      "v_add_f32_dpp %2, %2, %2 row_half_mirror row_mask:0xf bank_mask:0x5\n"
+      "v_add_f32_dpp %3, %3, %3 row_half_mirror row_mask:0xf bank_mask:0x5\n"
+      "v_add_f32_dpp %0, %4, %4 row_half_mirror row_mask:0xf bank_mask:0xa\n"
+      "v_add_f32_dpp %1, %5, %5 row_half_mirror row_mask:0xf bank_mask:0xa\n"
+      "v_add_f32_dpp %2, %6, %6 row_half_mirror row_mask:0xf bank_mask:0xa\n"
+      "v_add_f32_dpp %3, %7, %7 row_half_mirror row_mask:0xf bank_mask:0xa\n"
+      "s_nop 1"
+      : "+&v"(v[0]), "+&v"(v[1]), "+&v"(v[2]), "+&v"(v[3]), "+&v"(v[4]), "+&v"(v[5]), "+&v"(v[6]), "+&v"(v[7])
+      : "v"(v[8]), "v"(v[9]), "v"(v[10]), "v"(v[11]), "v"(v[12]), "v"(v[13]), "v"(v[14]), "v"(v[15]));
 #pragma unroll
   for (int j = 0; j < 2; ++j) {
-    const float send = b0 ? v[j] : v[j + 2];
-    const float keep = b0 ? v[j + 2] : v[j];
-    v[j] = keep + dpp<0xB1>(send);
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v[j]), __float_as_uint(v[j + 2]), false, false);
+    v[j] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
   }
-  float t;
-  {
-    const float send = b1 ? v[0] : v[1];
-    const float keep = b1 ? v[1] : v[0];
-    t = keep + dpp<0x4E>(send);
-  }
-  t += dpp<0x124>(t);  // row_ror:4
-  t += dpp<0x128>(t);  // row_ror:8
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v[0]), __float_as_uint(v[1]), false, false);
+  float t = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+  t += dpp<0xB1>(t);  // quad_perm [1,0,3,2]
+  t += dpp<0x4E>(t);  // quad_perm [2,3,0,1]
   return t;
+}
+
+// The same for three values: on return lanes with (lane & 12) == 0 hold the wave total of a, (lane & 4) that of
+// b, (lane & 12) == 8 that of c.  11 operations against 18 for three separate sums.
+__device__ __forceinline__ float reduce3_scatter(float a, float b, float c) {
+  asm("s_nop 1\n"
+      "v_add_f32_dpp %0, %0, %0 row_ror:8 row_mask:0xf bank_mask:0x3\n"
+      "v_add_f32_dpp %1, %1, %1 row_ror:8 row_mask:0xf bank_mask:0xf\n"
+      "v_add_f32_dpp %0, %2, %2 row_ror:8 row_mask:0xf bank_mask:0xc\n"
+      "s_nop 1\n"
+      "v_add_f32_dpp %0, %0, %0 row_half_mirror row_mask:0xf bank_mask:0x5\n"
+      "v_add_f32_dpp %0, %1, %1 row_half_mirror row_mask:0xf bank_mask:0xa\n"
+      "s_nop 1"
+      : "+&v"(a), "+&v"(b)
+      : "v"(c));
+  a += dpp<0xB1>(a);  // quad_perm [1,0,3,2]
+  a += dpp<0x4E>(a);  // quad_perm [2,3,0,1]
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(a), false, false);
+  a = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+  const auto q = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(a), false, false);
+  return __uint_as_float(q[0]) + __uint_as_float(q[1]);
 }
 
 // Where a surfel can reach alpha >= 1/255 (Sec. 3.1 cutoff).  rho is the smaller of the ray-splat

@@ -254,13 +254,17 @@ __device__ __forceinline__ uint32_t lane_copy(uint32_t x) {
 
 // Returns false when no pixel of the quadrant takes the entry (wave-uniform); true otherwise, which
 // covers every entry with a contributing fragment (a superset is all the reverse pass needs).
-// kContrib: also add the fragment's alpha^gamma T^(1-gamma) (T in front of it) and 1 to csum / ccnt.
+// kContrib: also add the fragment's alpha^gamma T^(1-gamma) (T in front of it) to csum and the quadrant's
+// number of blended pixels to ccnt.  kHalfGamma (the usual gamma = 1/2) is sqrt(alpha T): one transcendental
+// instead of two.
 constexpr float kLog2AlphaMax = -0.014499569695115089f;  // log2(0.99)
 
-template <bool kContrib>
+enum : int { kNoContrib = 0, kAnyGamma = 1, kHalfGamma = 2 };
+
+template <int kContrib>
 __device__ __forceinline__ bool fwd_px(const Px& e, const float4& q2, const float4& q3, const float4& q4,
                                        uint32_t e_idx, FwdState& f, unsigned long long& n_con, float gamma,
-                                       float& csum, float& ccnt) {
+                                       float& csum, uint32_t& ccnt) {
   // wave-uniform skip when no pixel of the quadrant takes this surfel; otherwise branch-free: a
   // contribution is a zero-weight no-op for pixels that skip or stop here
   const bool take = f.T > 0.f && e.alpha >= kAlphaMin;
@@ -270,11 +274,16 @@ __device__ __forceinline__ bool fwd_px(const Px& e, const float4& q2, const floa
   const bool upd = take && !(Tn < kTmin);
   n_con += upd ? 1u : 0u;
   if (kContrib) {
-    // log2(alpha) = min(log2(alpha_raw), log2(0.99))
-    const float la = fminf(e.arg, kLog2AlphaMax);
-    const float c = __builtin_amdgcn_exp2f(fmaf(gamma, la, (1.f - gamma) * __builtin_amdgcn_logf(f.T)));
+    float c;
+    if (kContrib == kHalfGamma) {
+      c = __builtin_amdgcn_sqrtf(e.alpha * f.T);
+    } else {
+      // log2(alpha) = min(log2(alpha_raw), log2(0.99))
+      const float la = fminf(e.arg, kLog2AlphaMax);
+      c = __builtin_amdgcn_exp2f(fmaf(gamma, la, (1.f - gamma) * __builtin_amdgcn_logf(f.T)));
+    }
     csum += upd ? c : 0.f;
-    ccnt += upd ? 1.f : 0.f;
+    ccnt += (uint32_t)__popcll(__ballot(upd));
   }
   const float wgt = upd ? e.alpha * f.T : 0.f;
   const float zf = e.is3d ? q2.w * e.iw : q2.z;
@@ -314,7 +323,7 @@ __device__ __forceinline__ uint32_t live_quadrants(const FwdState (&f)[4]) {
 // pixel meets, quadrant mask or not), the contributing pairs, and the pairs the reverse walks.
 // kContrib: instead of images, add each surfel's contribution sums (Sec. 3.3, Eq. 3) of this view into
 // a.cws, one wave reduction and one atomic pair per (surfel, tile or split block).
-template <bool kCount, bool kMask, bool kContrib, uint32_t kSub>
+template <bool kCount, bool kMask, int kContrib, uint32_t kSub>
 __device__ __forceinline__ void render_fwd_tile(const RenderArgs& a, Stage& s, uint32_t b) {
   const int lv = (int)(b / (uint32_t)a.tiles);
   const int v = a.cams.v0 + lv;
@@ -376,7 +385,8 @@ __device__ __forceinline__ void render_fwd_tile(const RenderArgs& a, Stage& s, u
       LaneTerms lt;
       lane_terms(lx0, ly0, q0, q1, q2, lt);
       const uint32_t e_idx = lane_copy(base + (uint32_t)j);
-      float csum = 0.f, ccnt = 0.f;
+      float csum = 0.f;
+      uint32_t ccnt = 0;  // wave-uniform
       bool took = false;
       Px e[4];
 #pragma unroll
@@ -392,13 +402,11 @@ __device__ __forceinline__ void render_fwd_tile(const RenderArgs& a, Stage& s, u
           if (kMask) cq[k] |= 1ull << j;
         }
       }
-      if (kContrib && took) {
-        const float ts = wave_sum_lane63(csum), tc = wave_sum_lane63(ccnt);
-        if (lane == 63 && tc > 0.f) {
-          float* w = a.cws + 2 * (vn + (int64_t)__float_as_uint(q3.w));
-          atomicAdd(w, ts);
-          atomicAdd(w + 1, tc);
-        }
+      if (kContrib && took && ccnt != 0) {
+        // the sum from lane 63, the count from lane 62: one atomic instruction
+        const float ts = wave_sum_lane63(csum);
+        if (lane >= 62)
+          atomicAdd(a.cws + 2 * (vn + (int64_t)__float_as_uint(q3.w)) + (63 - lane), lane == 63 ? ts : (float)ccnt);
       }
     };
     if constexpr (kOne && !kCount) {
@@ -489,7 +497,7 @@ __device__ __forceinline__ void render_fwd_tile(const RenderArgs& a, Stage& s, u
   }
 }
 
-template <bool kCount, bool kMask, bool kContrib>
+template <bool kCount, bool kMask, int kContrib>
 __global__ __launch_bounds__(64) void k_render_fwd(RenderArgs a) {
   __shared__ Stage s;
   uint32_t sub;
@@ -659,7 +667,7 @@ __device__ __forceinline__ float slot_scale(int slot) {
 
 // Adds one staged entry's wave-summed record gradients (acc of every lane) into (view, surfel) 'id':
 // fields G_CX..G_ZC by reduce-scatter (one atomic instruction, one lane per field), the normals (kGeom)
-// from lane 63.  sc = slot_scale of the lane's field.
+// likewise.  sc = slot_scale of the lane's field.
 template <bool kGeom>
 __device__ __forceinline__ void bwd_commit(float (&acc)[kGradFields], int lane, int slot, float sc, float io,
                                            float* rgv, float* rgn, uint32_t id) {
@@ -667,16 +675,12 @@ __device__ __forceinline__ void bwd_commit(float (&acc)[kGradFields], int lane, 
 #pragma unroll
   for (int f = 0; f < 16; ++f) red[f] = acc[f];
   const float tot = reduce16_scatter(red);
-  if ((lane & 12) == 0 && (kGeom || slot != G_ZC))
+  if ((lane & 3) == 0 && (kGeom || slot != G_ZC))
     atomicAdd(rgv + (int64_t)id * kGradRow + slot, tot * (slot == G_OP ? -0.5f * io : sc));
   if (kGeom) {
-    const float nx = wave_sum_lane63(acc[G_NX]), ny = wave_sum_lane63(acc[G_NY]), nz = wave_sum_lane63(acc[G_NZ]);
-    if (lane == 63) {
-      float* w = rgn + (int64_t)id * kGradNrm;
-      atomicAdd(w, -0.5f * nx);
-      atomicAdd(w + 1, -0.5f * ny);
-      atomicAdd(w + 2, -0.5f * nz);
-    }
+    const float nrm = reduce3_scatter(acc[G_NX], acc[G_NY], acc[G_NZ]);
+    // lanes 0, 4 and 8: nx, ny, nz
+    if ((lane & 0x33) == 0 && lane < 12) atomicAdd(rgn + (int64_t)id * kGradNrm + (lane >> 2), -0.5f * nrm);
   }
 }
 
@@ -933,8 +937,8 @@ hipError_t cgv2_launch_render_fwd(const cgv2_proj& p, const cgv2_bins& b, const 
   const unsigned grid = (unsigned)((int64_t)cams.count * a.tiles + 3 * a.n_q + a.n_h);
   if (img.qmask && a.n_q + a.n_h)
     hipLaunchKernelGGL(cgv2::k_clear_split_qmask, dim3(a.n_q + a.n_h), dim3(256), 0, st, a);
-  if (img.qmask) hipLaunchKernelGGL((cgv2::k_render_fwd<false, true, false>), dim3(grid), dim3(64), 0, st, a);
-  else hipLaunchKernelGGL((cgv2::k_render_fwd<false, false, false>), dim3(grid), dim3(64), 0, st, a);
+  if (img.qmask) hipLaunchKernelGGL((cgv2::k_render_fwd<false, true, cgv2::kNoContrib>), dim3(grid), dim3(64), 0, st, a);
+  else hipLaunchKernelGGL((cgv2::k_render_fwd<false, false, cgv2::kNoContrib>), dim3(grid), dim3(64), 0, st, a);
   return hipGetLastError();
 }
 
@@ -943,7 +947,7 @@ hipError_t cgv2_launch_render_count(const cgv2_proj& p, const cgv2_bins& b, cons
   cgv2::RenderArgs a = make_args(p, b, cams, n, tiles_x, tiles_y, nullptr, counters);
   split_fwd(a);
   const unsigned grid = (unsigned)((int64_t)cams.count * a.tiles + 3 * a.n_q + a.n_h);
-  hipLaunchKernelGGL((cgv2::k_render_fwd<true, false, false>), dim3(grid), dim3(64), 0, st, a);
+  hipLaunchKernelGGL((cgv2::k_render_fwd<true, false, cgv2::kNoContrib>), dim3(grid), dim3(64), 0, st, a);
   return hipGetLastError();
 }
 
@@ -974,6 +978,9 @@ hipError_t cgv2_launch_contribution(const cgv2_proj& p, const cgv2_bins& b, cons
   a.cws = cws;
   a.gamma = gamma;
   const unsigned grid = (unsigned)((int64_t)cams.count * a.tiles + 3 * a.n_q + a.n_h);
-  hipLaunchKernelGGL((cgv2::k_render_fwd<false, false, true>), dim3(grid), dim3(64), 0, st, a);
+  if (gamma == 0.5f)
+    hipLaunchKernelGGL((cgv2::k_render_fwd<false, false, cgv2::kHalfGamma>), dim3(grid), dim3(64), 0, st, a);
+  else
+    hipLaunchKernelGGL((cgv2::k_render_fwd<false, false, cgv2::kAnyGamma>), dim3(grid), dim3(64), 0, st, a);
   return hipGetLastError();
 }
