@@ -152,8 +152,7 @@ __device__ __forceinline__ float reduce3_scatter(float a, float b, float c) {
 // projected centre; A = the record's a_ij / sqrt 2, w(x) = w0 + w1 x + w2 y as the renderer stages
 // them, so this is the function its evaluation rounds), and the cutoff is rho <= ln(255 o) = k2 / 2.
 // {|A x|^2 <= c w(x)^2} is the conic g(x) = x'Gx + 2 b'x + d <= 0; when G is positive definite it is an
-// ellipse, met by a box iff its centre lies in the box or g <= 0 somewhere on one of the four edges
-// (g is convex, so each edge's minimum is at the clamped stationary point).  FP64, with the cutoff
+// ellipse, met by a box iff g <= 0 at its smallest there (see reach_box).  FP64, with the cutoff
 // enlarged to c = 0.5 k2 (1 + 2e-3) + 1e-3 and every box padded by kReachPad: far beyond the FP32
 // error of the evaluation and of the reciprocals used here, so a box is reported unreachable only
 // where no pixel sample in it can take the surfel.  A conic that is not an ellipse reaches every box.
@@ -191,19 +190,23 @@ __device__ __forceinline__ void reach_setup(float a11, float a12, float a21, flo
 }
 
 // Does the box [xl, xh] x [yl, yh] (centre-relative, already padded) hold a point with rho <= c?
+// The minimum of the convex g over a box that does not hold the ellipse's centre lies on an edge facing the
+// centre, so two evaluations decide: the best point of the vertical through the centre's x clamped to the
+// box, and of the horizontal through its clamped y (with the centre inside, either is the centre).
+// Against all four edges: 10 M surfels in 8 views, k_stage_big 396 -> 313 us, forward 2716 -> 2624, contribution
+// pass 2778 -> 2535; 1 M at 1600x1066, k_stage 27.5 -> 25.6, forward 194 -> 190.
 __device__ __forceinline__ bool reach_box(const Reach& q, double xl, double xh, double yl, double yh) {
+  auto clamp = [](double v, double lo, double hi) { return fmin(fmax(v, lo), hi); };
   // screen-filter disc |x|^2 <= c
-  const double dx = xl > 0.0 ? xl : (xh < 0.0 ? xh : 0.0), dy = yl > 0.0 ? yl : (yh < 0.0 ? yh : 0.0);
-  if (dx * dx + dy * dy <= q.c) return true;
-  if (!q.ellipse || (q.xs >= xl && q.xs <= xh && q.ys >= yl && q.ys <= yh)) return true;
-  auto g = [&](double x, double y) {
-    return fma(q.G00 * x, x, fma(2.0 * q.G01 * x, y, fma(q.G11 * y, y, fma(2.0 * q.b0, x, fma(2.0 * q.b1, y, q.d)))));
-  };
-  const double yA = fmin(fmax(-(q.G01 * xl + q.b1) * q.i11, yl), yh);
-  const double yB = fmin(fmax(-(q.G01 * xh + q.b1) * q.i11, yl), yh);
-  const double xA = fmin(fmax(-(q.G01 * yl + q.b0) * q.i00, xl), xh);
-  const double xB = fmin(fmax(-(q.G01 * yh + q.b0) * q.i00, xl), xh);
-  return fmin(fmin(g(xl, yA), g(xh, yB)), fmin(g(xA, yl), g(xB, yh))) <= 0.0;
+  const double dx = clamp(0.0, xl, xh), dy = clamp(0.0, yl, yh);
+  if (fma(dx, dx, dy * dy) <= q.c) return true;
+  if (!q.ellipse) return true;
+  const double X = clamp(q.xs, xl, xh), Y = clamp(q.ys, yl, yh);
+  const double p = fma(q.G01, X, q.b1), r = fma(q.G01, Y, q.b0);
+  const double y = clamp(-p * q.i11, yl, yh), x = clamp(-r * q.i00, xl, xh);
+  const double gx = fma(fma(q.G11, y, p + p), y, fma(fma(q.G00, X, 2.0 * q.b0), X, q.d));
+  const double gy = fma(fma(q.G00, x, r + r), x, fma(fma(q.G11, Y, 2.0 * q.b1), Y, q.d));
+  return fmin(gx, gy) <= 0.0;
 }
 
 // Box of the pixel samples [x0 + 0.5, x0 + span - 0.5] x [y0 + ...] of a tile-relative cell, relative to
