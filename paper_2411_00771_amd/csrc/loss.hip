@@ -3,34 +3,39 @@
 // gradient (Sec. 3.2, Eq. 2).
 //
 // SSIM (Wang et al. 2004): 11x11 separable Gaussian window (sigma 1.5), zero padding,
-// C1 = 0.01^2, C2 = 0.03^2.  Both kernels run one wave per strip of 64 columns x kStripH rows of one
-// image plane and walk down the strip: each input row (the 64 columns and a 5-column halo on either
-// side) goes through LDS once, its 11-tap horizontal sums enter a ring of the last 11 rows held in
-// registers, and each new row completes the vertical sums of one output row -- the only recomputation
-// is the 10-row halo at the strip's top.  The forward kernel computes the five local moments, the SSIM
-// map and its three partial derivatives (w.r.t. the local mean, E[x^2] and E[xy]) and deterministic
-// per-wave sums; the backward kernel correlates the three partial maps with the same window and
-// combines them with the L1 sign into dL/dI and d(lambda (1 - SSIM))/dI.
+// C1 = 0.01^2, C2 = 0.03^2.  Both kernels run one wave per strip of 64 columns of one image plane and walk
+// down the strip: each input row (the 64 columns and a 5-column halo on either side) goes through LDS once,
+// its 11-tap horizontal sums enter a ring of the last 11 rows held in registers, and each new row completes
+// the vertical sums of one output row -- the only recomputation is the 10-row halo at the strip's top.  The
+// forward kernel sums four moments (x, y, x^2 + y^2, xy: SSIM needs the variances only added up), formed once
+// per pixel on the way into LDS, and computes the SSIM map and its three partial derivatives (w.r.t. the
+// local mean, E[x^2] and E[xy]) and deterministic per-wave sums; the backward kernel correlates the three
+// partial maps with the same window and combines them with the L1 sign into dL/dI and
+// d(lambda (1 - SSIM))/dI.
+//
+// Both are bound by vector instructions and LDS reads (and, where a SIMD holds a single wave, by the latency of
+// a row's chain): a launch takes as long as the SIMD with the most rows, see strip_grid().
 #include "cgv2r_device.h"
 #include "cgv2r_kernels.h"
+
+#include <algorithm>
 
 namespace cgv2 {
 
 constexpr int kR = 5;
 constexpr int kTaps = 2 * kR + 1;       // 11
 constexpr int kStripW = 64;             // output columns per wave (one per lane)
-constexpr int kAhead = 2;               // rows loaded ahead of the one in use (queue slot = row % 2)
-constexpr int kLoops = 2;               // row loop iterations of 22 rows after the first 11
-constexpr int kInRows = kTaps + 2 * kTaps * kLoops;  // 55 input rows per strip
-constexpr int kStripH = kInRows - 2 * kR;            // 45 output rows per wave
 constexpr int kRowW = kStripW + 2 * kR;
 constexpr float kC1 = 0.0001f, kC2 = 0.0009f;
+// The moments are taken about mid-grey: the variances do not change, and less cancels in them (the gradient's
+// error against float64 on images in [0, 1] is 3.5e-5, about zero 9.5e-5).
+constexpr float kMid = 0.5f;
 
 struct Win { float g[kTaps]; };
 
 // Block -> (strip column, strip row, plane vc = v * 3 + channel).
 struct StripGrid {
-  int nx, ny;
+  int nx, ny, rows;  // strips per plane across and down, output rows per strip
 };
 
 // Hardware sends workgroup b to XCD b % 8: XCD x takes the x-th contiguous eighth of the strips (row-major
@@ -42,7 +47,7 @@ __device__ __forceinline__ int strip_of_block(const StripGrid& sg, int& x0, int&
   const int b = (int)(bb < full ? (bb % 8u) * (full / 8u) + bb / 8u : bb);
   const int r = b / sg.nx;
   x0 = (b - r * sg.nx) * kStripW;
-  y0 = (r % sg.ny) * kStripH;
+  y0 = (r % sg.ny) * sg.rows;
   vc = r / sg.ny;
   return b;
 }
@@ -72,10 +77,10 @@ __device__ __forceinline__ void store_or_drop(__amdgpu_buffer_rsrc_t r, float v,
 }
 
 // Byte offsets of row yy at columns x0 - 5 + lane (a) and x0 + 59 + lane for lane < 10 (b), kDrop
-// outside the image (or for a row past the strip, live = false).
-__device__ __forceinline__ void row_offsets(int W, int H, int x0, int yy, int lane, bool live, uint32_t& a,
+// outside the image.
+__device__ __forceinline__ void row_offsets(int W, int H, int x0, int yy, int lane, uint32_t& a,
                                             uint32_t& b) {
-  const bool row = live && yy >= 0 && yy < H;
+  const bool row = yy >= 0 && yy < H;
   const int c0 = x0 - kR + lane, c1 = x0 - kR + kStripW + lane;
   a = (row && c0 >= 0 && c0 < W) ? (uint32_t)((int64_t)yy * W + c0) * 4u : kDrop;
   b = (row && lane < 2 * kR && c1 < W) ? (uint32_t)((int64_t)yy * W + c1) * 4u : kDrop;
@@ -94,65 +99,63 @@ __device__ __forceinline__ void vsum(const float (&ring)[kTaps][N], const Win& w
   }
 }
 
+// Rows are loaded kTaps ahead of their use: the queue slot of a row is then its ring slot (row % 11), fixed at
+// every position of the unrolled loop.  (Two rows ahead: a wave alone on its SIMD waits on every row.)
 struct FwdStrip {
   __amdgpu_buffer_rsrc_t rx, ry, rm;
-  int W, H, x0, y0, lane;
+  int W, H, x0, y0, lane, rows;  // rows: input rows of the strip
   int64_t HW;
-  float xa[kAhead], xb[kAhead], ya[kAhead], yb[kAhead];  // the next kAhead rows, oldest first
-  float ring[kTaps][5];  // horizontal sums of the last 11 input rows, slot = row % 11
-  float cx[kTaps], cy[kTaps];  // the lane's own column of those rows
+  float xa[kTaps], xb[kTaps], ya[kTaps], yb[kTaps];  // the next rows' own and halo columns
+  float ring[kTaps][4];                              // horizontal sums of the last 11 input rows
   double m_sum, l1_sum;
 };
 
-// Loads input row rn of the strip into queue slot Q.
+// Loads input row rn of the strip into queue slot Q (rows past the strip are loaded too, and not used).
 template <int Q>
 __device__ __forceinline__ void fwd_load(FwdStrip& f, int rn) {
   uint32_t oa, ob;
-  row_offsets(f.W, f.H, f.x0, f.y0 - kR + rn, f.lane, rn < kInRows, oa, ob);
+  row_offsets(f.W, f.H, f.x0, f.y0 - kR + rn, f.lane, oa, ob);
   f.xa[Q] = load_or_zero(f.rx, oa);
   f.xb[Q] = load_or_zero(f.rx, ob);
   f.ya[Q] = load_or_zero(f.ry, oa);
   f.yb[Q] = load_or_zero(f.ry, ob);
 }
 
-template <int J, int Q>
-__device__ __forceinline__ void fwd_row(FwdStrip& f, float* sx, float* sy, const Win& win, int r) {
-  // r = input row index within the strip (y0 - 5 + r): ring slot J = r % 11, queue slot Q = r % 2
+// Input row r (image row y0 - 5 + r) into the ring; from row 10 on, output row y0 + r - 10 from the ring.
+template <int J>
+__device__ __forceinline__ void fwd_step(FwdStrip& f, float4* s, const Win& win, int r) {
   wave_lds_order();  // the previous row is no longer read
-  sx[f.lane] = f.xa[Q];
-  sy[f.lane] = f.ya[Q];
+  const float x = f.xa[J] - kMid, y = f.ya[J] - kMid;
+  s[f.lane] = make_float4(x, y, fmaf(x, x, y * y), x * y);
   if (f.lane < 2 * kR) {
-    sx[kStripW + f.lane] = f.xb[Q];
-    sy[kStripW + f.lane] = f.yb[Q];
+    const float u = f.xb[J] - kMid, v = f.yb[J] - kMid;
+    s[kStripW + f.lane] = make_float4(u, v, fmaf(u, u, v * v), u * v);
   }
   wave_lds_order();
-  fwd_load<Q>(f, r + kAhead);  // the slot is free again: the row two ahead
-  float m0 = 0, m1 = 0, m2 = 0, m3 = 0, m4 = 0;
+  fwd_load<J>(f, r + kTaps);  // the slot is free again
+  float m0 = 0, m1 = 0, m2 = 0, m3 = 0;
 #pragma unroll
   for (int a = 0; a < kTaps; ++a) {
-    const float xv = sx[f.lane + a], yv = sy[f.lane + a], g = win.g[a];
-    m0 = fmaf(g, xv, m0);
-    m1 = fmaf(g, yv, m1);
-    m2 = fmaf(g, xv * xv, m2);
-    m3 = fmaf(g, yv * yv, m3);
-    m4 = fmaf(g, xv * yv, m4);
+    const float4 q = s[f.lane + a];
+    const float g = win.g[a];
+    m0 = fmaf(g, q.x, m0);
+    m1 = fmaf(g, q.y, m1);
+    m2 = fmaf(g, q.z, m2);
+    m3 = fmaf(g, q.w, m3);
+    if (a == kR) {  // the lane's own column: its L1 term, where the row is one of the strip's outputs
+      const bool own = f.x0 + f.lane < f.W && r >= kR && r < f.rows - kR;
+      f.l1_sum += own ? (double)fabsf(q.x - q.y) : 0.0;
+    }
   }
-  f.ring[J][0] = m0; f.ring[J][1] = m1; f.ring[J][2] = m2; f.ring[J][3] = m3; f.ring[J][4] = m4;
-  f.cx[J] = sx[f.lane + kR];
-  f.cy[J] = sy[f.lane + kR];
-}
-
-// Output row y0 + r - 10 from the ring (its newest input row in slot J).
-template <int J>
-__device__ __forceinline__ void fwd_out(FwdStrip& f, const Win& win, int r) {
-  float v[5];
-  vsum<5, J>(f.ring, win, v);
-  const float mx = v[0], my = v[1], exx = v[2], eyy = v[3], exy = v[4];
+  f.ring[J][0] = m0; f.ring[J][1] = m1; f.ring[J][2] = m2; f.ring[J][3] = m3;
+  if (r < 2 * kR) return;
+  float v[4];
+  vsum<4, J>(f.ring, win, v);
+  const float sx = v[0], sy = v[1], mx = sx + kMid, my = sy + kMid;  // the means, shifted and true
   const int px = f.x0 + f.lane, py = f.y0 + r - 2 * kR;
   const bool in = px < f.W && py < f.H;
-  const float sxx = exx - mx * mx, syy = eyy - my * my, sxy = exy - mx * my;
-  const float A1 = 2.f * mx * my + kC1, A2 = 2.f * sxy + kC2;
-  const float B1 = mx * mx + my * my + kC1, B2 = sxx + syy + kC2;
+  const float A1 = fmaf(2.f * mx, my, kC1), A2 = fmaf(2.f, fmaf(-sx, sy, v[3]), kC2);
+  const float B1 = fmaf(mx, mx, fmaf(my, my, kC1)), B2 = (v[2] - fmaf(sx, sx, sy * sy)) + kC2;
   // single-precision reciprocals (1 ulp) in place of IEEE divisions
   const float iB1 = __builtin_amdgcn_rcpf(B1), iB2 = __builtin_amdgcn_rcpf(B2);
   const float iB = iB1 * iB2;
@@ -161,73 +164,47 @@ __device__ __forceinline__ void fwd_out(FwdStrip& f, const Win& win, int r) {
   store_or_drop(f.rm, 2.f * my * (A2 - A1) * iB - 2.f * m * mx * (iB1 - iB2), in ? o : kDrop);
   store_or_drop(f.rm, -m * iB2, in ? o + hw : kDrop);
   store_or_drop(f.rm, 2.f * A1 * iB, in ? o + 2u * hw : kDrop);
-  // the centre pixel is input row r - 5: slot J + 6 (mod 11)
-  constexpr int kc = (J + kR + 1) % kTaps;
   f.m_sum += in ? (double)m : 0.0;
-  f.l1_sum += in ? (double)fabsf(f.cx[kc] - f.cy[kc]) : 0.0;
 }
 
-template <int J, int Q>
-__device__ __forceinline__ void fwd_step(FwdStrip& f, float* sx, float* sy, const Win& win, int r, bool out) {
-  fwd_row<J, Q>(f, sx, sy, win, r);
-  if (out) fwd_out<J>(f, win, r);
+// The strip's rows in groups of kTaps, the first slot of each group first; ends after row f.rows - 1.
+#define CGV2_STRIP_ROWS(STEP)                    \
+  for (int r = 0;; r += kTaps) {                 \
+    STEP(0) STEP(1) STEP(2) STEP(3) STEP(4) STEP(5) STEP(6) STEP(7) STEP(8) STEP(9) STEP(10) \
+  }
+
+template <int J>
+__device__ __forceinline__ void fwd_fill(FwdStrip& f) {
+  fwd_load<J>(f, J);
+  if constexpr (J + 1 < kTaps) fwd_fill<J + 1>(f);
+}
+
+__device__ __forceinline__ void fwd_rows(FwdStrip& f, float4* s, const Win& win) {
+#define CGV2_STEP(J)              \
+  if (r + J >= f.rows) return;    \
+  fwd_step<J>(f, s, win, r + J);
+  CGV2_STRIP_ROWS(CGV2_STEP)
+#undef CGV2_STEP
 }
 
 __global__ __launch_bounds__(64) void k_ssim_fwd(const float* __restrict__ img, const float* __restrict__ tgt, int W,
                                                  int H, Win win, StripGrid sg, float* __restrict__ maps,
                                                  double* __restrict__ partial) {
-  __shared__ float sx[kRowW], sy[kRowW];
+  __shared__ float4 s[kRowW];
   FwdStrip f;
   int vc;
   const int strip = strip_of_block(sg, f.x0, f.y0, vc);
   f.W = W;
   f.H = H;
   f.lane = (int)threadIdx.x;
+  f.rows = min(sg.rows, H - f.y0) + 2 * kR;
   f.HW = (int64_t)W * H;
   f.rx = plane_rsrc(img + vc * f.HW, f.HW);
   f.ry = plane_rsrc(tgt + vc * f.HW, f.HW);
   f.rm = plane_rsrc(maps + (int64_t)vc * 3 * f.HW, 3 * f.HW);
   f.m_sum = f.l1_sum = 0.0;
-  fwd_load<0>(f, 0);
-  fwd_load<1>(f, 1);
-  // rows 0..10 fill the ring (the first output comes with row 10), then 22 rows per iteration, one output
-  // each; the ring slot is row % 11 and the queue slot row % 2, both fixed at every unrolled position
-  fwd_step<0, 0>(f, sx, sy, win, 0, false);
-  fwd_step<1, 1>(f, sx, sy, win, 1, false);
-  fwd_step<2, 0>(f, sx, sy, win, 2, false);
-  fwd_step<3, 1>(f, sx, sy, win, 3, false);
-  fwd_step<4, 0>(f, sx, sy, win, 4, false);
-  fwd_step<5, 1>(f, sx, sy, win, 5, false);
-  fwd_step<6, 0>(f, sx, sy, win, 6, false);
-  fwd_step<7, 1>(f, sx, sy, win, 7, false);
-  fwd_step<8, 0>(f, sx, sy, win, 8, false);
-  fwd_step<9, 1>(f, sx, sy, win, 9, false);
-  fwd_step<10, 0>(f, sx, sy, win, 10, true);
-#pragma nounroll
-  for (int r0 = kTaps; r0 < kInRows; r0 += 2 * kTaps) {
-    fwd_step<0, 1>(f, sx, sy, win, r0 + 0, true);
-    fwd_step<1, 0>(f, sx, sy, win, r0 + 1, true);
-    fwd_step<2, 1>(f, sx, sy, win, r0 + 2, true);
-    fwd_step<3, 0>(f, sx, sy, win, r0 + 3, true);
-    fwd_step<4, 1>(f, sx, sy, win, r0 + 4, true);
-    fwd_step<5, 0>(f, sx, sy, win, r0 + 5, true);
-    fwd_step<6, 1>(f, sx, sy, win, r0 + 6, true);
-    fwd_step<7, 0>(f, sx, sy, win, r0 + 7, true);
-    fwd_step<8, 1>(f, sx, sy, win, r0 + 8, true);
-    fwd_step<9, 0>(f, sx, sy, win, r0 + 9, true);
-    fwd_step<10, 1>(f, sx, sy, win, r0 + 10, true);
-    fwd_step<0, 0>(f, sx, sy, win, r0 + 11, true);
-    fwd_step<1, 1>(f, sx, sy, win, r0 + 12, true);
-    fwd_step<2, 0>(f, sx, sy, win, r0 + 13, true);
-    fwd_step<3, 1>(f, sx, sy, win, r0 + 14, true);
-    fwd_step<4, 0>(f, sx, sy, win, r0 + 15, true);
-    fwd_step<5, 1>(f, sx, sy, win, r0 + 16, true);
-    fwd_step<6, 0>(f, sx, sy, win, r0 + 17, true);
-    fwd_step<7, 1>(f, sx, sy, win, r0 + 18, true);
-    fwd_step<8, 0>(f, sx, sy, win, r0 + 19, true);
-    fwd_step<9, 1>(f, sx, sy, win, r0 + 20, true);
-    fwd_step<10, 0>(f, sx, sy, win, r0 + 21, true);
-  }
+  fwd_fill<0>(f);
+  fwd_rows(f, s, win);
   // per-wave sums in FP64, fixed order (butterfly)
   double m_sum = f.m_sum, l1_sum = f.l1_sum;
 #pragma unroll
@@ -243,11 +220,11 @@ __global__ __launch_bounds__(64) void k_ssim_fwd(const float* __restrict__ img, 
 
 struct BwdStrip {
   __amdgpu_buffer_rsrc_t rm, rx, ry, rs, ri;
-  int W, H, x0, y0, lane;
+  int W, H, x0, y0, lane, rows;
   int64_t HW;
   float ninv, lambda;
-  float va[kAhead][3], vb[kAhead][3];  // the next kAhead rows of the three maps, oldest first
-  float xv[kAhead], yv[kAhead];        // image and target at those rows' output pixels
+  float va[kTaps][3], vb[kTaps][3];  // the next rows of the three maps
+  float xv[kTaps], yv[kTaps];        // image and target at those rows' output pixels
   float ring[kTaps][3];
 };
 
@@ -255,7 +232,7 @@ struct BwdStrip {
 template <int k>
 __device__ __forceinline__ void bwd_load(BwdStrip& f, int rn) {
   uint32_t oa, ob;
-  row_offsets(f.W, f.H, f.x0, f.y0 - kR + rn, f.lane, rn < kInRows, oa, ob);
+  row_offsets(f.W, f.H, f.x0, f.y0 - kR + rn, f.lane, oa, ob);
   const uint32_t hw = (uint32_t)f.HW * 4u;
 #pragma unroll
   for (int q = 0; q < 3; ++q) {
@@ -263,33 +240,31 @@ __device__ __forceinline__ void bwd_load(BwdStrip& f, int rn) {
     f.vb[k][q] = load_or_zero(f.rm, ob == kDrop ? kDrop : ob + (uint32_t)q * hw);
   }
   const int px = f.x0 + f.lane, pyn = f.y0 + rn - 2 * kR;
-  const bool ok = rn >= 2 * kR && rn < kInRows && px < f.W && pyn < f.H;
+  const bool ok = rn >= 2 * kR && px < f.W && pyn < f.H;
   const uint32_t on = ok ? (uint32_t)((int64_t)pyn * f.W + px) * 4u : kDrop;
   f.xv[k] = load_or_zero(f.rx, on);
   f.yv[k] = load_or_zero(f.ry, on);
 }
 
-template <int J, int Q>
-__device__ __forceinline__ void bwd_step(BwdStrip& f, float (*sm)[kRowW], const Win& win, int r, bool out) {
+template <int J>
+__device__ __forceinline__ void bwd_step(BwdStrip& f, float4* s, const Win& win, int r) {
   wave_lds_order();
-#pragma unroll
-  for (int q = 0; q < 3; ++q) {
-    sm[q][f.lane] = f.va[Q][q];
-    if (f.lane < 2 * kR) sm[q][kStripW + f.lane] = f.vb[Q][q];
-  }
+  s[f.lane] = make_float4(f.va[J][0], f.va[J][1], f.va[J][2], 0.f);
+  if (f.lane < 2 * kR) s[kStripW + f.lane] = make_float4(f.vb[J][0], f.vb[J][1], f.vb[J][2], 0.f);
   wave_lds_order();
-  const float xc = f.xv[Q], yc = f.yv[Q];  // this row's output pixel
-  bwd_load<Q>(f, r + kAhead);
+  const float xc = f.xv[J], yc = f.yv[J];  // this row's output pixel
+  bwd_load<J>(f, r + kTaps);
   float m0 = 0, m1 = 0, m2 = 0;
 #pragma unroll
   for (int a = 0; a < kTaps; ++a) {
+    const float4 q = s[f.lane + a];
     const float g = win.g[a];
-    m0 = fmaf(g, sm[0][f.lane + a], m0);
-    m1 = fmaf(g, sm[1][f.lane + a], m1);
-    m2 = fmaf(g, sm[2][f.lane + a], m2);
+    m0 = fmaf(g, q.x, m0);
+    m1 = fmaf(g, q.y, m1);
+    m2 = fmaf(g, q.z, m2);
   }
   f.ring[J][0] = m0; f.ring[J][1] = m1; f.ring[J][2] = m2;
-  if (!out) return;
+  if (r < 2 * kR) return;
   float sv[3];
   vsum<3, J>(f.ring, win, sv);
   const int px = f.x0 + f.lane, py = f.y0 + r - 2 * kR;
@@ -302,6 +277,21 @@ __device__ __forceinline__ void bwd_step(BwdStrip& f, float (*sm)[kRowW], const 
   store_or_drop(f.ri, (1.f - f.lambda) * sgn * f.ninv - f.lambda * dssim, o);
 }
 
+template <int J>
+__device__ __forceinline__ void bwd_fill(BwdStrip& f) {
+  bwd_load<J>(f, J);
+  if constexpr (J + 1 < kTaps) bwd_fill<J + 1>(f);
+}
+
+__device__ __forceinline__ void bwd_rows(BwdStrip& f, float4* s, const Win& win) {
+#define CGV2_STEP(J)              \
+  if (r + J >= f.rows) return;    \
+  bwd_step<J>(f, s, win, r + J);
+  CGV2_STRIP_ROWS(CGV2_STEP)
+#undef CGV2_STEP
+}
+#undef CGV2_STRIP_ROWS
+
 __device__ __noinline__ void loss_final(const double* __restrict__ partial, int64_t blocks_per_view, int V, int64_t HW,
                                         float lambda, float* __restrict__ loss);
 
@@ -310,7 +300,7 @@ __global__ __launch_bounds__(64) void k_ssim_bwd(const float* __restrict__ img, 
                                                  const float* __restrict__ maps, float* __restrict__ d_img,
                                                  float* __restrict__ d_ssim, const double* __restrict__ partial,
                                                  int V, float* __restrict__ loss) {
-  __shared__ float sm[3][kRowW];
+  __shared__ float4 s[kRowW];
   if (blockIdx.x == 0) loss_final(partial, (int64_t)sg.nx * sg.ny * 3, V, (int64_t)W * H, lambda, loss);
   BwdStrip f;
   int vc;
@@ -318,6 +308,7 @@ __global__ __launch_bounds__(64) void k_ssim_bwd(const float* __restrict__ img, 
   f.W = W;
   f.H = H;
   f.lane = (int)threadIdx.x;
+  f.rows = min(sg.rows, H - f.y0) + 2 * kR;
   f.HW = (int64_t)W * H;
   f.ninv = 1.f / (3.f * (float)f.HW);
   f.lambda = lambda;
@@ -326,44 +317,8 @@ __global__ __launch_bounds__(64) void k_ssim_bwd(const float* __restrict__ img, 
   f.ry = plane_rsrc(tgt + vc * f.HW, f.HW);
   f.rs = plane_rsrc(d_ssim + vc * f.HW, f.HW);
   f.ri = plane_rsrc(d_img + vc * f.HW, f.HW);
-  bwd_load<0>(f, 0);
-  bwd_load<1>(f, 1);
-  bwd_step<0, 0>(f, sm, win, 0, false);
-  bwd_step<1, 1>(f, sm, win, 1, false);
-  bwd_step<2, 0>(f, sm, win, 2, false);
-  bwd_step<3, 1>(f, sm, win, 3, false);
-  bwd_step<4, 0>(f, sm, win, 4, false);
-  bwd_step<5, 1>(f, sm, win, 5, false);
-  bwd_step<6, 0>(f, sm, win, 6, false);
-  bwd_step<7, 1>(f, sm, win, 7, false);
-  bwd_step<8, 0>(f, sm, win, 8, false);
-  bwd_step<9, 1>(f, sm, win, 9, false);
-  bwd_step<10, 0>(f, sm, win, 10, true);
-#pragma nounroll
-  for (int r0 = kTaps; r0 < kInRows; r0 += 2 * kTaps) {
-    bwd_step<0, 1>(f, sm, win, r0 + 0, true);
-    bwd_step<1, 0>(f, sm, win, r0 + 1, true);
-    bwd_step<2, 1>(f, sm, win, r0 + 2, true);
-    bwd_step<3, 0>(f, sm, win, r0 + 3, true);
-    bwd_step<4, 1>(f, sm, win, r0 + 4, true);
-    bwd_step<5, 0>(f, sm, win, r0 + 5, true);
-    bwd_step<6, 1>(f, sm, win, r0 + 6, true);
-    bwd_step<7, 0>(f, sm, win, r0 + 7, true);
-    bwd_step<8, 1>(f, sm, win, r0 + 8, true);
-    bwd_step<9, 0>(f, sm, win, r0 + 9, true);
-    bwd_step<10, 1>(f, sm, win, r0 + 10, true);
-    bwd_step<0, 0>(f, sm, win, r0 + 11, true);
-    bwd_step<1, 1>(f, sm, win, r0 + 12, true);
-    bwd_step<2, 0>(f, sm, win, r0 + 13, true);
-    bwd_step<3, 1>(f, sm, win, r0 + 14, true);
-    bwd_step<4, 0>(f, sm, win, r0 + 15, true);
-    bwd_step<5, 1>(f, sm, win, r0 + 16, true);
-    bwd_step<6, 0>(f, sm, win, r0 + 17, true);
-    bwd_step<7, 1>(f, sm, win, r0 + 18, true);
-    bwd_step<8, 0>(f, sm, win, r0 + 19, true);
-    bwd_step<9, 1>(f, sm, win, r0 + 20, true);
-    bwd_step<10, 0>(f, sm, win, r0 + 21, true);
-  }
+  bwd_fill<0>(f);
+  bwd_rows(f, s, win);
 }
 
 // The loss values of every view from the forward's per-wave sums, in a fixed order: run by the first
@@ -396,12 +351,35 @@ __device__ __noinline__ void loss_final(const double* __restrict__ partial, int6
 
 }  // namespace cgv2
 
+// Output rows per strip: a launch lasts as long as the SIMD with the most strips, whose input rows (the output
+// rows and a 10-row halo each) cost about 0.35 us per strip when two or more share the SIMD and 0.52 us for a
+// strip alone (forward and reverse: 82 output rows, one strip per SIMD, 96 us at 1600x1066; 40 rows, two, 71;
+// 27 rows, three, 78; 45 rows, as before, 1.8 per SIMD, 80).  The cheapest height is taken, the largest of
+// equals (fewer halo rows read); small images take short strips (128x128: 50 -> 23 us).
+static cgv2::StripGrid strip_grid(int W, int H, int V) {
+  constexpr int64_t kSimds = 1024;
+  cgv2::StripGrid g;
+  g.nx = (W + cgv2::kStripW - 1) / cgv2::kStripW;
+  int64_t best = INT64_MAX;
+  for (int rows = 4; rows <= 128; ++rows) {
+    const int ny = (H + rows - 1) / rows;
+    const int64_t strips = (int64_t)g.nx * ny * 3 * V;
+    const int64_t per = (strips + kSimds - 1) / kSimds;
+    const int64_t cost = (per == 1 ? 52 : 35 * per) * (rows + 2 * cgv2::kR);
+    if (cost > best) continue;
+    best = cost;
+    g.rows = rows;
+    g.ny = ny;
+  }
+  return g;
+}
+
 size_t cgv2_loss_ws_layout(int W, int H, int V, size_t* off) {
-  const int64_t nx = (W + cgv2::kStripW - 1) / cgv2::kStripW, ny = (H + cgv2::kStripH - 1) / cgv2::kStripH;
+  const cgv2::StripGrid g = strip_grid(W, H, V);
   size_t o = 0;
   auto take = [&](size_t bytes) { size_t r = o; o += (bytes + 255) & ~(size_t)255; return r; };
   off[0] = take(sizeof(float) * 9 * (size_t)W * H * V);     // partial maps [V][3][3][H][W]
-  off[1] = take(sizeof(double) * 2 * (size_t)(nx * ny * 3 * V));  // per-wave sums
+  off[1] = take(sizeof(double) * 2 * (size_t)((int64_t)g.nx * g.ny * 3 * V));  // per-wave sums
   return o;
 }
 
@@ -415,9 +393,7 @@ hipError_t cgv2_launch_loss(const float* img, const float* tgt, int V, int W, in
   double g[11], gs = 0;
   for (int a = -5; a <= 5; ++a) { g[a + 5] = exp(-(double)(a * a) / (2 * 1.5 * 1.5)); gs += g[a + 5]; }
   for (int a = 0; a < 11; ++a) win.g[a] = (float)(g[a] / gs);
-  cgv2::StripGrid sg;
-  sg.nx = (W + cgv2::kStripW - 1) / cgv2::kStripW;
-  sg.ny = (H + cgv2::kStripH - 1) / cgv2::kStripH;
+  const cgv2::StripGrid sg = strip_grid(W, H, V);
   const unsigned blocks = (unsigned)(sg.nx * sg.ny * 3 * V);
   hipLaunchKernelGGL(cgv2::k_ssim_fwd, dim3(blocks), dim3(64), 0, st, img, tgt, W, H, win, sg, maps, partial);
   hipLaunchKernelGGL(cgv2::k_ssim_bwd, dim3(blocks), dim3(64), 0, st, img, tgt, W, H, win, sg, lambda, maps, d_img,
