@@ -131,6 +131,7 @@ __device__ __forceinline__ void load_row(const float* p, float (&v)[N]) {
   }
 }
 
+
 template <int N>
 __device__ __forceinline__ void store_row(float* p, const float (&v)[N]) {
   if constexpr (N % 4 == 0) {
@@ -194,6 +195,18 @@ struct CompactSource {
   }
 };
 
+// Unit direction (mu - C) / |mu - C| from the camera centre C = -R^T t, and the distance.
+__device__ __forceinline__ void view_dir(const DevCam& c, const double (&mu)[3], float (&dir)[3], float& dist) {
+  double v[3];
+  for (int k = 0; k < 3; ++k) {
+    const double Ck = -((double)c.R[k] * c.t[0] + (double)c.R[3 + k] * c.t[1] + (double)c.R[6 + k] * c.t[2]);
+    v[k] = mu[k] - Ck;
+  }
+  const double d = sqrt(v[0] * v[0] + v[1] * v[1] + v[2] * v[2]);
+  dist = (float)d;
+  for (int k = 0; k < 3; ++k) dir[k] = (float)(v[k] / d);
+}
+
 template <class Src>
 __device__ __forceinline__ void load_geom(const Src& s, const DevCam& c, int64_t i, Geom& g) {
   g.su = (double)expf(s.log_scale(0, i));
@@ -221,15 +234,7 @@ __device__ __forceinline__ void load_geom(const Src& s, const DevCam& c, int64_t
   }
   g.flip = (ncd[0] * g.pc[0] + ncd[1] * g.pc[1] + ncd[2] * g.pc[2]) > 0 ? -1.0 : 1.0;
   for (int r = 0; r < 3; ++r) g.nc[r] = (float)(g.flip * ncd[r]);
-  // camera centre C = -R^T t
-  double v[3];
-  for (int k = 0; k < 3; ++k) {
-    const double Ck = -((double)c.R[k] * c.t[0] + (double)c.R[3 + k] * c.t[1] + (double)c.R[6 + k] * c.t[2]);
-    v[k] = mu[k] - Ck;
-  }
-  const double d = sqrt(v[0] * v[0] + v[1] * v[1] + v[2] * v[2]);
-  g.dist = (float)d;
-  for (int k = 0; k < 3; ++k) g.dir[k] = (float)(v[k] / d);
+  view_dir(c, mu, g.dir, g.dist);
 }
 
 // Centre, inverse-homography coefficients (unscaled) in the centre-shifted pixel frame.
@@ -370,158 +375,376 @@ __global__ __launch_bounds__(256) void k_project_compact(cgv2_surfels_compact s,
 // ------------------------------------------------------------------------------------------
 // Reverse: record gradients of every view -> parameter gradients (+=), view-space gradients.
 // ------------------------------------------------------------------------------------------
+// A surfel's loads for one view: record gradients, the gradients being added to, the geometry.
+struct BwdIn {
+  float d[kGradFields], gmu[3], gq[4], gls[2], glo;
+  Geom g;
+};
+
+__device__ __forceinline__ void project_bwd_load(const cgv2_surfels& s, const DevCam& c, int v, const RecGrads& rg,
+                                                 const cgv2_grads& gr, int64_t i, BwdIn& in) {
+  const int64_t n = s.n;
+  float(&d)[kGradFields] = in.d;
+  float(&gmu)[3] = in.gmu;
+  float(&gq)[4] = in.gq;
+  float(&gls)[2] = in.gls;
+  float& glo = in.glo;
+  {
+    const float4* r = (const float4*)(rg.row + ((int64_t)v * n + i) * kGradRow);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const float4 q = r[k];
+      d[4 * k] = q.x;
+      d[4 * k + 1] = q.y;
+      d[4 * k + 2] = q.z;
+      d[4 * k + 3] = q.w;
+    }
+    const float4 q = *(const float4*)(rg.nrm + ((int64_t)v * n + i) * kGradNrm);
+    d[G_NX] = q.x;
+    d[G_NY] = q.y;
+    d[G_NZ] = q.z;
+  }
+#pragma unroll
+  for (int k = 0; k < 3; ++k) gmu[k] = gr.d_mean[k * n + i];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) gq[k] = gr.d_quat[k * n + i];
+  gls[0] = gr.d_log_scale[i];
+  gls[1] = gr.d_log_scale[n + i];
+  glo = gr.d_opacity_logit[i];
+  load_geom(FullSource{s}, c, i, in.g);
+}
+
+// The FP64 chain of one surfel and view from the loads to the stores of everything but the SH gradients;
+// direction(d, dir, ddir) gives the gradient with respect to the view direction.
+template <class Direction>
+__device__ __forceinline__ void project_bwd_chain(const cgv2_surfels& s, const DevCam& c, int v, const cgv2_grads& gr,
+                                                  int64_t i, const BwdIn& in, Direction direction) {
+  const int64_t n = s.n;
+  const float(&d)[kGradFields] = in.d;
+  const float(&gmu)[3] = in.gmu;
+  const float(&gq)[4] = in.gq;
+  const float(&gls)[2] = in.gls;
+  const float glo = in.glo;
+  const Geom& g = in.g;
+
+  // ---- record -> (alpha, beta, gamma) -> M; the common scale of the coefficients leaves every
+  // output unchanged, so it is held constant
+  double dmu[3] = {0, 0, 0}, dq[4] = {0, 0, 0, 0};
+  Homog h;
+  homography(g.M, h);
+  const double* M = g.M;
+  const double sc = h.scale;
+  const double dA11 = d[G_A11] * sc, dA12 = d[G_A12] * sc, dA21 = d[G_A21] * sc, dA22 = d[G_A22] * sc;
+  const double dW0 = d[G_W0] * sc, dW1 = d[G_W1] * sc, dW2 = d[G_W2] * sc;
+  const double g1 = M[6], g2 = M[7], g3 = M[8];
+  const double dal1 = dA22 * g3 + dW0 * h.be2 - dW2 * g2;
+  const double dal2 = -dA12 * g3 - dW0 * h.be1 + dW2 * g1;
+  const double dbe1 = -dA21 * g3 - dW0 * h.al2 + dW1 * g2;
+  const double dbe2 = dA11 * g3 + dW0 * h.al1 - dW1 * g1;
+  const double dg1 = -dW1 * h.be2 + dW2 * h.al2;
+  const double dg2 = dW1 * h.be1 - dW2 * h.al1;
+  const double dg3 = dA11 * h.be2 - dA12 * h.al2 - dA21 * h.be1 + dA22 * h.al1 + d[G_ZC];
+  double dM[9];
+  dM[0] = dal1; dM[1] = dal2; dM[3] = dbe1; dM[4] = dbe2;
+  dM[6] = dg1 - dal1 * h.cx - dbe1 * h.cy;
+  dM[7] = dg2 - dal2 * h.cx - dbe2 * h.cy;
+  const double dcx = (double)d[G_CX] - dal1 * M[6] - dal2 * M[7];
+  const double dcy = (double)d[G_CY] - dbe1 * M[6] - dbe2 * M[7];
+  dM[2] = dcx / M[8];
+  dM[5] = dcy / M[8];
+  dM[8] = dg3 - (dcx * h.cx + dcy * h.cy) / M[8];
+  // M columns = K_int [cu | cv | pc]
+  double vw[3][3];
+  for (int k = 0; k < 3; ++k) {
+    const double a = (double)c.fx * dM[k], b = (double)c.fy * dM[3 + k];
+    const double e2 = (double)c.cx * dM[k] + (double)c.cy * dM[3 + k] + dM[6 + k];
+    for (int r2 = 0; r2 < 3; ++r2) vw[k][r2] = (double)c.R[r2] * a + (double)c.R[3 + r2] * b + (double)c.R[6 + r2] * e2;
+  }
+  double dsu = 0, dsv = 0, dR[9];
+  for (int r2 = 0; r2 < 3; ++r2) {
+    dsu += vw[0][r2] * g.Rw[3 * r2];
+    dsv += vw[1][r2] * g.Rw[3 * r2 + 1];
+    dR[3 * r2] = g.su * vw[0][r2];
+    dR[3 * r2 + 1] = g.sv * vw[1][r2];
+    dmu[r2] += vw[2][r2];
+  }
+  const double dn[3] = {d[G_NX], d[G_NY], d[G_NZ]};
+  for (int r2 = 0; r2 < 3; ++r2)
+    dR[3 * r2 + 2] = g.flip * ((double)c.R[r2] * dn[0] + (double)c.R[3 + r2] * dn[1] + (double)c.R[6 + r2] * dn[2]);
+  // rotation -> normalised quaternion
+  {
+    const double w = g.qn[0], x = g.qn[1], y = g.qn[2], z = g.qn[3];
+    double dqn[4];
+    dqn[0] = -2 * z * dR[1] + 2 * y * dR[2] + 2 * z * dR[3] - 2 * x * dR[5] - 2 * y * dR[6] + 2 * x * dR[7];
+    dqn[1] = 2 * y * dR[1] + 2 * z * dR[2] + 2 * y * dR[3] - 4 * x * dR[4] - 2 * w * dR[5] + 2 * z * dR[6] +
+             2 * w * dR[7] - 4 * x * dR[8];
+    dqn[2] = -4 * y * dR[0] + 2 * x * dR[1] + 2 * w * dR[2] + 2 * x * dR[3] + 2 * z * dR[5] - 2 * w * dR[6] +
+             2 * z * dR[7] - 4 * y * dR[8];
+    dqn[3] = -4 * z * dR[0] - 2 * w * dR[1] + 2 * x * dR[2] + 2 * w * dR[3] - 4 * z * dR[4] + 2 * y * dR[5] +
+             2 * x * dR[6] + 2 * y * dR[7];
+    const double dot = g.qn[0] * dqn[0] + g.qn[1] * dqn[1] + g.qn[2] * dqn[2] + g.qn[3] * dqn[3];
+    for (int k = 0; k < 4; ++k) dq[k] += (dqn[k] - g.qn[k] * dot) / g.qlen;
+  }
+  const double dls0 = dsu * g.su, dls1 = dsv * g.sv;
+  const double dlogit = (double)d[G_OP] * g.o * (1 - g.o);
+  float ddir[3];
+  direction(d, g.dir, ddir);
+  const float dd = ddir[0] * g.dir[0] + ddir[1] * g.dir[1] + ddir[2] * g.dir[2];
+  for (int k = 0; k < 3; ++k) dmu[k] += (double)((ddir[k] - g.dir[k] * dd) / g.dist);
+
+  // ---- stores
+  if (gr.g_view_total) {
+    float* gvt = gr.g_view_total + (int64_t)v * 2 * n;
+    gvt[i] = d[G_CX] * (0.5f * (float)c.W);
+    gvt[n + i] = d[G_CY] * (0.5f * (float)c.H);
+  }
+  if (gr.g_view_ssim) {
+    float* gvs = gr.g_view_ssim + (int64_t)v * 2 * n;
+    gvs[i] = d[G_SCX] * (0.5f * (float)c.W);
+    gvs[n + i] = d[G_SCY] * (0.5f * (float)c.H);
+  }
+#pragma unroll
+  for (int k = 0; k < 3; ++k) gr.d_mean[k * n + i] = gmu[k] + (float)dmu[k];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) gr.d_quat[k * n + i] = gq[k] + (float)dq[k];
+  gr.d_log_scale[i] = gls[0] + (float)dls0;
+  gr.d_log_scale[n + i] = gls[1] + (float)dls1;
+  gr.d_opacity_logit[i] = glo + (float)dlogit;
+}
+
 // One view (cams.c[0], view index cams.v0), one thread per entry of its visible list
 // (list[vstart[0] .. vstart[1])); each surfel appears once per list, so the parameter gradients are
 // added without atomics.  Every load of a surfel (parameters, record gradients, the gradient values
 // being added to) is issued before its first store: the stores may alias the loaded arrays, so an
 // interleaved read-modify-write would cost one full memory round trip per element.
 template <int DEG>
-__global__ __launch_bounds__(64) void k_project_bwd(cgv2_surfels s, CamPack cams,
-                                                      const uint32_t* __restrict__ list,
-                                                      const uint32_t* __restrict__ vstart,
-                                                      RecGrads rg, cgv2_grads gr) {
-  const int64_t n = s.n;
+__global__ __launch_bounds__(64) void k_project_bwd(cgv2_surfels s, CamPack cams, const uint32_t* __restrict__ list,
+                                                    const uint32_t* __restrict__ vstart, RecGrads rg, cgv2_grads gr) {
   const uint32_t e0 = vstart[0], e1 = vstart[1];
   constexpr int K = (DEG + 1) * (DEG + 1);
   const int v = cams.v0;
   const DevCam& c = cams.c[0];
   for (uint32_t e = e0 + blockIdx.x * blockDim.x + threadIdx.x; e < e1; e += gridDim.x * blockDim.x) {
     const int64_t i = list[e];
-    // ---- loads
-    float d[kGradFields];
-    {
-      const float4* r = (const float4*)(rg.row + ((int64_t)v * n + i) * kGradRow);
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        const float4 q = r[k];
-        d[4 * k] = q.x;
-        d[4 * k + 1] = q.y;
-        d[4 * k + 2] = q.z;
-        d[4 * k + 3] = q.w;
-      }
-      const float4 q = *(const float4*)(rg.nrm + ((int64_t)v * n + i) * kGradNrm);
-      d[G_NX] = q.x;
-      d[G_NY] = q.y;
-      d[G_NZ] = q.z;
-    }
     float f[3 * K], gsh[3 * K];  // index k * 3 + channel
+    BwdIn in;
     load_row<3 * K>(s.sh + i * 3 * K, f);
     load_row<3 * K>(gr.d_sh + i * 3 * K, gsh);
-    float gmu[3], gq[4], gls[2], glo;
+    project_bwd_load(s, c, v, rg, gr, i, in);
+    project_bwd_chain(s, c, v, gr, i, in, [&](const float(&d)[kGradFields], const float(&dir)[3], float(&ddir)[3]) {
+      // colour through SH: the coefficient gradients are added per view, the direction gradient is
+      // contracted on the fly; a channel clamped at zero passes nothing
+      float Y[K], gY[K];
+      sh_basis<DEG>(dir[0], dir[1], dir[2], Y, nullptr);
 #pragma unroll
-    for (int k = 0; k < 3; ++k) gmu[k] = gr.d_mean[k * n + i];
+      for (int k = 0; k < K; ++k) gY[k] = 0.f;
+      const float dcol[3] = {d[G_R], d[G_G], d[G_B]};
 #pragma unroll
-    for (int k = 0; k < 4; ++k) gq[k] = gr.d_quat[k * n + i];
-    gls[0] = gr.d_log_scale[i];
-    gls[1] = gr.d_log_scale[n + i];
-    glo = gr.d_opacity_logit[i];
-    Geom g;
-    load_geom(FullSource{s}, c, i, g);
+      for (int ch = 0; ch < 3; ++ch) {
+        float raw = 0.5f;
+#pragma unroll
+        for (int k = 0; k < K; ++k) raw = fmaf(f[k * 3 + ch], Y[k], raw);
+        const float dc = raw < 0.f ? 0.f : dcol[ch];
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+          gY[k] = fmaf(dc, f[k * 3 + ch], gY[k]);
+          gsh[k * 3 + ch] = fmaf(dc, Y[k], gsh[k * 3 + ch]);
+        }
+      }
+      sh_grad_dot<DEG>(gY, dir[0], dir[1], dir[2], ddir);
+      // channels clamped at zero store their unchanged values back
+      store_row<3 * K>(gr.d_sh + i * 3 * K, gsh);
+    });
+  }
+}
 
-    // ---- record -> (alpha, beta, gamma) -> M; the common scale of the coefficients leaves every
-    // output unchanged, so it is held constant
-    double dmu[3] = {0, 0, 0}, dq[4] = {0, 0, 0, 0};
-    Homog h;
-    homography(g.M, h);
-    const double* M = g.M;
-    const double sc = h.scale;
-    const double dA11 = d[G_A11] * sc, dA12 = d[G_A12] * sc, dA21 = d[G_A21] * sc, dA22 = d[G_A22] * sc;
-    const double dW0 = d[G_W0] * sc, dW1 = d[G_W1] * sc, dW2 = d[G_W2] * sc;
-    const double g1 = M[6], g2 = M[7], g3 = M[8];
-    const double dal1 = dA22 * g3 + dW0 * h.be2 - dW2 * g2;
-    const double dal2 = -dA12 * g3 - dW0 * h.be1 + dW2 * g1;
-    const double dbe1 = -dA21 * g3 - dW0 * h.al2 + dW1 * g2;
-    const double dbe2 = dA11 * g3 + dW0 * h.al1 - dW1 * g1;
-    const double dg1 = -dW1 * h.be2 + dW2 * h.al2;
-    const double dg2 = dW1 * h.be1 - dW2 * h.al1;
-    const double dg3 = dA11 * h.be2 - dA12 * h.al2 - dA21 * h.be1 + dA22 * h.al1 + d[G_ZC];
-    double dM[9];
-    dM[0] = dal1; dM[1] = dal2; dM[3] = dbe1; dM[4] = dbe2;
-    dM[6] = dg1 - dal1 * h.cx - dbe1 * h.cy;
-    dM[7] = dg2 - dal2 * h.cx - dbe2 * h.cy;
-    const double dcx = (double)d[G_CX] - dal1 * M[6] - dal2 * M[7];
-    const double dcy = (double)d[G_CY] - dbe1 * M[6] - dbe2 * M[7];
-    dM[2] = dcx / M[8];
-    dM[5] = dcy / M[8];
-    dM[8] = dg3 - (dcx * h.cx + dcy * h.cy) / M[8];
-    // M columns = K_int [cu | cv | pc]
-    double vw[3][3];
-    for (int k = 0; k < 3; ++k) {
-      const double a = (double)c.fx * dM[k], b = (double)c.fy * dM[3 + k];
-      const double e2 = (double)c.cx * dM[k] + (double)c.cy * dM[3 + k] + dM[6 + k];
-      for (int r2 = 0; r2 < 3; ++r2) vw[k][r2] = (double)c.R[r2] * a + (double)c.R[3 + r2] * b + (double)c.R[6 + r2] * e2;
-    }
-    double dsu = 0, dsv = 0, dR[9];
-    for (int r2 = 0; r2 < 3; ++r2) {
-      dsu += vw[0][r2] * g.Rw[3 * r2];
-      dsv += vw[1][r2] * g.Rw[3 * r2 + 1];
-      dR[3 * r2] = g.su * vw[0][r2];
-      dR[3 * r2 + 1] = g.sv * vw[1][r2];
-      dmu[r2] += vw[2][r2];
-    }
-    const double dn[3] = {d[G_NX], d[G_NY], d[G_NZ]};
-    for (int r2 = 0; r2 < 3; ++r2)
-      dR[3 * r2 + 2] = g.flip * ((double)c.R[r2] * dn[0] + (double)c.R[3 + r2] * dn[1] + (double)c.R[6 + r2] * dn[2]);
-    // rotation -> normalised quaternion
-    {
-      const double w = g.qn[0], x = g.qn[1], y = g.qn[2], z = g.qn[3];
-      double dqn[4];
-      dqn[0] = -2 * z * dR[1] + 2 * y * dR[2] + 2 * z * dR[3] - 2 * x * dR[5] - 2 * y * dR[6] + 2 * x * dR[7];
-      dqn[1] = 2 * y * dR[1] + 2 * z * dR[2] + 2 * y * dR[3] - 4 * x * dR[4] - 2 * w * dR[5] + 2 * z * dR[6] +
-               2 * w * dR[7] - 4 * x * dR[8];
-      dqn[2] = -4 * y * dR[0] + 2 * x * dR[1] + 2 * w * dR[2] + 2 * x * dR[3] + 2 * z * dR[5] - 2 * w * dR[6] +
-               2 * z * dR[7] - 4 * y * dR[8];
-      dqn[3] = -4 * z * dR[0] - 2 * w * dR[1] + 2 * x * dR[2] + 2 * w * dR[3] - 4 * z * dR[4] + 2 * y * dR[5] +
-               2 * x * dR[6] + 2 * y * dR[7];
-      const double dot = g.qn[0] * dqn[0] + g.qn[1] * dqn[1] + g.qn[2] * dqn[2] + g.qn[3] * dqn[3];
-      for (int k = 0; k < 4; ++k) dq[k] += (dqn[k] - g.qn[k] * dot) / g.qlen;
-    }
-    const double dls0 = dsu * g.su, dls1 = dsv * g.sv;
-    const double dlogit = (double)d[G_OP] * g.o * (1 - g.o);
-    // colour through SH: the coefficient gradients are added per view, the direction gradient is
-    // contracted on the fly; a channel clamped at zero passes nothing
-    float Y[K], gY[K];
-    sh_basis<DEG>(g.dir[0], g.dir[1], g.dir[2], Y, nullptr);
+// The SH part of project_bwd for a wave's surfels (ids[0 .. entries), in: direction and colour gradients), by
+// four lanes per surfel: a surfel's row (384 of its 776 bytes at degree 3, with its gradients) is read and
+// written by neighbouring lanes and takes 24 registers of a lane instead of 96.  Leaves the direction
+// gradients in ddir_out.  Loads go before stores: the stores may alias the loaded arrays.
+template <int DEG>
+__device__ __forceinline__ void sh_bwd(const float* __restrict__ in, const float* sh, float* d_sh, uint32_t entries,
+                                       const int64_t* ids, float* ddir_out) {
+  constexpr int K = (DEG + 1) * (DEG + 1);
+  constexpr int J = (K + 3) / 4;  // coefficients per lane
+  // whole float4s per lane: lane q holds 4 q .. 4 q + 3
+  constexpr bool kWide = K % 16 == 0;
+  constexpr int kBatch = 2;       // surfels of a lane in flight
+  const uint32_t q = threadIdx.x & 3u, slot = (threadIdx.x & 63u) >> 2;
+#pragma unroll 1
+  for (uint32_t s0 = 0; s0 < 64u; s0 += 16u * kBatch) {
+    float f[kBatch][J][3], g[kBatch][J][3];
 #pragma unroll
-    for (int k = 0; k < K; ++k) gY[k] = 0.f;
-    const float dcol[3] = {d[G_R], d[G_G], d[G_B]};
+    for (int b = 0; b < kBatch; ++b) {
+      const uint32_t sl = s0 + 16u * b + slot;
+      const int64_t row = sl < entries ? ids[sl] * 3 * K : 0;
+      if constexpr (kWide) {
+        const float4* pf = (const float4*)(sh + row + 3 * J * q);
+        const float4* pg = (const float4*)(d_sh + row + 3 * J * q);
 #pragma unroll
-    for (int ch = 0; ch < 3; ++ch) {
-      float raw = 0.5f;
+        for (int m = 0; m < 3 * J / 4; ++m) {
+          const float4 u = pf[m], w = pg[m];
+          float* fb = &f[b][0][0] + 4 * m;
+          float* gb = &g[b][0][0] + 4 * m;
+          fb[0] = u.x; fb[1] = u.y; fb[2] = u.z; fb[3] = u.w;
+          gb[0] = w.x; gb[1] = w.y; gb[2] = w.z; gb[3] = w.w;
+        }
+        continue;
+      }
 #pragma unroll
-      for (int k = 0; k < K; ++k) raw = fmaf(f[k * 3 + ch], Y[k], raw);
-      const float dc = raw < 0.f ? 0.f : dcol[ch];
+      for (int j = 0; j < J; ++j) {
+        const uint32_t k = q + 4u * j;
+        const bool on = sl < entries && k < (uint32_t)K;
 #pragma unroll
-      for (int k = 0; k < K; ++k) {
-        gY[k] = fmaf(dc, f[k * 3 + ch], gY[k]);
-        gsh[k * 3 + ch] = fmaf(dc, Y[k], gsh[k * 3 + ch]);
+        for (int ch = 0; ch < 3; ++ch) {
+          f[b][j][ch] = on ? sh[row + 3 * k + ch] : 0.f;
+          g[b][j][ch] = on ? d_sh[row + 3 * k + ch] : 0.f;
+        }
       }
     }
-    float ddir[3];
-    sh_grad_dot<DEG>(gY, g.dir[0], g.dir[1], g.dir[2], ddir);
-    const float dd = ddir[0] * g.dir[0] + ddir[1] * g.dir[1] + ddir[2] * g.dir[2];
-    for (int k = 0; k < 3; ++k) dmu[k] += (double)((ddir[k] - g.dir[k] * dd) / g.dist);
+#pragma unroll
+    for (int b = 0; b < kBatch; ++b) {
+      const uint32_t sl = s0 + 16u * b + slot;
+      if (s0 + 16u * b >= entries) break;  // wave-uniform
+      const float* p = in + 6u * min(sl, entries - 1u);
+      const float x = p[0], y = p[1], z = p[2];
+      float Y[K], Yj[J];
+      sh_basis<DEG>(x, y, z, Y, nullptr);
+#pragma unroll
+      for (int j = 0; j < J; ++j) {
+        if constexpr (kWide) {
+          Yj[j] = (q & 2u) ? ((q & 1u) ? Y[3 * J + j] : Y[2 * J + j]) : ((q & 1u) ? Y[J + j] : Y[j]);
+          continue;
+        }
+        const float y0 = Y[4 * j], y1 = 4 * j + 1 < K ? Y[4 * j + 1 < K ? 4 * j + 1 : 0] : 0.f;
+        const float y2 = 4 * j + 2 < K ? Y[4 * j + 2 < K ? 4 * j + 2 : 0] : 0.f;
+        const float y3 = 4 * j + 3 < K ? Y[4 * j + 3 < K ? 4 * j + 3 : 0] : 0.f;
+        Yj[j] = (q & 2u) ? ((q & 1u) ? y3 : y2) : ((q & 1u) ? y1 : y0);
+      }
+      // colour through SH: a channel clamped at zero passes nothing
+      float dc[3];
+#pragma unroll
+      for (int ch = 0; ch < 3; ++ch) {
+        float raw = 0.f;
+#pragma unroll
+        for (int j = 0; j < J; ++j) raw = fmaf(f[b][j][ch], Yj[j], raw);
+        raw += dpp<0xB1>(raw);  // the quad's sum
+        raw += dpp<0x4E>(raw);
+        dc[ch] = 0.5f + raw < 0.f ? 0.f : p[3 + ch];
+      }
+      float gY[4 * J];
+#pragma unroll
+      for (int j = 0; j < J; ++j) {
+        const float w = fmaf(dc[0], f[b][j][0], fmaf(dc[1], f[b][j][1], dc[2] * f[b][j][2]));
+        // every lane of the quad gets the four lanes' values
+        gY[kWide ? j : 4 * j] = dpp<0x00>(w);
+        gY[kWide ? J + j : 4 * j + 1] = dpp<0x55>(w);
+        gY[kWide ? 2 * J + j : 4 * j + 2] = dpp<0xAA>(w);
+        gY[kWide ? 3 * J + j : 4 * j + 3] = dpp<0xFF>(w);
+      }
+      float ddir[3];
+      sh_grad_dot<DEG>(gY, x, y, z, ddir);
+      if (sl < entries) {
+        if (q < 3u) ddir_out[3u * sl + q] = q == 0u ? ddir[0] : q == 1u ? ddir[1] : ddir[2];
+        const int64_t row = ids[sl] * 3 * K;
+        if constexpr (kWide) {
+          float o[3 * J];
+#pragma unroll
+          for (int j = 0; j < J; ++j)
+#pragma unroll
+            for (int ch = 0; ch < 3; ++ch) o[3 * j + ch] = fmaf(dc[ch], Yj[j], g[b][j][ch]);
+          float4* po = (float4*)(d_sh + row + 3 * J * q);
+#pragma unroll
+          for (int m = 0; m < 3 * J / 4; ++m) po[m] = make_float4(o[4 * m], o[4 * m + 1], o[4 * m + 2], o[4 * m + 3]);
+          continue;
+        }
+#pragma unroll
+        for (int j = 0; j < J; ++j) {
+          const uint32_t k = q + 4u * j;
+          if (k >= (uint32_t)K) continue;
+          // channels clamped at zero store their unchanged values back
+#pragma unroll
+          for (int ch = 0; ch < 3; ++ch) d_sh[row + 3 * k + ch] = fmaf(dc[ch], Yj[j], g[b][j][ch]);
+        }
+      }
+    }
+  }
+}
 
-    // ---- stores
-    if (gr.g_view_total) {
-      float* gvt = gr.g_view_total + (int64_t)v * 2 * n;
-      gvt[i] = d[G_CX] * (0.5f * (float)c.W);
-      gvt[n + i] = d[G_CY] * (0.5f * (float)c.H);
-    }
-    if (gr.g_view_ssim) {
-      float* gvs = gr.g_view_ssim + (int64_t)v * 2 * n;
-      gvs[i] = d[G_SCX] * (0.5f * (float)c.W);
-      gvs[n + i] = d[G_SCY] * (0.5f * (float)c.H);
-    }
-    // channels clamped at zero store their unchanged values back
-    store_row<3 * K>(gr.d_sh + i * 3 * K, gsh);
+// LDS of a wave's 64 surfels.
+struct BwdLds {
+  float in[64 * 6], ddir[64 * 3];
+  int64_t ids[64];
+};
+
+// One wave's surfels of one view: lane l handles surfel i when l < entries.
+template <int DEG>
+__device__ __forceinline__ void project_bwd_wave(const cgv2_surfels& s, const DevCam& c, int v, const RecGrads& rg,
+                                                 const cgv2_grads& gr, BwdLds& lds, uint32_t entries, int64_t i) {
+  const int64_t n = s.n;
+  const bool live = threadIdx.x < entries;
+  if (live) {
+    const double mu[3] = {s.mean[i], s.mean[n + i], s.mean[2 * n + i]};
+    float dir[3], dist;
+    view_dir(c, mu, dir, dist);
+    const float* r = rg.row + ((int64_t)v * n + i) * kGradRow;
+    lds.ids[threadIdx.x] = i;
 #pragma unroll
-    for (int k = 0; k < 3; ++k) gr.d_mean[k * n + i] = gmu[k] + (float)dmu[k];
+    for (int k = 0; k < 3; ++k) {
+      lds.in[6u * threadIdx.x + k] = dir[k];
+      lds.in[6u * threadIdx.x + 3 + k] = r[G_R + k];
+    }
+  }
+  __syncthreads();
+  sh_bwd<DEG>(lds.in, s.sh, gr.d_sh, entries, lds.ids, lds.ddir);
+  __syncthreads();
+  if (!live) return;
+  BwdIn in;
+  project_bwd_load(s, c, v, rg, gr, i, in);
+  project_bwd_chain(s, c, v, gr, i, in, [&](const float(&)[kGradFields], const float(&)[3], float(&ddir)[3]) {
 #pragma unroll
-    for (int k = 0; k < 4; ++k) gr.d_quat[k * n + i] = gq[k] + (float)dq[k];
-    gr.d_log_scale[i] = gls[0] + (float)dls0;
-    gr.d_log_scale[n + i] = gls[1] + (float)dls1;
-    gr.d_opacity_logit[i] = glo + (float)dlogit;
+    for (int k = 0; k < 3; ++k) ddir[k] = lds.ddir[3u * threadIdx.x + k];
+  });
+}
+
+// Several views: a wave takes kRange consecutive surfels and goes through the views, so that
+// the parameter and gradient lines of neighbouring surfels, and of one surfel in several views, are still in
+// the caches (a visible surfel touches some 30 sectors of the planar arrays, of which 4 % of the floats are
+// used in one view), and the view-space gradients of a view (zero outside its list) are written once, in
+// order.  10 M surfels, 8 views: 2,670 us with a launch per view and the zeroing before -> 1,930; 4 M, 4
+// views: 499 -> 391; ranges of 1,024 and 256: 2,500 and 2,130 (before the float4 rows).
+constexpr int kRange = 512;
+
+template <int DEG>
+__global__ __launch_bounds__(64, 2) void k_project_bwd_views(cgv2_surfels s, CamPack cams,
+                                                            const uint8_t* __restrict__ flags, RecGrads rg,
+                                                            cgv2_grads gr) {
+  __shared__ BwdLds lds;
+  __shared__ uint16_t list[kRange];
+  const int64_t n = s.n, i0 = (int64_t)blockIdx.x * kRange;
+  const unsigned long long lt = (1ull << threadIdx.x) - 1ull;
+  for (int lv = 0; lv < cams.count; ++lv) {
+    const int v = cams.v0 + lv;
+    uint32_t count = 0;
+    for (int k = 0; k < kRange; k += 64) {
+      const int64_t i = i0 + k + threadIdx.x;
+      const bool vis = i < n && (flags[(int64_t)v * n + i] & CGV2_F_VISIBLE);
+      const unsigned long long b = __ballot(vis);
+      if (vis) list[count + __popcll(b & lt)] = (uint16_t)(k + threadIdx.x);
+      count += (uint32_t)__popcll(b);
+      if (i < n && !vis) {
+        const int64_t at = (int64_t)v * 2 * n + i;
+        if (gr.g_view_total) gr.g_view_total[at] = gr.g_view_total[at + n] = 0.f;
+        if (gr.g_view_ssim) gr.g_view_ssim[at] = gr.g_view_ssim[at + n] = 0.f;
+      }
+    }
+    __syncthreads();
+    for (uint32_t base = 0; base < count; base += 64u) {
+      const uint32_t entries = min(64u, count - base);
+      const int64_t i = threadIdx.x < entries ? i0 + list[base + threadIdx.x] : 0;
+      project_bwd_wave<DEG>(s, cams.c[lv], v, rg, gr, lds, entries, i);
+      __syncthreads();  // also orders this view's gradient stores before the next view's loads
+    }
   }
 }
 
@@ -595,10 +818,25 @@ hipError_t cgv2_launch_zero_grads(const cgv2_grads& g, int64_t n, int sh_degree,
   return hipGetLastError();
 }
 
+// Several views of many surfels go through k_project_bwd_views; below kViewsMin a launch per view is as fast (us:
+// 4 M surfels, 2 views 240 -> 233 through the views; 1 M, 5 views 120 -> 122; 132 k, 8 views 73 -> 80) and the
+// range would no longer fill the chip.
+constexpr int64_t kViewsMin = 2000000;
+
 hipError_t cgv2_launch_project_bwd(const cgv2_surfels& s, const cgv2::CamPack& cams, const cgv2_proj& p,
                                    const cgv2::RecGrads& rg, const cgv2_grads& g, hipStream_t st) {
   if (s.n == 0) return hipSuccess;
   const int64_t n = s.n;
+  if (cams.count > 1 && n >= kViewsMin) {
+    const dim3 grid((unsigned)((n + cgv2::kRange - 1) / cgv2::kRange));
+    switch (s.sh_degree) {
+      case 0: hipLaunchKernelGGL(cgv2::k_project_bwd_views<0>, grid, dim3(64), 0, st, s, cams, p.flags, rg, g); break;
+      case 1: hipLaunchKernelGGL(cgv2::k_project_bwd_views<1>, grid, dim3(64), 0, st, s, cams, p.flags, rg, g); break;
+      case 2: hipLaunchKernelGGL(cgv2::k_project_bwd_views<2>, grid, dim3(64), 0, st, s, cams, p.flags, rg, g); break;
+      default: hipLaunchKernelGGL(cgv2::k_project_bwd_views<3>, grid, dim3(64), 0, st, s, cams, p.flags, rg, g); break;
+    }
+    return hipGetLastError();
+  }
   // one wave per workgroup: the visible surfels (a few percent of n) then spread over every CU instead
   // of filling the first few with four-wave workgroups
   const unsigned blocks = (unsigned)std::min<int64_t>((n + 63) / 64, 16384);
