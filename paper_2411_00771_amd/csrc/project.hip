@@ -711,8 +711,8 @@ __device__ __forceinline__ void project_bwd_wave(const cgv2_surfels& s, const De
 // the parameter and gradient lines of neighbouring surfels, and of one surfel in several views, are still in
 // the caches (a visible surfel touches some 30 sectors of the planar arrays, of which 4 % of the floats are
 // used in one view), and the view-space gradients of a view (zero outside its list) are written once, in
-// order.  10 M surfels, 8 views: 2,670 us with a launch per view and the zeroing before -> 1,930; 4 M, 4
-// views: 499 -> 391; ranges of 1,024 and 256: 2,500 and 2,130 (before the float4 rows).
+// order.  10 M surfels, 8 views: 2,700 us with a launch per view and the zeroing before -> 1,940; 4 M, 4
+// views: 477 -> 386; ranges of 1,024 and 256: 2,500 and 2,130 (before the float4 rows).
 constexpr int kRange = 512;
 
 template <int DEG>
@@ -819,7 +819,7 @@ hipError_t cgv2_launch_zero_grads(const cgv2_grads& g, int64_t n, int sh_degree,
 }
 
 // Several views of many surfels go through k_project_bwd_views; below kViewsMin a launch per view is as fast (us:
-// 4 M surfels, 2 views 240 -> 233 through the views; 1 M, 5 views 120 -> 122; 132 k, 8 views 73 -> 80) and the
+// 4 M surfels, 2 views 240 -> 214 through the views; 1 M, 5 views 120 -> 122; 132 k, 8 views 73 -> 80) and the
 // range would no longer fill the chip.
 constexpr int64_t kViewsMin = 2000000;
 
