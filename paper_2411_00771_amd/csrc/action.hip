@@ -12,7 +12,7 @@
 //   k_src_fill   inverse map slot -> (source id, kind: survivor, copy, child 0, child 1)
 //   k_apply      geometry of each slot (a split child is placed in FP64 and rounded once), then the
 //                slots' SH blocks copied by the whole workgroup
-//   k_gather     the same re-layout for any other per-surfel float field
+//   k_gather_*   the same re-layout for any other per-surfel float field
 #include "cgv2r_device.h"
 #include "cgv2r_kernels.h"
 
@@ -28,19 +28,19 @@ constexpr uint32_t kNone = 0xffffffffu;
 enum : uint32_t { A_KEEP = 0, A_CLONE = 1, A_SPLIT = 2, A_REMOVE = 3 };
 enum : uint32_t { S_SURVIVOR = 0, S_COPY = 1, S_CHILD0 = 2, S_CHILD1 = 3 };
 
-// The action of surfel i, decided in FP64 on the float32 parameters.
-__device__ __forceinline__ uint32_t action_of(const uint8_t* __restrict__ mask, const uint8_t* __restrict__ remove,
-                                              const float* __restrict__ ls, const float* __restrict__ logit,
-                                              int64_t n, int64_t i, double dense_scale, double min_opacity) {
-  const double o = 1.0 / (1.0 + exp(-(double)logit[i]));
-  if ((remove && remove[i]) || o < min_opacity) return A_REMOVE;
-  if (!(mask[i] & 4u)) return A_KEEP;
-  const double smax = fmax(exp((double)ls[i]), exp((double)ls[n + i]));
+// The action of a surfel, decided in FP64 on the float32 parameters.
+__device__ __forceinline__ uint32_t action_of(bool cand, bool remove, float l0, float l1, float logit,
+                                              double dense_scale, double min_opacity) {
+  const double o = 1.0 / (1.0 + exp(-(double)logit));
+  if (remove || o < min_opacity) return A_REMOVE;
+  if (!cand) return A_KEEP;
+  const double smax = fmax(exp((double)l0), exp((double)l1));
   return smax <= dense_scale ? A_CLONE : A_SPLIT;
 }
 
 // Items k * kABlock + thread of the workgroup's chunk: every load and the action store are coalesced
-// (the counts need no order).
+// (the counts need no order).  Few waves: the chunk's loads are all in flight before the first action (1 M
+// surfels 18.2 us with one surfel after the other, 13.4 now).
 __global__ __launch_bounds__(kABlock) void k_act_count(const uint8_t* __restrict__ mask,
                                                        const uint8_t* __restrict__ remove,
                                                        const float* __restrict__ ls,
@@ -51,11 +51,23 @@ __global__ __launch_bounds__(kABlock) void k_act_count(const uint8_t* __restrict
   const int64_t base = (int64_t)blockIdx.x * kAChunk + threadIdx.x;
   // four counts of at most kAChunk each, 16 bits apiece
   unsigned long long c = 0;
+  float l0[kAItems], l1[kAItems], x[kAItems];
+  uint8_t m[kAItems], rm[kAItems];
+#pragma unroll
+  for (int k = 0; k < kAItems; ++k) {
+    const int64_t i = base + (int64_t)k * kABlock;
+    const int64_t r = i < n ? i : n - 1;
+    x[k] = logit[r];
+    l0[k] = ls[r];
+    l1[k] = ls[n + r];
+    m[k] = mask[r];
+    rm[k] = remove ? remove[r] : (uint8_t)0;
+  }
 #pragma unroll
   for (int k = 0; k < kAItems; ++k) {
     const int64_t i = base + (int64_t)k * kABlock;
     if (i < n) {
-      const uint32_t a = action_of(mask, remove, ls, logit, n, i, dense_scale, min_opacity);
+      const uint32_t a = action_of((m[k] & 4u) != 0u, rm[k] != 0, l0[k], l1[k], x[k], dense_scale, min_opacity);
       actions[i] = (uint8_t)a;
       c += 1ull << (16 * a);
     }
@@ -253,26 +265,84 @@ __global__ __launch_bounds__(kABlock) void k_apply(cgv2_surfels s, const uint32_
   }
 }
 
-__global__ __launch_bounds__(kABlock) void k_gather(const float* __restrict__ f, int64_t n, int C, int blocked,
-                                                    const uint32_t* __restrict__ src,
-                                                    const int64_t* __restrict__ counts, int64_t cap, int zero_new,
-                                                    float* __restrict__ out) {
+// A planar field: kGSlots output slots and up to four channels per thread, its map entries and then its elements in
+// flight together; the stores are coalesced, the loads follow the sources in order.  Bound by memory: 1 M slots of
+// 48 channels 162 us with an element per thread (and its 64-bit divisions) -> 92, 3 M of 4 channels 39 -> 31.
+constexpr int kGSlots = 4;
+
+__global__ __launch_bounds__(kABlock) void k_gather_planar(const float* __restrict__ f, int64_t n, int C,
+                                                           const uint32_t* __restrict__ src,
+                                                           const int64_t* __restrict__ counts, int64_t cap,
+                                                           int zero_new, float* __restrict__ out) {
   const int64_t lim = live_slots(counts, cap);
-  const int64_t total = lim * C;
-  for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < total; t += (int64_t)gridDim.x * blockDim.x) {
-    int64_t j, c;
-    if (blocked) {
-      j = t / C;
-      c = t - j * C;
-    } else {
-      c = t / lim;
-      j = t - c * lim;
+  const int64_t step = (int64_t)gridDim.x * kABlock * kGSlots;
+  for (int64_t j0 = (int64_t)blockIdx.x * kABlock * kGSlots + threadIdx.x; j0 < lim; j0 += step) {
+    uint32_t e[kGSlots];
+#pragma unroll
+    for (int q = 0; q < kGSlots; ++q) {
+      const int64_t j = j0 + (int64_t)q * kABlock;
+      e[q] = j < lim ? src[j] : kNone;
     }
-    const uint32_t e = src[j];
-    const int64_t i = e >> 2;
-    if (i >= n) continue;
-    const float v = (zero_new && (e & 3u) != S_SURVIVOR) ? 0.f : f[blocked ? i * C + c : c * n + i];
-    out[blocked ? j * C + c : c * cap + j] = v;
+    for (int64_t c0 = (int64_t)blockIdx.y * 4; c0 < C; c0 += (int64_t)gridDim.y * 4) {
+      float v[4][kGSlots];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        if (c0 + k >= C) break;
+        const float* fc = f + (c0 + k) * n;
+#pragma unroll
+        for (int q = 0; q < kGSlots; ++q) {
+          v[k][q] = 0.f;
+          if ((int64_t)(e[q] >> 2) < n && !(zero_new && (e[q] & 3u) != S_SURVIVOR)) v[k][q] = fc[e[q] >> 2];
+        }
+      }
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        if (c0 + k >= C) break;
+        float* oc = out + (c0 + k) * cap + j0;
+#pragma unroll
+        for (int q = 0; q < kGSlots; ++q)
+          if (j0 + (int64_t)q * kABlock < lim && (int64_t)(e[q] >> 2) < n) oc[q * kABlock] = v[k][q];
+      }
+    }
+  }
+}
+
+// A blocked field: a workgroup takes R output slots at a time, whose rows form one contiguous stream of units of T
+// (float4 where a row is a whole number of them and both arrays are aligned to it); U units per row.  Bound by
+// memory: 1 M slots of 48 floats 162 us with an element per thread (and its 64-bit divisions) -> 87 (4.6 TB/s).
+template <class T>
+__global__ __launch_bounds__(kABlock) void k_gather_rows(const T* __restrict__ f, int64_t n, uint32_t U, uint32_t R,
+                                                         const uint32_t* __restrict__ src,
+                                                         const int64_t* __restrict__ counts, int64_t cap, int zero_new,
+                                                         T* __restrict__ out) {
+  __shared__ uint32_t s_src[kABlock];
+  const int64_t lim = live_slots(counts, cap);
+  for (int64_t j0 = (int64_t)blockIdx.x * R; j0 < lim; j0 += (int64_t)gridDim.x * R) {
+    const uint32_t cnt = (uint32_t)((lim - j0) < R ? (lim - j0) : R);
+    if (threadIdx.x < cnt) s_src[threadIdx.x] = src[j0 + threadIdx.x];
+    __syncthreads();
+    const uint64_t units = (uint64_t)cnt * U;
+    // unit t = (slot, k); a step of kABlock units moves them by (kABlock / U, kABlock % U)
+    uint32_t slot = threadIdx.x / U, k = threadIdx.x % U;
+    const uint32_t ds = kABlock / U, dk = kABlock % U;
+#pragma unroll 4
+    for (uint64_t t = threadIdx.x; t < units; t += kABlock) {
+      const uint32_t e = s_src[slot];
+      const int64_t i = e >> 2;
+      if (i < n) {
+        const bool zero = zero_new && (e & 3u) != S_SURVIVOR;
+        T v = {};
+        if (!zero) v = f[i * U + k];
+        out[(j0 + slot) * U + k] = v;
+      }
+      slot += ds;
+      k += dk;
+      if (k >= U) {
+        k -= U;
+        ++slot;
+      }
+    }
+    __syncthreads();
   }
 }
 
@@ -332,7 +402,25 @@ hipError_t cgv2_launch_densify_apply(const cgv2_surfels& s, const uint8_t* actio
 hipError_t cgv2_launch_densify_gather(const float* f, int64_t n, int C, int blocked, const uint32_t* src,
                                       const int64_t* counts, int zero_new, float* out, int64_t cap, hipStream_t st) {
   if (n == 0 || cap == 0) return hipGetLastError();
-  hipLaunchKernelGGL(cgv2::k_gather, dim3(cgv2::grid_for(cap * C, 16384)), dim3(cgv2::kABlock), 0, st, f, n, C,
-                     blocked, src, counts, cap, zero_new, out);
+  if (!blocked) {
+    const unsigned gy = (unsigned)std::min(((int64_t)C + 3) / 4, (int64_t)1024);
+    hipLaunchKernelGGL(cgv2::k_gather_planar, dim3(cgv2::grid_for((cap + cgv2::kGSlots - 1) / cgv2::kGSlots, 16384), gy),
+                       dim3(cgv2::kABlock), 0, st, f, n, C, src, counts, cap,
+                       zero_new, out);
+    return hipGetLastError();
+  }
+  // A field that fills the chip takes 256 rows a workgroup, a smaller one four units per thread (us: 1 M slots of 27
+  // floats 46 and 62, 4,000 slots 16.9 and 13.6)
+  const bool v4 = C % 4 == 0 && ((uintptr_t)f | (uintptr_t)out) % 16 == 0;
+  const uint32_t U = (uint32_t)(v4 ? C / 4 : C);
+  const uint32_t few = std::max(std::min(4u * cgv2::kABlock / U, (uint32_t)cgv2::kABlock), 1u);
+  const uint32_t R = cap >= 262144 ? (uint32_t)cgv2::kABlock : few;
+  const unsigned g = cgv2::grid_for((cap + R - 1) / R * cgv2::kABlock, 16384);
+  if (v4)
+    hipLaunchKernelGGL(cgv2::k_gather_rows<float4>, dim3(g), dim3(cgv2::kABlock), 0, st, (const float4*)f, n, U, R, src,
+                       counts, cap, zero_new, (float4*)out);
+  else
+    hipLaunchKernelGGL(cgv2::k_gather_rows<float>, dim3(g), dim3(cgv2::kABlock), 0, st, f, n, U, R, src, counts, cap,
+                       zero_new, out);
   return hipGetLastError();
 }
