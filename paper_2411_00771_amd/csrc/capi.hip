@@ -402,7 +402,7 @@ int cgv2_visibility_count(const float* points, int64_t m, const cgv2_camera* cam
   const hipStream_t st = (hipStream_t)stream;
   for (int v0 = 0; v0 < V; v0 += cgv2::kMaxViews) {
     const int cnt = V - v0 < cgv2::kMaxViews ? V - v0 : cgv2::kMaxViews;
-    const int rc = hip_status(cgv2_launch_vis_table(pack(cams, v0, cnt), V, radius, filter_px, workspace, st));
+    const int rc = hip_status(cgv2_launch_vis_table(pack(cams, v0, cnt), V, radius, workspace, st));
     if (rc) return rc;
   }
   return hip_status(cgv2_launch_vis_count(points, m, V, radius, filter_px, count, workspace, st));

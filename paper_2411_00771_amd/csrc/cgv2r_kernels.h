@@ -67,7 +67,7 @@ hipError_t cgv2_launch_densify_gather(const float* f, int64_t n, int C, int bloc
 // visibility-frequency crop volume (crop.hip)
 constexpr int kVisMaxViews = 4096;  // views per k_vis_count launch (its LDS list of edge views)
 size_t cgv2_vis_ws_layout(int V);
-hipError_t cgv2_launch_vis_table(const cgv2::CamPack& cams, int V, double rho, double rf, void* ws, hipStream_t st);
+hipError_t cgv2_launch_vis_table(const cgv2::CamPack& cams, int V, double rho, void* ws, hipStream_t st);
 hipError_t cgv2_launch_vis_count(const float* pts, int64_t m, int V, double rho, double rf, uint32_t* count,
                                  void* ws, hipStream_t st);
 size_t cgv2_crop_ws_layout(int64_t m, size_t* off);

@@ -8,16 +8,14 @@
 // sample (i + 0.5, j + 0.5) lies in the footprint's box (a sphere reaching the camera plane, depth <=
 // rho, is visible).  Every decision is taken in FP64.
 //
-//   k_vis_table  per view: the camera in FP64 (a row) and, as columns across the views, eight
-//                world-space planes: four that bound where a footprint can reach the image, four that bound
-//                where every projected centre is inside it
-//   k_vis_count  per workgroup of kVisSuper consecutive points: the box of its points is classified
-//                against 256 views at a time, one view per thread, then each of its sub-boxes against the
-//                views left undecided.  A view that cannot see any point of
-//                the box is skipped; a view in which every centre projects inside the sample range
-//                counts for all points at once (rf >= 0.5 guarantees the nearest sample is covered); only
-//                the remaining views, whose image edge crosses the box, test the points one by one (with
-//                rf >= 0.5, the sphere's extent is computed only for centres outside the extended image).
+//   k_vis_table  per view: the camera in FP64 (a row) and, as columns across the views, its depth row, znear and
+//                the planes through the camera and the four image edges
+//   k_vis_count  per workgroup of up to 4,096 consecutive points: the box of its points is classified against 256
+//                views at a time, one view per thread; then each wave classifies the views left undecided, one
+//                per lane, against each of its boxes of 128 points.  A view that cannot see any point of a box is
+//                skipped; a view in which every centre projects inside the sample range counts for all points at
+//                once (rf >= 0.5 guarantees the nearest sample is covered); only the remaining views test the
+//                points one by one, and most of them by the sign of a single plane.
 //                Points in spatially coherent order make the boxes small; any order gives the same counts.
 //   k_crop_*     threshold, FP64 ground transform, height range, order-preserving compaction
 #include "cgv2r_device.h"
@@ -29,21 +27,19 @@
 namespace cgv2 {
 
 constexpr int kVisThreads = 256;
-constexpr int kVisPts = 2;
-constexpr int kVisChunk = kVisThreads * kVisPts;  // points per sub-box
-constexpr int kVisSub = 8;                         // sub-boxes per workgroup
-constexpr int kVisSuper = kVisChunk * kVisSub;
-// Per-view table in the workspace: an FP64 camera row per view (read with scalar loads by the per-point
-// test) and, for the workgroup classification, one column per plane coefficient across the views (one
-// view per lane: coalesced loads).
-constexpr int kRow = 36;                 // doubles per camera row: camera (20), four exact edge planes
-constexpr int kCols = 37;                // classification columns: depth row (4), znear, 8 planes x 4
+constexpr int kVisWaves = kVisThreads / 64;
+constexpr int kVisPts = 2;              // points per lane of a wave's box
+constexpr int kVisRun = 64 * kVisPts;   // points per wave box
+constexpr int kVisRuns = 8;             // most boxes per wave
+// Per-view table in the workspace: an FP64 camera row per view (read with scalar loads by the general per-point
+// test) and one column per coefficient across the views (one view per lane: coalesced loads).
+constexpr int kRow = 36;                 // doubles of room per camera row (19 used)
+constexpr int kCols = 37;                // doubles of room per view in the columns (25 used)
 constexpr double kEdgeMarginPx = 1e-2;   // the plane tests keep this far from every decision edge
 constexpr double kDepthMargin = 1e-7;
 
-enum : int { T_R = 0, T_T = 9, T_FX = 12, T_FY, T_CX, T_CY, T_ZN, T_W, T_H, T_E = 20 };
-enum : int { C_Z = 0, C_ZN = 4, C_PL = 5 };  // column index of the depth row, znear, plane q at C_PL + 4 q
-enum : int { V_OUT = 0, V_IN = 1, V_EDGE = 2 };
+enum : int { T_R = 0, T_T = 9, T_FX = 12, T_FY, T_CX, T_CY, T_ZN, T_W, T_H };  // row of the general test
+enum : int { C_Z = 0, C_ZN = 4, C_PL = 5, C_N = 21 };  // columns: depth row, znear, side q's plane at C_PL + 4 q, reach
 
 struct VisTable {
   double* row;  // [V][kRow]
@@ -51,7 +47,7 @@ struct VisTable {
   int V;
 };
 
-__global__ void k_vis_table(CamPack cams, double rho, double rf, VisTable tab) {
+__global__ void k_vis_table(CamPack cams, double rho, VisTable tab) {
   const int k = threadIdx.x;
   if (k >= cams.count) return;
   const DevCam& c = cams.c[k];
@@ -63,68 +59,76 @@ __global__ void k_vis_table(CamPack cams, double rho, double rf, VisTable tab) {
   for (int i = 0; i < 3; ++i) t[i] = T[T_T + i] = (double)c.t[i];
   const double fx = c.fx, fy = c.fy, cx = c.cx, cy = c.cy, W = c.W, H = c.H, zn = c.znear;
   T[T_FX] = fx, T[T_FY] = fy, T[T_CX] = cx, T[T_CY] = cy, T[T_ZN] = zn, T[T_W] = W, T[T_H] = H;
-  T[19] = 0.0;
   for (int i = 0; i < 3; ++i) col(C_Z + i) = R[6 + i];
   col(C_Z + 3) = t[2];
   col(C_ZN) = zn;
-  // u >= k  <=>  fx Xc + (cx - k) Zc >= 0 (Zc > 0); world plane w . p + off with w = fx R0 + (cx - k) R2
-  auto plane = [&](int q, int row, double f, double cc, double kk, double sign) {
+  // u >= k  <=>  fx Xc + (cx - k) Zc >= 0 (Zc > 0); world plane w . p + off with w = fx R0 + (cx - k) R2, and a
+  // sphere of radius rho reaches rho |(fx, cx - k)| beyond it in its own units
+  auto side = [&](int q, int row, double f, double cc, double kk, double sign) {
     for (int i = 0; i < 3; ++i) col(C_PL + 4 * q + i) = sign * (f * R[3 * row + i] + (cc - kk) * R[6 + i]);
     col(C_PL + 4 * q + 3) = sign * (f * t[row] + (cc - kk) * t[2]);
+    col(C_N + q) = rho * sqrt(f * f + (cc - kk) * (cc - kk));
   };
-  // exact edge planes of the centre's disc (row): uc + rf >= 0.5, uc - rf <= W - 0.5, likewise v
-  auto edge_plane = [&](int q, int row, double f, double cc, double kk, double sign) {
-    double* P = T + T_E + 4 * q;
-    for (int i = 0; i < 3; ++i) P[i] = sign * (f * R[3 * row + i] + (cc - kk) * R[6 + i]);
-    P[3] = sign * (f * t[row] + (cc - kk) * t[2]);
-  };
-  edge_plane(0, 0, fx, cx, 0.5 - rf, 1.0);
-  edge_plane(1, 0, fx, cx, W - 0.5 + rf, -1.0);
-  edge_plane(2, 1, fy, cy, 0.5 - rf, 1.0);
-  edge_plane(3, 1, fy, cy, H - 0.5 + rf, -1.0);
-  // reach planes: beyond them no footprint touches a sample
-  plane(0, 0, fx, cx, 0.5 - rf - kEdgeMarginPx, 1.0);
-  plane(1, 0, fx, cx, W - 0.5 + rf + kEdgeMarginPx, -1.0);
-  plane(2, 1, fy, cy, 0.5 - rf - kEdgeMarginPx, 1.0);
-  plane(3, 1, fy, cy, H - 0.5 + rf + kEdgeMarginPx, -1.0);
-  // interior planes: inside all four every projected centre lies within the sample range
-  plane(4, 0, fx, cx, 0.5 + kEdgeMarginPx, 1.0);
-  plane(5, 0, fx, cx, W - 0.5 - kEdgeMarginPx, -1.0);
-  plane(6, 1, fy, cy, 0.5 + kEdgeMarginPx, 1.0);
-  plane(7, 1, fy, cy, H - 0.5 - kEdgeMarginPx, -1.0);
+  side(0, 0, fx, cx, 0.5, 1.0);
+  side(1, 0, fx, cx, W - 0.5, -1.0);
+  side(2, 1, fy, cy, 0.5, 1.0);
+  side(3, 1, fy, cy, H - 0.5, -1.0);
 }
 
-// Class of view v for the points inside the box c +- h (world, FP64).
-__device__ __forceinline__ int classify(const double* __restrict__ col, int V, int v, const double c[3],
-                                        const double h[3], double rho, bool interior) {
-  auto at = [&](int q) { return col[(int64_t)q * V + v]; };
-  const double z0 = at(C_Z), z1 = at(C_Z + 1), z2 = at(C_Z + 2);
-  const double zc = z0 * c[0] + z1 * c[1] + z2 * c[2] + at(C_Z + 3);
-  const double zr = fabs(z0) * h[0] + fabs(z1) * h[1] + fabs(z2) * h[2];
-  const double zn = at(C_ZN);
-  if (zc + zr < zn - kDepthMargin) return V_OUT;  // every centre at or before znear
-  if (zc - zr > rho + kDepthMargin) {
-    // no sphere reaches the camera plane: the box grown by rho bounds every sphere
+// A view's coefficients: depth row, znear, the planes through the camera and the first and last sample column and
+// row (inside is positive), and the reach of the sphere beyond each.
+struct ViewPlanes {
+  double z[4], zn, p[4][4], n[4];
+};
+
+__device__ __forceinline__ void load_planes(const VisTable& tab, int v, ViewPlanes& k) {
+  auto at = [&](int q) { return tab.col[(int64_t)q * tab.V + v]; };
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const double p0 = at(C_PL + 4 * q), p1 = at(C_PL + 4 * q + 1), p2 = at(C_PL + 4 * q + 2);
-      const double s = p0 * c[0] + p1 * c[1] + p2 * c[2] + at(C_PL + 4 * q + 3) + fabs(p0) * (h[0] + rho) +
-                       fabs(p1) * (h[1] + rho) + fabs(p2) * (h[2] + rho);
-      if (s < 0.0) return V_OUT;
-    }
-  }
-  if (interior && zc - zr > zn + kDepthMargin) {
-    bool in = true;
+  for (int i = 0; i < 4; ++i) k.z[i] = at(C_Z + i);
+  k.zn = at(C_ZN);
 #pragma unroll
-    for (int q = 4; q < 8; ++q) {
-      const double p0 = at(C_PL + 4 * q), p1 = at(C_PL + 4 * q + 1), p2 = at(C_PL + 4 * q + 2);
-      const double s = p0 * c[0] + p1 * c[1] + p2 * c[2] + at(C_PL + 4 * q + 3) - fabs(p0) * h[0] -
-                       fabs(p1) * h[1] - fabs(p2) * h[2];
-      in = in && s > 0.0;
-    }
-    if (in) return V_IN;
+  for (int q = 0; q < 4; ++q) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) k.p[q][i] = at(C_PL + 4 * q + i);
+    k.n[q] = at(C_N + q);
   }
-  return V_EDGE;
+}
+
+// What a box of points c +- h (world, FP64) leaves undecided of a view: 0 every centre projects inside the sample
+// range (all visible), else a bit per image side that crosses the box and kDepthBit when its depths need a test;
+// kViewOut when no point can be visible, kDepthOnly when only those can whose sphere reaches the camera plane (the
+// boxes beside an oblique camera: half of all that are left undecided).  'wide' (rf >= 0.5): a centre in the sample range covers a sample.
+// With L the value of a side's plane at a point, no sample is covered beyond that side when L < -max(rf Z, reach).
+constexpr uint32_t kDepthBit = 16u, kAllBits = 31u, kViewOut = 32u, kDepthOnly = 64u;
+
+struct Depths {
+  double lo, hi;  // of the box in the view
+};
+
+__device__ __forceinline__ uint32_t classify(const ViewPlanes& k, const double c[3], const double h[3], double rho,
+                                             double rf, bool wide, Depths& z) {
+  const double zc = fma(k.z[0], c[0], fma(k.z[1], c[1], fma(k.z[2], c[2], k.z[3])));
+  const double zr = fma(fabs(k.z[0]), h[0], fma(fabs(k.z[1]), h[1], fabs(k.z[2]) * h[2]));
+  z.lo = zc - zr;
+  z.hi = zc + zr;
+  const bool behind = z.hi < k.zn - kDepthMargin;  // every centre at or before znear
+  const bool far = z.lo > rho + kDepthMargin;      // no sphere reaches the camera plane
+  const bool front = z.lo > k.zn + kDepthMargin;
+  const double disc = rf * z.hi, margin = kEdgeMarginPx * z.hi;
+  bool out = false;
+  uint32_t sides = 0;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const double* P = k.p[q];
+    const double s = fma(P[0], c[0], fma(P[1], c[1], fma(P[2], c[2], P[3])));
+    const double r = fma(fabs(P[0]), h[0], fma(fabs(P[1]), h[1], fabs(P[2]) * h[2]));
+    out = out || s + r < -(margin + (disc > k.n[q] ? disc : k.n[q]));
+    if (!(s - r > margin)) sides |= 1u << q;
+  }
+  if (behind || (far && out)) return kViewOut;
+  if (out) return kDepthOnly;
+  if (!wide || !front) return kAllBits;
+  return sides == 0u || far ? sides : sides | kDepthBit;
 }
 
 // The visible mask of one point in one view, as defined (FP64): any filter reach.
@@ -148,189 +152,256 @@ __device__ __forceinline__ bool vis_exact(const double* T, double x, double y, d
   return i0 <= i1 && j0 <= j1;
 }
 
-// The same mask when rf >= 0.5.  Then the footprint's extent along an axis is at least one pixel, so it
-// holds a sample exactly when it overlaps [0.5, W - 0.5]: on x, max(u1, uc + rf) >= 0.5 and
-// min(u0, uc - rf) <= W - 0.5.  With Z > 0, uc + rf >= 0.5 is the sign of a world-space plane through
-// the camera (likewise the other three), so the common case costs four plane evaluations; since
-// u0 <= uc <= u1, the sphere's bounds are computed only on a side whose plane test fails.
-__device__ __forceinline__ bool vis_exact_wide(const double* T, double x, double y, double z,
-                                               double rho) {
-  const double Z = T[6] * x + T[7] * y + T[8] * z + T[11];
-  if (!(Z > T[T_ZN])) return false;
-  if (Z <= rho) return true;
-  double e[4];
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const double* P = T + T_E + 4 * q;
-    e[q] = P[0] * x + P[1] * y + P[2] * z + P[3];
-  }
-  if (e[0] >= 0.0 && e[1] >= 0.0 && e[2] >= 0.0 && e[3] >= 0.0) return true;
-  const double iden = 1.0 / (Z * Z - rho * rho);
-  if (e[0] < 0.0 || e[1] < 0.0) {
-    const double X = T[0] * x + T[1] * y + T[2] * z + T[9];
-    const double sx = sqrt(X * X + Z * Z - rho * rho);
-    const bool ok = e[0] < 0.0 ? T[T_FX] * ((X * Z + rho * sx) * iden) + T[T_CX] >= 0.5
-                               : T[T_FX] * ((X * Z - rho * sx) * iden) + T[T_CX] <= T[T_W] - 0.5;
-    if (!ok) return false;
-  }
-  if (e[2] < 0.0 || e[3] < 0.0) {
-    const double Y = T[3] * x + T[4] * y + T[5] * z + T[10];
-    const double sy = sqrt(Y * Y + Z * Z - rho * rho);
-    return e[2] < 0.0 ? T[T_FY] * ((Y * Z + rho * sy) * iden) + T[T_CY] >= 0.5
-                      : T[T_FY] * ((Y * Z - rho * sy) * iden) + T[T_CY] <= T[T_H] - 0.5;
-  }
-  return true;
+// The same mask when rf >= 0.5, tested on the given sides only (the others hold for every point of the box).  The
+// footprint's extent along an axis is then at least one pixel, so it holds a sample exactly when it overlaps
+// [0.5, W - 0.5]: on x, max(u1, uc + rf) >= 0.5 and min(u0, uc - rf) <= W - 0.5.  Let L = fx X + (cx - 0.5) Z.
+// With Z > rho, uc + rf >= 0.5 says L >= -rf Z, and u1 >= 0.5 says that the sphere reaches the plane L = 0 through
+// the camera: L >= -rho |(fx, cx - 0.5)|.  So each side is one plane against the larger of the two reaches: no
+// root, no division.  A point at infinity stays as the comparisons of the bounds have it (a plane value of -inf
+// fails, NaN passes).
+// The view is lane l's: its coefficients are read from that lane's registers (a wave alone waits about 1,000 cycles
+// for a row of the table by scalar loads).
+__device__ __forceinline__ double lane_value(double x, int l) {
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x), l), __builtin_amdgcn_readlane(__double2loint(x), l));
 }
 
-// Box of the kVisPts points per thread at pts[base + k kVisThreads] (k < kVisPts, below m) over the
-// workgroup: c +- h in FP64.  Ends with a barrier; red is reused only after the caller's next barrier.
-__device__ __forceinline__ void block_box(const float (&p)[kVisPts][3], const bool (&ok)[kVisPts],
-                                          float (&red)[6][kVisThreads / 64], double c[3], double h[3]) {
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  float lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
+__device__ __forceinline__ void vis_exact_wide(const ViewPlanes& v, int l, uint32_t bits, const double (&p)[kVisPts][3],
+                                               double rho, double rf, uint32_t (&cnt)[kVisPts]) {
+  const double z0 = lane_value(v.z[0], l), z1 = lane_value(v.z[1], l), z2 = lane_value(v.z[2], l),
+               z3 = lane_value(v.z[3], l);
+  double Z[kVisPts], rz[kVisPts];
+  bool ok[kVisPts];
 #pragma unroll
   for (int k = 0; k < kVisPts; ++k) {
-    if (!ok[k]) continue;
-#pragma unroll
-    for (int d = 0; d < 3; ++d) {
-      lo[d] = fminf(lo[d], p[k][d]);
-      hi[d] = fmaxf(hi[d], p[k][d]);
-    }
+    Z[k] = fma(z0, p[k][0], fma(z1, p[k][1], fma(z2, p[k][2], z3)));
+    rz[k] = rf * fmin(Z[k], 1e300);
+    ok[k] = true;
   }
 #pragma unroll
-  for (int d = 0; d < 3; ++d) {
+  for (int q = 0; q < 4; ++q) {
+    if (!(bits & (1u << q))) continue;
+    const double p0 = lane_value(v.p[q][0], l), p1 = lane_value(v.p[q][1], l), p2 = lane_value(v.p[q][2], l),
+                 p3 = lane_value(v.p[q][3], l), n = lane_value(v.n[q], l);
 #pragma unroll
-    for (int s = 32; s > 0; s >>= 1) {
+    for (int k = 0; k < kVisPts; ++k) {
+        const double L = fma(p0, p[k][0], fma(p1, p[k][1], fma(p2, p[k][2], p3)));
+      ok[k] = ok[k] && !(L < -fmax(rz[k], n));
+    }
+  }
+  if (bits & kDepthBit) {
+    const double zn = lane_value(v.zn, l);
+#pragma unroll
+    for (int k = 0; k < kVisPts; ++k) ok[k] = Z[k] > zn && (ok[k] || Z[k] <= rho);
+  }
+#pragma unroll
+  for (int k = 0; k < kVisPts; ++k) cnt[k] += ok[k] ? 1u : 0u;
+}
+
+// Box lo, hi of the wave's points over all lanes.
+__device__ __forceinline__ void wave_box(float (&lo)[3], float (&hi)[3]) {
+#pragma unroll
+  for (int s = 32; s > 0; s >>= 1) {
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
       lo[d] = fminf(lo[d], __shfl_xor(lo[d], s, 64));
       hi[d] = fmaxf(hi[d], __shfl_xor(hi[d], s, 64));
     }
   }
-  if (lane == 0) {
-#pragma unroll
-    for (int d = 0; d < 3; ++d) {
-      red[d][w] = lo[d];
-      red[3 + d][w] = hi[d];
-    }
-  }
-  __syncthreads();
-#pragma unroll
-  for (int d = 0; d < 3; ++d) {
-    float a = red[d][0], b = red[3 + d][0];
-#pragma unroll
-    for (int q = 1; q < kVisThreads / 64; ++q) {
-      a = fminf(a, red[d][q]);
-      b = fmaxf(b, red[3 + d][q]);
-    }
-    c[d] = 0.5 * ((double)a + (double)b);
-    h[d] = 0.5 * ((double)b - (double)a);
-  }
 }
 
-// Classifies the views list[0 .. n) (or 0 .. n when list is null) against the box c +- h: adds the
-// inside views to *n_in and appends the edge views to out (*n_out).  Every thread must call it.
-__device__ __forceinline__ void classify_views(const VisTable& tab, int v_begin, const uint32_t* list, int n,
-                                               const double c[3], const double h[3], double rho, bool wide,
-                                               uint32_t* n_in, uint32_t* out, uint32_t* n_out) {
-  const int lane = threadIdx.x & 63;
-  for (int q0 = 0; q0 < n; q0 += kVisThreads) {
-    const int q = q0 + (int)threadIdx.x;
-    uint32_t v = 0;
-    int cls = V_OUT;
-    if (q < n) {
-      v = list ? list[q] : (uint32_t)q;
-      cls = classify(tab.col, tab.V, v_begin + (int)v, c, h, rho, wide);
-    }
-    const unsigned long long in_mask = __ballot(cls == V_IN);
-    const unsigned long long ed_mask = __ballot(cls == V_EDGE);
-    uint32_t at = 0;
-    if (lane == 0) {
-      if (in_mask) atomicAdd(n_in, (uint32_t)__popcll(in_mask));
-      if (ed_mask) at = atomicAdd(n_out, (uint32_t)__popcll(ed_mask));
-    }
-    at = __shfl(at, 0, 64);
-    if (cls == V_EDGE) out[at + __popcll(ed_mask & ((1ull << lane) - 1ull))] = v;
-  }
-}
+constexpr uint32_t kNanPoint = 0x80000000u;
 
-// One workgroup per kVisSuper consecutive points, in kVisSub sub-boxes of kVisChunk: the views are
-// classified once against the whole box; only its edge views are classified again per sub-box, and only a
-// sub-box's edge views test its points one by one.
-__global__ __launch_bounds__(kVisThreads) void k_vis_count(const float* __restrict__ pts, int64_t m, VisTable tab,
-                                                           int v_begin, int V, double rho, double rf,
-                                                           uint32_t* __restrict__ count) {
-  __shared__ float red[6][kVisThreads / 64];
-  __shared__ uint32_t edge_all[kVisMaxViews], edge_sub[kVisMaxViews];
-  __shared__ uint32_t n_all, in_all, n_sub, in_sub;
-  const bool wide = rf >= 0.5;
-  const int64_t base = (int64_t)blockIdx.x * kVisSuper + threadIdx.x;
+// Workgroup (x, y): kVisWaves * runs * kVisRun consecutive points, a slice of the views.
+// Bound by FP64 instructions and the waits between its phases (118 registers, 4 waves per SIMD).  31.4 M points in
+// octree order, 958 views: 2,820 us with boxes of 512 points per workgroup and every undecided view tested by all
+// four sides, roots and divisions where one failed -> 870 (a point is left 14 undecided views instead of 26, 5 of
+// them by depth only, 5.5 by one plane).  Boxes of 64 points 1,070 us; 2,048 or 8,192 points per workgroup 930
+// and 1,020; 5 waves per SIMD spill (1,120).
+template <bool kWide>
+__global__ __launch_bounds__(kVisThreads, 4) void k_vis_count(const float* __restrict__ pts, int64_t m, VisTable tab,
+                                                              int v_begin, int V, int slice, int runs, double rho,
+                                                              double rf, uint32_t* __restrict__ count) {
+  __shared__ float box[kVisWaves][kVisRuns][6];
+  __shared__ uint32_t s_cnt[kVisWaves][kVisRuns][kVisRun];
+  __shared__ uint16_t edge[kVisMaxViews];
+  __shared__ uint32_t n_edge, n_in;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int64_t base = (int64_t)blockIdx.x * kVisWaves * runs * kVisRun;
+  const int64_t wbase = base + (int64_t)w * runs * kVisRun;
+  const int va = (int)blockIdx.y * slice, vb = min(V, va + slice);
 
-  // whole box: every point of the workgroup, in kVisSub passes of kVisPts per thread
-  {
+  if (threadIdx.x == 0) n_edge = n_in = 0;
+  // a NaN coordinate is in no box: its point is not visible in any view (kNanPoint in its counter)
+  auto first_pass = [&](int r, const float (&x)[kVisPts][3]) {
     float lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
-    for (int k = 0; k < kVisSub * kVisPts; ++k) {
-      const int64_t i = base + (int64_t)k * kVisThreads;
-      if (i >= m) break;
+#pragma unroll
+    for (int k = 0; k < kVisPts; ++k) {
 #pragma unroll
       for (int d = 0; d < 3; ++d) {
-        const float x = pts[d * m + i];
-        lo[d] = fminf(lo[d], x);
-        hi[d] = fmaxf(hi[d], x);
+        lo[d] = fminf(lo[d], x[k][d]);
+        hi[d] = fmaxf(hi[d], x[k][d]);
+      }
+      s_cnt[w][r][k * 64 + lane] = isnan(x[k][0]) || isnan(x[k][1]) || isnan(x[k][2]) ? kNanPoint : 0u;
+    }
+    wave_box(lo, hi);
+    if (lane == 0) {
+#pragma unroll
+      for (int d = 0; d < 3; ++d) {
+        box[w][r][d] = lo[d];
+        box[w][r][3 + d] = hi[d];
       }
     }
-    float p1[kVisPts][3];
-    bool ok1[kVisPts];
+  };
+  auto load_run = [&](int r, float (&x)[kVisPts][3]) {  // past the end: the last point once more
 #pragma unroll
     for (int k = 0; k < kVisPts; ++k) {
-      ok1[k] = k < 2 && lo[0] <= hi[0];
+      const int64_t i = min(wbase + (int64_t)r * kVisRun + k * 64 + lane, m - 1);
 #pragma unroll
-      for (int d = 0; d < 3; ++d) p1[k][d] = k == 0 ? lo[d] : hi[d];
+      for (int d = 0; d < 3; ++d) x[k][d] = pts[d * m + i];
     }
-    if (threadIdx.x == 0) n_all = in_all = 0;
-    double c[3], h[3];
-    block_box(p1, ok1, red, c, h);
-    classify_views(tab, v_begin, nullptr, V, c, h, rho, wide, &in_all, edge_all, &n_all);
-    __syncthreads();
+  };
+  for (int r0 = 0; r0 < runs; r0 += 4) {  // four runs' points in flight
+    float x[4][kVisPts][3];
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      if (r0 + j < runs) load_run(r0 + j, x[j]);
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      if (r0 + j < runs) first_pass(r0 + j, x[j]);
   }
-  const uint32_t na = n_all, ia = in_all;
-
-  for (int sb = 0; sb < kVisSub; ++sb) {
-    const int64_t sbase = base + (int64_t)sb * kVisChunk;
-    if (sbase - threadIdx.x >= m) break;  // uniform: the sub-box starts past the end
-    float p[kVisPts][3];
-    bool ok[kVisPts];
+  __syncthreads();
+  double c[3], h[3];
+  auto middle = [&](const float* lo, const float* hi) {
 #pragma unroll
-    for (int k = 0; k < kVisPts; ++k) {
-      const int64_t i = sbase + (int64_t)k * kVisThreads;
-      ok[k] = i < m;
-#pragma unroll
-      for (int d = 0; d < 3; ++d) p[k][d] = ok[k] ? pts[d * m + i] : 0.f;
+    for (int d = 0; d < 3; ++d) {
+      c[d] = 0.5 * ((double)lo[d] + (double)hi[d]);
+      h[d] = 0.5 * ((double)hi[d] - (double)lo[d]);
     }
-    if (threadIdx.x == 0) n_sub = in_sub = 0;
-    double c[3], h[3];
-    block_box(p, ok, red, c, h);
-    classify_views(tab, v_begin, edge_all, (int)na, c, h, rho, wide, &in_sub, edge_sub, &n_sub);
-    __syncthreads();
-    const uint32_t ne = n_sub;
-    uint32_t cnt[kVisPts];
+  };
+  {
+    // the workgroup's box: its kVisWaves * runs <= 64 wave boxes, one per lane
+    float lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
+    if (lane < kVisWaves * runs) {
 #pragma unroll
-    for (int k = 0; k < kVisPts; ++k) cnt[k] = ia + in_sub;
-    for (uint32_t e = 0; e < ne; ++e) {
-      // the view index is uniform: its camera row is read with scalar loads
-      const double* T = tab.row + (int64_t)(v_begin + (int)__builtin_amdgcn_readfirstlane(edge_sub[e])) * kRow;
-      if (wide) {
-#pragma unroll
-        for (int k = 0; k < kVisPts; ++k)
-          cnt[k] += vis_exact_wide(T, (double)p[k][0], (double)p[k][1], (double)p[k][2], rho) ? 1u : 0u;
-      } else {
-#pragma unroll
-        for (int k = 0; k < kVisPts; ++k)
-          cnt[k] += vis_exact(T, (double)p[k][0], (double)p[k][1], (double)p[k][2], rho, rf) ? 1u : 0u;
+      for (int d = 0; d < 3; ++d) {
+        lo[d] = box[lane / runs][lane % runs][d];
+        hi[d] = box[lane / runs][lane % runs][3 + d];
       }
     }
+    wave_box(lo, hi);
+    middle(lo, hi);
+  }
+  for (int q0 = va; q0 < vb; q0 += kVisThreads) {
+    const int q = q0 + (int)threadIdx.x;
+    uint32_t bits = kViewOut;
+    if (q < vb) {
+      ViewPlanes k;
+      load_planes(tab, v_begin + q, k);
+      Depths z;
+      bits = classify(k, c, h, rho, rf, kWide, z);
+    }
+    const unsigned long long in_mask = __ballot(bits == 0u);
+    const unsigned long long ed_mask = __ballot(bits != 0u && bits != kViewOut);
+    uint32_t at = 0;
+    if (lane == 0) {
+      if (in_mask) atomicAdd(&n_in, (uint32_t)__popcll(in_mask));
+      if (ed_mask) at = atomicAdd(&n_edge, (uint32_t)__popcll(ed_mask));
+    }
+    at = __shfl(at, 0, 64);
+    if (bits != 0u && bits != kViewOut) edge[at + __popcll(ed_mask & ((1ull << lane) - 1ull))] = (uint16_t)q;
+  }
+  __syncthreads();
+
+  const int na = (int)n_edge;
+  for (int e0 = 0; e0 < na; e0 += 64) {
+    // a lane keeps one edge view's planes for all runs of its wave
+    const int v = v_begin + (e0 + lane < na ? (int)edge[e0 + lane] : (int)edge[e0]);
+    ViewPlanes kp;
+    load_planes(tab, v, kp);
+    float x[kVisPts][3];
+    load_run(0, x);
+    for (int r = 0; r < runs; ++r) {
+      if (wbase + (int64_t)r * kVisRun >= m) break;
+      double p[kVisPts][3];
 #pragma unroll
-    for (int k = 0; k < kVisPts; ++k)
-      if (ok[k]) count[sbase + (int64_t)k * kVisThreads] += cnt[k];
-    __syncthreads();  // edge_sub, the counters and red are rewritten by the next sub-box
+      for (int k = 0; k < kVisPts; ++k)
+#pragma unroll
+        for (int d = 0; d < 3; ++d) p[k][d] = x[k][d];
+      if (r + 1 < runs) load_run(r + 1, x);  // in flight during this run's tests
+      middle(&box[w][r][0], &box[w][r][3]);
+      Depths z;
+      uint32_t bits = classify(kp, c, h, rho, rf, kWide, z);
+      if (e0 + lane >= na) bits = kViewOut;
+      uint32_t cnt[kVisPts];
+#pragma unroll
+      for (int k = 0; k < kVisPts; ++k) cnt[k] = (uint32_t)__popcll(__ballot(bits == 0u));
+      if constexpr (kWide) {
+        // Most views have one side crossing the box and one of the two reaches the larger over all of it: their
+        // test is the sign of one plane.
+        double a[4], n = kp.n[0];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) a[i] = kp.p[0][i];
+#pragma unroll
+        for (int q = 1; q < 4; ++q) {
+          const bool is = bits == (1u << q);
+#pragma unroll
+          for (int i = 0; i < 4; ++i) a[i] = is ? kp.p[q][i] : a[i];
+          n = is ? kp.n[q] : n;
+        }
+        const bool sphere = rf * z.hi < n * (1.0 - 1e-9), disc = rf < 1e300 && rf * z.lo > n * (1.0 + 1e-9);
+        const bool one = (bits == 1u || bits == 2u || bits == 4u || bits == 8u) && (sphere || disc);
+        a[3] = sphere ? a[3] + n : fma(rf, kp.z[3], a[3]);
+#pragma unroll
+        for (int i = 0; i < 3; ++i) a[i] = sphere ? a[i] : fma(rf, kp.z[i], a[i]);
+        for (unsigned long long ed = __ballot(one); ed; ed &= ed - 1) {
+          const int l = __builtin_ctzll(ed);
+          const double a0 = lane_value(a[0], l), a1 = lane_value(a[1], l), a2 = lane_value(a[2], l),
+                       a3 = lane_value(a[3], l);
+#pragma unroll
+          for (int k = 0; k < kVisPts; ++k)
+            cnt[k] += fma(a0, p[k][0], fma(a1, p[k][1], fma(a2, p[k][2], a3))) >= 0.0 ? 1u : 0u;
+        }
+        for (unsigned long long ed = __ballot(bits == kDepthOnly); ed; ed &= ed - 1) {
+          const int l = __builtin_ctzll(ed);
+          const double z0 = lane_value(kp.z[0], l), z1 = lane_value(kp.z[1], l), z2 = lane_value(kp.z[2], l),
+                       z3 = lane_value(kp.z[3], l), zn = lane_value(kp.zn, l);
+#pragma unroll
+          for (int k = 0; k < kVisPts; ++k) {
+            const double Z = fma(z0, p[k][0], fma(z1, p[k][1], fma(z2, p[k][2], z3)));
+            cnt[k] += Z > zn && Z <= rho ? 1u : 0u;
+          }
+        }
+        for (unsigned long long ed = __ballot(bits != 0u && bits < kViewOut && !one); ed; ed &= ed - 1) {
+          const int l = __builtin_ctzll(ed);
+          vis_exact_wide(kp, l, __builtin_amdgcn_readlane(bits, l), p, rho, rf, cnt);
+        }
+      } else {
+        for (unsigned long long ed = __ballot(bits != kViewOut); ed; ed &= ed - 1) {
+          // the view is uniform: its camera row is read with scalar loads
+          const double* T = tab.row + (int64_t)__builtin_amdgcn_readlane(v, __builtin_ctzll(ed)) * kRow;
+#pragma unroll
+          for (int k = 0; k < kVisPts; ++k) cnt[k] += vis_exact(T, p[k][0], p[k][1], p[k][2], rho, rf) ? 1u : 0u;
+        }
+      }
+#pragma unroll
+      for (int k = 0; k < kVisPts; ++k) s_cnt[w][r][k * 64 + lane] += cnt[k];
+    }
+  }
+  const uint32_t ia = n_in;
+#pragma unroll 4
+  for (int r = 0; r < runs; ++r) {
+#pragma unroll
+    for (int k = 0; k < kVisPts; ++k) {
+      const int64_t i = wbase + (int64_t)r * kVisRun + k * 64 + lane;
+      if (i >= m) continue;
+      const uint32_t own = s_cnt[w][r][k * 64 + lane];
+      const uint32_t t = own & kNanPoint ? 0u : ia + own;
+      if (gridDim.y > 1) {
+        if (t) atomicAdd(&count[i], t);
+      } else {
+        count[i] += t;
+      }
+    }
   }
 }
 
@@ -486,19 +557,34 @@ static cgv2::VisTable vis_table(void* ws, int V) {
   return t;
 }
 
-hipError_t cgv2_launch_vis_table(const cgv2::CamPack& cams, int V, double rho, double rf, void* ws, hipStream_t st) {
-  hipLaunchKernelGGL(cgv2::k_vis_table, dim3(1), dim3(64), 0, st, cams, rho, rf, vis_table(ws, V));
+hipError_t cgv2_launch_vis_table(const cgv2::CamPack& cams, int V, double rho, void* ws, hipStream_t st) {
+  hipLaunchKernelGGL(cgv2::k_vis_table, dim3(1), dim3(64), 0, st, cams, rho, vis_table(ws, V));
   return hipGetLastError();
 }
+
+// Workgroups that fill the chip twice: fewer points per workgroup, then slices of the views (their counts are added
+// atomically) until there are that many (us: 20,000 points, 958 views 5,930 -> 127; 200,000 points, 60 views 243 -> 42).
+constexpr int64_t kVisGroups = 2048;
 
 hipError_t cgv2_launch_vis_count(const float* pts, int64_t m, int V, double rho, double rf, uint32_t* count,
                                  void* ws, hipStream_t st) {
   if (m == 0) return hipGetLastError();
-  const unsigned nb = (unsigned)((m + cgv2::kVisSuper - 1) / cgv2::kVisSuper);
   for (int v0 = 0; v0 < V; v0 += kVisMaxViews) {
     const int vc = std::min(V - v0, kVisMaxViews);
-    hipLaunchKernelGGL(cgv2::k_vis_count, dim3(nb), dim3(cgv2::kVisThreads), 0, st, pts, m, vis_table(ws, V), v0, vc,
-                       rho, rf, count);
+    const int64_t boxes = (m + cgv2::kVisWaves * cgv2::kVisRun - 1) / (cgv2::kVisWaves * cgv2::kVisRun);
+    const int runs = (int)std::max<int64_t>(1, std::min<int64_t>(boxes / kVisGroups, cgv2::kVisRuns));
+    const int64_t gx = (boxes + runs - 1) / runs;
+    const int64_t gy = std::max<int64_t>(1, std::min<int64_t>(kVisGroups / gx, (vc + 63) / 64));
+    const int slice = (int)(((vc + gy - 1) / gy + 63) / 64 * 64);
+    const dim3 grid((unsigned)gx, (unsigned)((vc + slice - 1) / slice));
+    auto go = [&](auto kernel) {
+      hipLaunchKernelGGL(kernel, grid, dim3(cgv2::kVisThreads), 0, st, pts, m, vis_table(ws, V), v0, vc, slice, runs, rho,
+                         rf, count);
+    };
+    if (rf >= 0.5)
+      go(cgv2::k_vis_count<true>);
+    else
+      go(cgv2::k_vis_count<false>);
   }
   return hipGetLastError();
 }
