@@ -472,25 +472,41 @@ __global__ __launch_bounds__(kCropBlock) void k_crop_count(const float* __restri
   }
 }
 
+constexpr int kScanBlock = 1024;
+constexpr int kScanItems = 8;
+
+// Latency bound: 8,192 partials a round (15,332 of them: 59 us in rounds of 256 -> 22).
 // one workgroup: exclusive offsets of the kept points per workgroup, the kept total, the height range
-__global__ __launch_bounds__(kCropBlock) void k_crop_scan(uint32_t* __restrict__ kpart, const double* __restrict__ hpart,
+__global__ __launch_bounds__(kScanBlock) void k_crop_scan(uint32_t* __restrict__ kpart, const double* __restrict__ hpart,
                                                           int nb, int64_t* __restrict__ kept,
                                                           double* __restrict__ hrange) {
-  __shared__ unsigned long long lds[kCropBlock / 64];
-  __shared__ double hred[2][kCropBlock / 64];
+  __shared__ unsigned long long lds[kScanBlock / 64];
+  __shared__ double hred[2][kScanBlock / 64];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   unsigned long long carry = 0;
   double hmin = INFINITY, hmax = -INFINITY;
-  for (int b0 = 0; b0 < nb; b0 += kCropBlock) {
-    const int b = b0 + (int)threadIdx.x;
-    const unsigned long long v = b < nb ? kpart[b] : 0ull;
-    if (b < nb) {
-      hmin = fmin(hmin, hpart[2 * b]);
-      hmax = fmax(hmax, hpart[2 * b + 1]);
+  for (int b0 = 0; b0 < nb; b0 += kScanBlock * kScanItems) {
+    const int b = b0 + (int)threadIdx.x * kScanItems;
+    uint32_t v[kScanItems];
+    unsigned long long own = 0;
+#pragma unroll
+    for (int k = 0; k < kScanItems; ++k) {
+      v[k] = b + k < nb ? kpart[b + k] : 0u;
+      own += v[k];
+      // (the heights in any order: coalesced)
+      const int c = b0 + k * kScanBlock + (int)threadIdx.x;
+      if (c < nb) {
+        hmin = fmin(hmin, hpart[2 * (int64_t)c]);
+        hmax = fmax(hmax, hpart[2 * (int64_t)c + 1]);
+      }
     }
     unsigned long long tot;
-    const unsigned long long ex = block_exscan<kCropBlock>(v, lds, tot) + carry;
-    if (b < nb) kpart[b] = (uint32_t)ex;
+    unsigned long long ex = block_exscan<kScanBlock>(own, lds, tot) + carry;
+#pragma unroll
+    for (int k = 0; k < kScanItems; ++k) {
+      if (b + k < nb) kpart[b + k] = (uint32_t)ex;
+      ex += v[k];
+    }
     carry += tot;
   }
 #pragma unroll
@@ -505,7 +521,7 @@ __global__ __launch_bounds__(kCropBlock) void k_crop_scan(uint32_t* __restrict__
   __syncthreads();
   if (threadIdx.x == 0) {
     double a = hred[0][0], b = hred[1][0];
-    for (int q = 1; q < kCropBlock / 64; ++q) {
+    for (int q = 1; q < kScanBlock / 64; ++q) {
       a = fmin(a, hred[0][q]);
       b = fmax(b, hred[1][q]);
     }
@@ -516,30 +532,43 @@ __global__ __launch_bounds__(kCropBlock) void k_crop_scan(uint32_t* __restrict__
 }
 
 // per workgroup: ground coordinates of its kept points at their slots (id order)
+// Bound by memory: consecutive lanes take consecutive points, so loads and stores are coalesced (31.4 M points, 95 %
+// kept: 669 us with eight consecutive points per thread -> 146, 5.9 TB/s).
 __global__ __launch_bounds__(kCropBlock) void k_crop_write(const float* __restrict__ pts, int64_t m,
                                                            const uint8_t* __restrict__ keep, Ground g,
                                                            const uint32_t* __restrict__ koff,
                                                            double* __restrict__ ground) {
-  __shared__ uint32_t lds[kCropBlock / 64];
-  const int64_t chunk = (int64_t)blockIdx.x * kCropChunk;
-  const int64_t base = chunk + (int64_t)threadIdx.x * kCropItems;
-  uint32_t kp[kCropItems];
-  uint32_t k_local = 0;
+  constexpr int kW = kCropBlock / 64;
+  __shared__ uint32_t s_kept[kCropItems][kW];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int64_t base = (int64_t)blockIdx.x * kCropChunk + threadIdx.x;
+  uint8_t kp[kCropItems];
+  uint32_t rank[kCropItems];  // among the kept points of the wave's 64
 #pragma unroll
   for (int k = 0; k < kCropItems; ++k) {
-    kp[k] = base + k < m ? keep[base + k] : 0u;
-    k_local += kp[k];
+    const int64_t i = base + (int64_t)k * kCropBlock;
+    kp[k] = i < m ? keep[i] : (uint8_t)0;
   }
-  uint32_t tot;
-  uint32_t at = koff[blockIdx.x] + block_exscan<kCropBlock>(k_local, lds, tot);
 #pragma unroll
   for (int k = 0; k < kCropItems; ++k) {
-    if (!kp[k]) continue;
-    double gx, gy, gh;
-    ground_of(g, pts, m, base + k, gx, gy, gh);
-    ground[at] = gx;
-    ground[m + at] = gy;
-    ++at;
+    const unsigned long long kept = __ballot(kp[k] != 0);
+    rank[k] = (uint32_t)__popcll(kept & ((1ull << lane) - 1ull));
+    if (lane == 0) s_kept[k][w] = (uint32_t)__popcll(kept);
+  }
+  __syncthreads();
+  uint32_t at = koff[blockIdx.x];
+#pragma unroll
+  for (int k = 0; k < kCropItems; ++k) {
+#pragma unroll
+    for (int q = 0; q < kW; ++q) {
+      if (q == w && kp[k]) {
+        double gx, gy, gh;
+        ground_of(g, pts, m, base + (int64_t)k * kCropBlock, gx, gy, gh);
+        ground[at + rank[k]] = gx;
+        ground[m + at + rank[k]] = gy;
+      }
+      at += s_kept[k][q];
+    }
   }
 }
 
@@ -613,7 +642,7 @@ hipError_t cgv2_launch_crop(const float* pts, int64_t m, const uint32_t* count, 
     hipLaunchKernelGGL((cgv2::k_fill<uint32_t>), dim3(1), dim3(64), 0, st, kpart, (int64_t)1, 0u);
     hipLaunchKernelGGL((cgv2::k_fill<double>), dim3(1), dim3(64), 0, st, hpart, (int64_t)2, 0.0);
   }
-  hipLaunchKernelGGL(cgv2::k_crop_scan, dim3(1), dim3(cgv2::kCropBlock), 0, st, kpart, hpart, nb, kept, hrange);
+  hipLaunchKernelGGL(cgv2::k_crop_scan, dim3(1), dim3(cgv2::kScanBlock), 0, st, kpart, hpart, nb, kept, hrange);
   if (m > 0)
     hipLaunchKernelGGL(cgv2::k_crop_write, dim3((unsigned)nb), dim3(cgv2::kCropBlock), 0, st, pts, m, keep, g, kpart,
                        ground);

@@ -57,3 +57,24 @@ def test_points_without_a_position(cuda, rf):
     Q[0, np.flatnonzero(bad)[::3]] = np.inf  # a point at infinity leaves its box's other points as they are
     got = _counts(Q, cams, 0.4, rf)
     assert np.array_equal(got[~bad][frag == 0], ref[frag == 0])
+
+
+@pytest.mark.parametrize("m", [1, 63, 255, 257, 2047, 2049, 70_001])
+@pytest.mark.parametrize("share", [0.0, 0.3, 1.0])
+def test_crop_volume_keeps_the_order(cuda, m, share):
+    import torch
+    from paper_2411_00771_amd import crop
+    rng = np.random.default_rng(m)
+    P = rng.uniform(-50, 50, (3, m)).astype(np.float32)
+    cnt = (rng.random(m) < share) * 3
+    T = np.array([[0.6, -0.8, 0, 5.0], [0.8, 0.6, 0, -2.0], [0, 0, 1.0, -10.0]])
+    keep, ground, (h0, h1) = crop.crop_volume(torch.from_numpy(P).cuda(),
+                                              torch.from_numpy(cnt.astype(np.int32)).cuda(), 2, T)
+    rk, rg, rh0, rh1 = ovis.crop_volume(P, cnt, 2, T)
+    assert np.array_equal(keep.cpu().numpy().astype(bool), rk)
+    # sums of four products of at most 50 in FP64, in another order
+    assert ground.shape == rg.shape and np.allclose(ground.cpu().numpy(), rg, rtol=0, atol=8 * 50 * 2.0 ** -52)
+    if rk.any():
+        assert abs(h0 - rh0) <= 8 * 50 * 2.0 ** -52 and abs(h1 - rh1) <= 8 * 50 * 2.0 ** -52
+    else:
+        assert np.isnan(h0) and np.isnan(h1)
