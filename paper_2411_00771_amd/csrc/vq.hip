@@ -5,7 +5,7 @@
 //   k_part_*      stable partition by the quantize mask: kept surfels first, both groups in id order
 //   k_vq_init     codeword j = row floor(j m / K) of the quantized vectors
 //   k_vq_assign   nearest codeword: |c|^2 - 2 x.c on the matrix cores (FP32 MFMA 16x16x4), the argmin
-//                 fused into the epilogue; codewords stream through LDS in chunks, transposed
+//                 fused into the epilogue; codewords stream through LDS in chunks
 //   k_vq_accum / k_vq_final   Lloyd update: FP64 sums per codeword, mean, empty codewords kept
 //   k_compact_*   the stored arrays in partition order (float16 by round-to-nearest-even)
 #include "cgv2r_device.h"
@@ -98,7 +98,7 @@ __global__ __launch_bounds__(256) void k_vq_init(const float* __restrict__ x, in
 }
 
 // Nearest codeword for kVqRows query vectors per workgroup (kVqRowsWave per wave: two 16-row MFMA
-// tiles), against codewords staged kVqCols at a time in LDS as cwT[dim][col] (conflict-free B reads).
+// tiles), against codewords staged kVqCols at a time in LDS.
 // MFMA 16x16x4 f32 operand layout (wave64): A[i][k] in lane i + 16 k, B[k][j] in lane j + 16 k, and
 // D[4 (lane / 16) + r][lane % 16] in accumulator element r.
 constexpr int kVqThreads = 256;
@@ -120,17 +120,35 @@ __global__ __launch_bounds__(256) void k_vq_norms(const float* __restrict__ cb, 
   norms[j] = s2;
 }
 
+// The codewords lie in LDS as the lanes read them (a lane's values of all steps together, wide reads), in two buffers:
+// the next chunk's loads, one contiguous stream of the codebook, are in flight while this one is multiplied.
+// The first 'full' workgroups take kVqRows queries each.  The rest take kVqRowsWave each: their waves multiply the
+// same queries with a quarter of the column tiles each.
+// Bound by the FP32 matrix rate and the argmin's vector instructions beside it (matrix cores busy 1.2 ms of 1.8 at
+// 400 k queries, 8,192 codewords of 27 dimensions): 2,130 us with strided codebook loads, a transposed single buffer
+// (four-way bank conflicts) and accumulators copied out of the accumulation registers -> 1,785; 48 dimensions 3,970
+// -> 2,765; 2 M queries 9,300 -> 8,240.  The column tiles unrolled by 8 spill (3,660); wave priorities give nothing.
 template <int DP>  // dimensions padded to a multiple of 4
-__global__ __launch_bounds__(kVqThreads) void k_vq_assign(const float* __restrict__ x, int D,
-                                                          const uint32_t* __restrict__ rows, int64_t m,
-                                                          const float* __restrict__ cb, const float* __restrict__ norms,
-                                                          int K, int half_cb, uint16_t* __restrict__ code) {
+__global__ __launch_bounds__(kVqThreads, DP > 28 ? 3 : 4) void k_vq_assign(
+    const float* __restrict__ x, int D, const uint32_t* __restrict__ rows, int64_t m, const float* __restrict__ cb,
+    const float* __restrict__ norms, int K, int half_cb, uint16_t* __restrict__ code, unsigned full) {
   constexpr int kSteps = DP / 4;
-  __shared__ float cwT[DP][kVqCols];
-  __shared__ float norm[kVqCols];
+  constexpr int kPad = kSteps == 1 ? 1 : (kSteps + 3) / 4 * 4;  // floats per lane and column tile
+  constexpr int kTiles = kVqCols / 16;
+  constexpr int kWaves = kVqThreads / 64;
+  constexpr int kLoads = (kVqCols * DP + kVqThreads - 1) / kVqThreads;
+  constexpr int kSure = kVqCols * (DP - 3) / kVqThreads;  // loads that every thread has for every D
+  const int count = kVqCols * D;
+  __shared__ __align__(16) float frag[2][kTiles][64][kPad];
+  __shared__ float norm[2][kVqCols];
+  __shared__ float s_best[kWaves][kVqRowsWave];
+  __shared__ int s_idx[kWaves][kVqRowsWave];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int li = lane & 15, lk = lane >> 4;
-  const int64_t row0 = (int64_t)blockIdx.x * kVqRows + (int64_t)w * kVqRowsWave;
+  const bool split = blockIdx.x >= full;
+  const int64_t row0 = split ? (int64_t)full * kVqRows + (int64_t)(blockIdx.x - full) * kVqRowsWave
+                             : (int64_t)blockIdx.x * kVqRows + (int64_t)w * kVqRowsWave;
+  const int ct_begin = split ? w * (kTiles / kWaves) : 0, ct_end = split ? ct_begin + kTiles / kWaves : kTiles;
   // A operands: query (row0 + 16 t + li), dimension 4 s + lk
   float a[2][kSteps];
 #pragma unroll
@@ -152,36 +170,69 @@ __global__ __launch_bounds__(kVqThreads) void k_vq_assign(const float* __restric
       best[t][r] = INFINITY;
       bidx[t][r] = 0x7fffffff;
     }
-  for (int c0 = 0; c0 < K; c0 += kVqCols) {
-    __syncthreads();  // the previous chunk is no longer read
-    // thread (j, group of 4 dimensions): consecutive threads fill consecutive columns of a row of cwT
-    for (int e = threadIdx.x; e < kVqCols * kSteps; e += kVqThreads) {
-      const int j = e % kVqCols, d4 = e / kVqCols;
-      const bool live = c0 + j < K;
-      const float* src = cb + (int64_t)(c0 + j) * D + 4 * d4;
+  // the dimensions past D stay zero
+  if (D < DP)
+    for (int e = threadIdx.x; e < 2 * kTiles * 64 * kPad; e += kVqThreads) (&frag[0][0][0][0])[e] = 0.f;
+  // value e = thread + 256 k of a chunk: codeword e / D of it, dimension e % D
+  float v[kLoads], nv = INFINITY;
+  int at[kLoads];
+  int j = (int)threadIdx.x / D, d = (int)threadIdx.x - j * D;
+  const int dj = kVqThreads / D, dd = kVqThreads - dj * D;
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        float v = 0.f;
-        if (live && 4 * d4 + q < D) {
-          v = src[q];
-          if (half_cb) v = (float)(_Float16)v;
-        }
-        cwT[4 * d4 + q][j] = v;
-      }
+  for (int k = 0; k < kLoads; ++k) {  // (past the chunk: not stored)
+    at[k] = ((j >> 4) * 64 + (j & 15) + 16 * (d & 3)) * kPad + (d >> 2);
+    j += dj;
+    d += dd;
+    if (d >= D) {
+      d -= D;
+      ++j;
     }
-    if (threadIdx.x < kVqCols) norm[threadIdx.x] = c0 + (int)threadIdx.x < K ? norms[c0 + threadIdx.x] : INFINITY;
-    __syncthreads();
+  }
+  auto mine = [&](int k) { return k < kSure || (int)threadIdx.x + k * kVqThreads < count; };
+  auto load = [&](int c0) {
+    const float* src = cb + (int64_t)c0 * D + threadIdx.x;
+    if (c0 + kVqCols <= K) {
 #pragma unroll
-    for (int ct = 0; ct < kVqCols / 16; ++ct) {
+      for (int k = 0; k < kLoads; ++k)
+        if (mine(k)) v[k] = src[k * kVqThreads];
+      if (threadIdx.x < kVqCols) nv = norms[c0 + threadIdx.x];
+    } else {
+      const int live = (K - c0) * D - (int)threadIdx.x;
+#pragma unroll
+      for (int k = 0; k < kLoads; ++k) v[k] = mine(k) && k * kVqThreads < live ? src[k * kVqThreads] : 0.f;
+      if (threadIdx.x < kVqCols) nv = c0 + (int)threadIdx.x < K ? norms[c0 + threadIdx.x] : INFINITY;
+    }
+  };
+  auto put = [&](int buf) {
+    float* to = &frag[buf][0][0][0];
+    if (half_cb) {
+#pragma unroll
+      for (int k = 0; k < kLoads; ++k) v[k] = (float)(_Float16)v[k];
+    }
+#pragma unroll
+    for (int k = 0; k < kLoads; ++k)
+      if (mine(k)) to[at[k]] = v[k];
+    if (threadIdx.x < kVqCols) norm[buf][threadIdx.x] = nv;
+  };
+  load(0);
+  __syncthreads();  // the zeros are written
+  put(0);
+  __syncthreads();
+  for (int c0 = 0, buf = 0; c0 < K; c0 += kVqCols, buf ^= 1) {
+    const bool more = c0 + kVqCols < K;
+    if (more) load(c0 + kVqCols);
+    for (int ct = ct_begin; ct < ct_end; ++ct) {
       floatx4 acc0 = {0.f, 0.f, 0.f, 0.f}, acc1 = {0.f, 0.f, 0.f, 0.f};
+      float b[kPad];
+#pragma unroll
+      for (int s = 0; s < kPad; ++s) b[s] = frag[buf][ct][lane][s];
 #pragma unroll
       for (int s = 0; s < kSteps; ++s) {
-        const float b = cwT[4 * s + lk][16 * ct + li];
-        acc0 = __builtin_amdgcn_mfma_f32_16x16x4f32(a[0][s], b, acc0, 0, 0, 0);
-        acc1 = __builtin_amdgcn_mfma_f32_16x16x4f32(a[1][s], b, acc1, 0, 0, 0);
+        acc0 = __builtin_amdgcn_mfma_f32_16x16x4f32(a[0][s], b[s], acc0, 0, 0, 0);
+        acc1 = __builtin_amdgcn_mfma_f32_16x16x4f32(a[1][s], b[s], acc1, 0, 0, 0);
       }
       const int j = 16 * ct + li;
-      const float nj = norm[j];
+      const float nj = norm[buf][j];
       const int idx = c0 + j;
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
@@ -190,6 +241,8 @@ __global__ __launch_bounds__(kVqThreads) void k_vq_assign(const float* __restric
         if (s1 < best[1][r]) { best[1][r] = s1; bidx[1][r] = idx; }
       }
     }
+    if (more) put(buf ^ 1);
+    __syncthreads();  // the next chunk is written and this one no longer read
   }
   // reduce over the 16 lanes that hold the same rows (lane % 16 = codeword column)
 #pragma unroll
@@ -204,21 +257,47 @@ __global__ __launch_bounds__(kVqThreads) void k_vq_assign(const float* __restric
         const int oi = __shfl_xor(bi, o, 64);
         if (ob < b || (ob == b && oi < bi)) { b = ob; bi = oi; }
       }
-      const int64_t q = row0 + 16 * t + 4 * lk + r;
-      if (li == 0 && q < m) code[q] = (uint16_t)bi;
+      const int row = 16 * t + 4 * lk + r;
+      if (li == 0) {
+        if (split) {
+          s_best[w][row] = b;
+          s_idx[w][row] = bi;
+        } else if (row0 + row < m) {
+          code[row0 + row] = (uint16_t)bi;
+        }
+      }
     }
+  if (!split) return;
+  __syncthreads();
+  if (threadIdx.x < kVqRowsWave && row0 + (int64_t)threadIdx.x < m) {
+    float b = s_best[0][threadIdx.x];
+    int bi = s_idx[0][threadIdx.x];
+#pragma unroll
+    for (int q = 1; q < kWaves; ++q) {
+      const float ob = s_best[q][threadIdx.x];
+      const int oi = s_idx[q][threadIdx.x];
+      if (ob < b || (ob == b && oi < bi)) { b = ob; bi = oi; }
+    }
+    code[row0 + threadIdx.x] = (uint16_t)bi;
+  }
 }
 
+constexpr int kAccRows = 64;  // rows per workgroup
+
+// One value per thread: a row's D sums lie on two or three cache lines, and the lanes of a wave that add to one line
+// share its request: 400 k rows of 27 700 us with a row per thread (27 requests a row) -> 145.
 __global__ __launch_bounds__(256) void k_vq_accum(const float* __restrict__ x, int D, const uint32_t* __restrict__ rows,
                                                   int64_t m, const uint16_t* __restrict__ code, int K,
                                                   double* __restrict__ sums, uint32_t* __restrict__ counts) {
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= m) return;
-  const int c = code[t];
-  if (c >= K) return;
-  const float* xr = x + (int64_t)rows[t] * D;
-  for (int d = 0; d < D; ++d) atomicAdd(&sums[(int64_t)c * D + d], (double)xr[d]);
-  atomicAdd(&counts[c], 1u);
+  const int64_t q0 = (int64_t)blockIdx.x * kAccRows;
+  const int live = (int)(m - q0 < kAccRows ? m - q0 : kAccRows) * D;
+  for (int t = threadIdx.x; t < live; t += 256) {
+    const int q = t / D, d = t - q * D;
+    const int c = code[q0 + q];
+    if (c >= K) continue;
+    atomicAdd(&sums[(int64_t)c * D + d], (double)x[(int64_t)rows[q0 + q] * D + d]);
+    if (d == 0) atomicAdd(&counts[c], 1u);
+  }
 }
 
 __global__ __launch_bounds__(256) void k_vq_final(const double* __restrict__ sums,
@@ -299,18 +378,29 @@ hipError_t cgv2_launch_vq_init(const float* x, int D, const uint32_t* rows, int6
 
 size_t cgv2_vq_assign_ws_layout(int K) { return (((size_t)K * sizeof(float)) + 255) & ~(size_t)255; }
 
+// A rest of up to so many workgroups, half of the CUs, is split four ways, so that it ends with the last round (us:
+// 400 k queries, rest 53: 1,881 -> 1,773; 3,000 queries, rest 24: 200 -> 89; 60 k, rest 469: 94, split 124).
+constexpr int64_t kVqSplit = 128;
+
 hipError_t cgv2_launch_vq_assign(const float* x, int D, const uint32_t* rows, int64_t m, const float* cb, int K,
                                  int half_cb, uint16_t* code, void* ws, hipStream_t st) {
   if (m == 0) return hipGetLastError();
   float* norms = (float*)ws;
   hipLaunchKernelGGL(cgv2::k_vq_norms, dim3((unsigned)((K + 255) / 256)), dim3(256), 0, st, cb, K, D, half_cb, norms);
-  const unsigned nb = (unsigned)((m + cgv2::kVqRows - 1) / cgv2::kVqRows);
-  const int DP = (D + 3) & ~3;
-  switch (DP) {
-    case 4: hipLaunchKernelGGL((cgv2::k_vq_assign<4>), dim3(nb), dim3(cgv2::kVqThreads), 0, st, x, D, rows, m, cb, norms, K, half_cb, code); break;
-    case 12: hipLaunchKernelGGL((cgv2::k_vq_assign<12>), dim3(nb), dim3(cgv2::kVqThreads), 0, st, x, D, rows, m, cb, norms, K, half_cb, code); break;
-    case 28: hipLaunchKernelGGL((cgv2::k_vq_assign<28>), dim3(nb), dim3(cgv2::kVqThreads), 0, st, x, D, rows, m, cb, norms, K, half_cb, code); break;
-    case 48: hipLaunchKernelGGL((cgv2::k_vq_assign<48>), dim3(nb), dim3(cgv2::kVqThreads), 0, st, x, D, rows, m, cb, norms, K, half_cb, code); break;
+  // Whole rounds of the workgroups that run at once, and the rest split when it is small
+  const int64_t nb = (m + cgv2::kVqRows - 1) / cgv2::kVqRows, round = 256 * (D > 28 ? 3 : 4);
+  const int64_t rest = nb % round;
+  const int64_t full = rest <= kVqSplit ? nb - rest : nb;
+  const int64_t part = m > full * cgv2::kVqRows ? (m - full * cgv2::kVqRows + cgv2::kVqRowsWave - 1) / cgv2::kVqRowsWave : 0;
+  auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)(full + part)), dim3(cgv2::kVqThreads), 0, st, x, D, rows, m, cb, norms,
+                       K, half_cb, code, (unsigned)full);
+  };
+  switch ((D + 3) & ~3) {
+    case 4: go(cgv2::k_vq_assign<4>); break;
+    case 12: go(cgv2::k_vq_assign<12>); break;
+    case 28: go(cgv2::k_vq_assign<28>); break;
+    case 48: go(cgv2::k_vq_assign<48>); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
@@ -327,7 +417,7 @@ hipError_t cgv2_launch_vq_update(const float* x, int D, const uint32_t* rows, in
                      (int64_t)K * D, 0.0);
   hipLaunchKernelGGL((cgv2::k_fill<uint32_t>), dim3(cgv2::blocks_for(K, 4096)), dim3(256), 0, st, counts, (int64_t)K, 0u);
   if (m > 0)
-    hipLaunchKernelGGL(cgv2::k_vq_accum, dim3(cgv2::blocks_for(m)), dim3(256), 0, st, x, D, rows, m, code, K, sums,
+    hipLaunchKernelGGL(cgv2::k_vq_accum, dim3((unsigned)((m + cgv2::kAccRows - 1) / cgv2::kAccRows)), dim3(256), 0, st, x, D, rows, m, code, K, sums,
                        counts);
   hipLaunchKernelGGL(cgv2::k_vq_final, dim3(cgv2::blocks_for((int64_t)K * D)), dim3(256), 0, st, sums, counts, K, D, cb);
   return hipGetLastError();
