@@ -1,10 +1,11 @@
 // Per-surfel projection (2DGS surfel model of CityGaussianV2 Sec. 3.1, low-pass filter of
 // Sec. 3.2) and its reverse (chain from per-view record gradients to the parameters).
 //
-// One thread per (surfel, view).  Parameters are read as coalesced planar SoA; the geometry
-// (screen transform, centre, inverse homography, conic bound) is computed in FP64, which on
+// One thread per surfel and some of its views.  Parameters are read as coalesced planar SoA; the
+// geometry (screen transform, centre, inverse homography, conic bound) is computed in FP64, which on
 // MI355X runs at the non-packed FP32 rate and keeps the projected centre exact to ~1e-9 px at
-// 1600-px widths; the kernel is HBM-bound either way.  SH colour is FP32.
+// 1600-px widths.  SH colour is FP32.  One view is bound by HBM and by the FP64 instructions alike,
+// several by the instructions.
 #include "cgv2r_device.h"
 #include "cgv2r_kernels.h"
 
@@ -207,8 +208,9 @@ __device__ __forceinline__ void view_dir(const DevCam& c, const double (&mu)[3],
   for (int k = 0; k < 3; ++k) dir[k] = (float)(v[k] / d);
 }
 
+// What no view changes: scales, opacity, rotation, centre.
 template <class Src>
-__device__ __forceinline__ void load_geom(const Src& s, const DevCam& c, int64_t i, Geom& g) {
+__device__ __forceinline__ void load_shape(const Src& s, int64_t i, Geom& g, double (&mu)[3]) {
   g.su = (double)expf(s.log_scale(0, i));
   g.sv = (double)expf(s.log_scale(1, i));
   g.o = 1.0 / (1.0 + (double)expf(-s.opacity_logit(i)));
@@ -217,7 +219,11 @@ __device__ __forceinline__ void load_geom(const Src& s, const DevCam& c, int64_t
   const double iq = 1.0 / g.qlen;
   for (int k = 0; k < 4; ++k) g.qn[k] = q[k] * iq;
   rot_from_quat(g.qn, g.Rw);
-  const double mu[3] = {s.mean(0, i), s.mean(1, i), s.mean(2, i)};
+  for (int k = 0; k < 3; ++k) mu[k] = s.mean(k, i);
+}
+
+// The surfel in a view: camera-space centre, screen transform, normal.
+__device__ __forceinline__ void shape_in_view(const DevCam& c, const double (&mu)[3], Geom& g) {
   double cu[3], cv[3], ncd[3];
   for (int r = 0; r < 3; ++r) {
     const double R0 = c.R[3 * r], R1 = c.R[3 * r + 1], R2 = c.R[3 * r + 2];
@@ -234,6 +240,13 @@ __device__ __forceinline__ void load_geom(const Src& s, const DevCam& c, int64_t
   }
   g.flip = (ncd[0] * g.pc[0] + ncd[1] * g.pc[1] + ncd[2] * g.pc[2]) > 0 ? -1.0 : 1.0;
   for (int r = 0; r < 3; ++r) g.nc[r] = (float)(g.flip * ncd[r]);
+}
+
+template <class Src>
+__device__ __forceinline__ void load_geom(const Src& s, const DevCam& c, int64_t i, Geom& g) {
+  double mu[3];
+  load_shape(s, i, g, mu);
+  shape_in_view(c, mu, g);
   view_dir(c, mu, g.dir, g.dist);
 }
 
@@ -243,8 +256,9 @@ struct Homog {
 };
 
 __device__ __forceinline__ void homography(const double* M, Homog& h) {
-  h.cx = M[2] / M[8];
-  h.cy = M[5] / M[8];
+  const double iz = 1.0 / M[8];
+  h.cx = M[2] * iz;
+  h.cy = M[5] * iz;
   h.al1 = M[0] - h.cx * M[6];
   h.al2 = M[1] - h.cx * M[7];
   h.be1 = M[3] - h.cy * M[6];
@@ -263,42 +277,40 @@ __device__ __forceinline__ void homography(const double* M, Homog& h) {
   h.scale = m > 0 ? 1.0 / m : 1.0;
 }
 
-// Projects surfel i into view v; returns whether it is binned (visible).
+// Projects surfel i, its shape in g and mu, into view v.
 template <int DEG, class Src>
-__device__ __forceinline__ bool project_one(const Src& s, const DevCam& c, int v, int64_t i,
-                                            const cgv2_proj& out) {
+__device__ __forceinline__ void project_one(const Src& s, const DevCam& c, int v, int64_t i, bool valid, double k2, double ik2,
+                                            const double (&mu)[3], Geom& g, const cgv2_proj& out) {
   const int64_t n = s.n();
   const int64_t vi = (int64_t)v * n + i;
   uint16_t* rect = out.rect + 4 * vi;
-  Geom g;
-  load_geom(s, c, i, g);
+  shape_in_view(c, mu, g);
   unsigned fl = 0;
-  bool finite = isfinite(g.o) && isfinite(g.su) && isfinite(g.sv) && isfinite(g.qlen) && g.qlen > 0 && s.valid(i);
+  bool finite = valid;
   for (int k = 0; k < 9; ++k) finite = finite && isfinite(g.M[k]);
-  const double k2 = 2.0 * log(255.0 * g.o);
   if (!finite) fl = CGV2_F_NONFINITE;
   else if (!(g.M[8] > (double)c.znear)) fl = CGV2_F_NEAR;
   else if (!(k2 > 0)) fl = CGV2_F_OPACITY;
   double Q33 = 0;
   if (!fl) {
-    Q33 = g.M[6] * g.M[6] + g.M[7] * g.M[7] - g.M[8] * g.M[8] / k2;
+    Q33 = g.M[6] * g.M[6] + g.M[7] * g.M[7] - g.M[8] * g.M[8] * ik2;
     if (!(Q33 < 0)) fl = CGV2_F_BEHIND;
   }
   if (fl) {
     out.flags[vi] = (uint8_t)fl;
     out.radius[vi] = 0.f;
     *(uint2*)rect = make_uint2(0u, 0u);
-    return false;
+    return;
   }
   const double* M = g.M;
-  const double ik2 = 1.0 / k2;
   const double Q13 = M[0] * M[6] + M[1] * M[7] - M[2] * M[8] * ik2;
   const double Q23 = M[3] * M[6] + M[4] * M[7] - M[5] * M[8] * ik2;
   const double Q11 = M[0] * M[0] + M[1] * M[1] - M[2] * M[2] * ik2;
   const double Q22 = M[3] * M[3] + M[4] * M[4] - M[5] * M[5] * ik2;
-  const double xb = Q13 / Q33, yb = Q23 / Q33;
-  const double ex = sqrt(fmax(0.0, xb * xb - Q11 / Q33));
-  const double ey = sqrt(fmax(0.0, yb * yb - Q22 / Q33));
+  const double iQ = 1.0 / Q33;  // (one FP64 division for four)
+  const double xb = Q13 * iQ, yb = Q23 * iQ;
+  const double ex = sqrt(fmax(0.0, xb * xb - Q11 * iQ));
+  const double ey = sqrt(fmax(0.0, yb * yb - Q22 * iQ));
   Homog h;
   homography(M, h);
   const double rf = sqrt(0.5 * k2);
@@ -321,7 +333,7 @@ __device__ __forceinline__ bool project_one(const Src& s, const DevCam& c, int v
   if (!(i0 <= i1 && j0 <= j1)) {
     out.flags[vi] = (uint8_t)fl;
     *(uint2*)rect = make_uint2(0u, 0u);
-    return false;
+    return;
   }
   fl |= CGV2_F_VISIBLE;
   out.flags[vi] = (uint8_t)fl;
@@ -331,6 +343,7 @@ __device__ __forceinline__ bool project_one(const Src& s, const DevCam& c, int v
 
   // SH colour
   constexpr int K = (DEG + 1) * (DEG + 1);
+  view_dir(c, mu, g.dir, g.dist);
   float Y[K];
   sh_basis<DEG>(g.dir[0], g.dir[1], g.dir[2], Y, nullptr);
   float f[3 * K];
@@ -355,21 +368,34 @@ __device__ __forceinline__ bool project_one(const Src& s, const DevCam& c, int v
   rp[4] = make_float4(g.nc[0], g.nc[1], g.nc[2], (float)k2);
   const uint32_t pxr = (uint32_t)i0 | ((uint32_t)i1 << 16), pyr = (uint32_t)j0 | ((uint32_t)j1 << 16);
   rp[5] = make_float4(__uint_as_float(pxr), __uint_as_float(pyr), 0.f, 0.f);
-  return true;
+}
+
+// Surfel i in the views [blockIdx.y * per, + per) of the launch: its scales, rotation and opacity (a third of the FP64
+// work) once for all.  10 M surfels, 8 views: 2,220 us with a thread per view -> 1,425; 1 M, one view 32 -> 29 (three
+// divisions by one number are one).  4 waves per SIMD instead of 3 spill (1,655).
+template <int DEG, class Src>
+__device__ __forceinline__ void project_views(const Src& s, const CamPack& cams, int per, const cgv2_proj& out) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= s.n()) return;
+  Geom g;
+  double mu[3];
+  load_shape(s, i, g, mu);
+  const bool valid = isfinite(g.o) && isfinite(g.su) && isfinite(g.sv) && isfinite(g.qlen) && g.qlen > 0 && s.valid(i);
+  const double k2 = 2.0 * log(255.0 * g.o), ik2 = 1.0 / k2;
+  const int end = min(cams.count, ((int)blockIdx.y + 1) * per);
+  for (int lv = (int)blockIdx.y * per; lv < end; ++lv)
+    project_one<DEG>(s, cams.c[lv], cams.v0 + lv, i, valid, k2, ik2, mu, g, out);
 }
 
 template <int DEG>
-__global__ __launch_bounds__(256) void k_project(cgv2_surfels s, CamPack cams, cgv2_proj out) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int v = cams.v0 + (int)blockIdx.y;
-  if (i < s.n) project_one<DEG>(FullSource{s}, cams.c[blockIdx.y], v, i, out);
+__global__ __launch_bounds__(256) void k_project(cgv2_surfels s, CamPack cams, int per, cgv2_proj out) {
+  project_views<DEG>(FullSource{s}, cams, per, out);
 }
 
 template <int DEG>
-__global__ __launch_bounds__(256) void k_project_compact(cgv2_surfels_compact s, CamPack cams, cgv2_proj out) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int v = cams.v0 + (int)blockIdx.y;
-  if (i < s.n) project_one<DEG>(CompactSource{s}, cams.c[blockIdx.y], v, i, out);
+__global__ __launch_bounds__(256) void k_project_compact(cgv2_surfels_compact s, CamPack cams, int per,
+                                                         cgv2_proj out) {
+  project_views<DEG>(CompactSource{s}, cams, per, out);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -750,27 +776,39 @@ __global__ __launch_bounds__(64, 2) void k_project_bwd_views(cgv2_surfels s, Cam
 
 }  // namespace cgv2
 
+// Views per thread: all of a launch's once the surfels alone fill the chip four times (us: 1 M surfels, 5 views, 3 a
+// thread 115 -> 82); fewer surfels keep a view a thread (132 k, 8 views 34, as before).
+constexpr int64_t kProjectBlocks = 4096;
+
+static int views_per_thread(int64_t n, int count) {
+  const int64_t blocks = (n + 255) / 256;
+  const int64_t slices = std::min<int64_t>(count, (kProjectBlocks + blocks - 1) / blocks);
+  return (int)((count + slices - 1) / slices);
+}
+
 hipError_t cgv2_launch_project_compact(const cgv2_surfels_compact& s, const cgv2::CamPack& cams, const cgv2_proj& p,
                                       hipStream_t st) {
   if (s.n == 0) return hipSuccess;
-  dim3 grid((unsigned)((s.n + 255) / 256), (unsigned)cams.count);
+  const int per = views_per_thread(s.n, cams.count);
+  dim3 grid((unsigned)((s.n + 255) / 256), (unsigned)((cams.count + per - 1) / per));
   switch (s.sh_degree) {
-    case 0: hipLaunchKernelGGL(cgv2::k_project_compact<0>, grid, dim3(256), 0, st, s, cams, p); break;
-    case 1: hipLaunchKernelGGL(cgv2::k_project_compact<1>, grid, dim3(256), 0, st, s, cams, p); break;
-    case 2: hipLaunchKernelGGL(cgv2::k_project_compact<2>, grid, dim3(256), 0, st, s, cams, p); break;
-    default: hipLaunchKernelGGL(cgv2::k_project_compact<3>, grid, dim3(256), 0, st, s, cams, p); break;
+    case 0: hipLaunchKernelGGL(cgv2::k_project_compact<0>, grid, dim3(256), 0, st, s, cams, per, p); break;
+    case 1: hipLaunchKernelGGL(cgv2::k_project_compact<1>, grid, dim3(256), 0, st, s, cams, per, p); break;
+    case 2: hipLaunchKernelGGL(cgv2::k_project_compact<2>, grid, dim3(256), 0, st, s, cams, per, p); break;
+    default: hipLaunchKernelGGL(cgv2::k_project_compact<3>, grid, dim3(256), 0, st, s, cams, per, p); break;
   }
   return hipGetLastError();
 }
 
 hipError_t cgv2_launch_project(const cgv2_surfels& s, const cgv2::CamPack& cams, const cgv2_proj& p, hipStream_t st) {
   if (s.n == 0) return hipSuccess;
-  dim3 grid((unsigned)((s.n + 255) / 256), (unsigned)cams.count);
+  const int per = views_per_thread(s.n, cams.count);
+  dim3 grid((unsigned)((s.n + 255) / 256), (unsigned)((cams.count + per - 1) / per));
   switch (s.sh_degree) {
-    case 0: hipLaunchKernelGGL(cgv2::k_project<0>, grid, dim3(256), 0, st, s, cams, p); break;
-    case 1: hipLaunchKernelGGL(cgv2::k_project<1>, grid, dim3(256), 0, st, s, cams, p); break;
-    case 2: hipLaunchKernelGGL(cgv2::k_project<2>, grid, dim3(256), 0, st, s, cams, p); break;
-    default: hipLaunchKernelGGL(cgv2::k_project<3>, grid, dim3(256), 0, st, s, cams, p); break;
+    case 0: hipLaunchKernelGGL(cgv2::k_project<0>, grid, dim3(256), 0, st, s, cams, per, p); break;
+    case 1: hipLaunchKernelGGL(cgv2::k_project<1>, grid, dim3(256), 0, st, s, cams, per, p); break;
+    case 2: hipLaunchKernelGGL(cgv2::k_project<2>, grid, dim3(256), 0, st, s, cams, per, p); break;
+    default: hipLaunchKernelGGL(cgv2::k_project<3>, grid, dim3(256), 0, st, s, cams, per, p); break;
   }
   return hipGetLastError();
 }
