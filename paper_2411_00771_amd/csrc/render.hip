@@ -19,6 +19,7 @@
 #include "cgv2r_kernels.h"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace cgv2 {
 
@@ -37,28 +38,39 @@ struct RenderArgs {
   float* cws;   // contribution mode: [V][n] pairs (sum of alpha^gamma T^(1-gamma), pixel count)
   float gamma;
   const uint32_t* order;  // launch order of this view chunk (heaviest tiles first), or null
-  uint32_t n_q, n_h;      // the first n_q tiles of 'order' run as four quadrant blocks, the next n_h as two halves
+  // the first n_b tiles of 'order' run as sixteen 4x4 blocks (the forward image only), the next n_q as four
+  // quadrant blocks, the next n_h as two halves
+  uint32_t n_b, n_q, n_h;
 };
 
 // Block -> (local view, tile) index and quadrant subset.  Without a launch order: the XCD-aware spatial
 // mapping, whole tiles.  With one (the bin_sort's heaviest-first order; bounded, so a stale order cannot
-// leave the launch), the n_q heaviest tiles run as four single-quadrant blocks each (blocks [0, 4 n_q)),
-// the next n_h as two halves (top 0x3, bottom 0xc; the following 2 n_h blocks), the rest whole; the
-// launch has 3 n_q + n_h blocks more than tiles.
+// leave the launch), the n_b heaviest tiles run as sixteen blocks each (bit kBlockBit of sub, the block's
+// row-major number below it), the next n_q as four single-quadrant blocks, the next n_h as two halves
+// (top 0x3, bottom 0xc), the rest whole; the launch has 15 n_b + 3 n_q + n_h blocks more than tiles.
+constexpr uint32_t kBlockBit = 16u;
 __device__ __forceinline__ uint32_t tile_of_block(const RenderArgs& a, uint32_t& sub) {
-  const uint32_t bid = blockIdx.x, tiles = gridDim.x - 3u * a.n_q - a.n_h;
+  const uint32_t tiles = gridDim.x - 15u * a.n_b - 3u * a.n_q - a.n_h;
+  uint32_t bid = blockIdx.x;
   sub = 0xfu;
   if (!a.order) return xcd_remap(bid, tiles);
   uint32_t i;
-  if (bid < 4u * a.n_q) {
-    i = bid >> 2;
-    sub = 1u << (bid & 3u);
-  } else if (bid < 4u * a.n_q + 2u * a.n_h) {
-    const uint32_t r = bid - 4u * a.n_q;
-    i = a.n_q + (r >> 1);
-    sub = (r & 1u) ? 0xcu : 0x3u;
+  if (bid < 16u * a.n_b) {
+    i = bid >> 4;
+    sub = kBlockBit | (bid & 15u);
   } else {
-    i = bid - 3u * a.n_q - a.n_h;
+    bid -= 16u * a.n_b;
+    if (bid < 4u * a.n_q) {
+      i = bid >> 2;
+      sub = 1u << (bid & 3u);
+    } else if (bid < 4u * a.n_q + 2u * a.n_h) {
+      const uint32_t r = bid - 4u * a.n_q;
+      i = a.n_q + (r >> 1);
+      sub = (r & 1u) ? 0xcu : 0x3u;
+    } else {
+      i = bid - 3u * a.n_q - a.n_h;
+    }
+    i += a.n_b;
   }
   const uint32_t b = a.order[i];
   return b < tiles ? b : tiles - 1u;
@@ -135,7 +147,10 @@ __device__ __forceinline__ void stage_load(StageIn& in, const float* rec, int64_
 // Writes the entry's LDS record and returns its mask among the quadrants in.qm: those its pixel rect
 // meets and, with 'reach', that some pixel sample of the surfel can reach (reach_quadrants; without it
 // in.qm is the forward's mask of the quadrants with a contributing pixel).
-__device__ __forceinline__ uint32_t stage_put(Stage& s, int lane, const StageIn& in, int ox, int oy, bool reach) {
+// kBlock: instead, whether the pixel rect meets the 4x4 block at (bx, by) of a reached quadrant.
+template <bool kBlock = false>
+__device__ __forceinline__ uint32_t stage_put(Stage& s, int lane, const StageIn& in, int ox, int oy, bool reach,
+                                              int bx = 0, int by = 0) {
   // an entry no pixel takes reaches no quadrant here
   if (in.qm == 0u) return 0u;
   const float4 r0 = in.r[0], r1 = in.r[1], r2 = in.r[2], r3 = in.r[3], r4 = in.r[4], r5 = in.r[5];
@@ -158,6 +173,7 @@ __device__ __forceinline__ uint32_t stage_put(Stage& s, int lane, const StageIn&
     if (i0 <= x0 + 7 && i1 >= x0 && j0 <= y0 + 7 && j1 >= y0) m |= 1u << k;
   }
   m &= in.qm;
+  if (kBlock && !(i0 <= bx + 3 && i1 >= bx && j0 <= by + 3 && j1 >= by)) m = 0u;
   if (reach && m) m = reach_quadrants(m, q0, q1, r2.z, r4.w);
   return in.valid ? m : 0u;
 }
@@ -497,12 +513,176 @@ __device__ __forceinline__ void render_fwd_tile(const RenderArgs& a, Stage& s, u
   }
 }
 
+// Quad-lane broadcast of lane s's value (0 to 3).
+template <int s>
+__device__ __forceinline__ float quad_lane(float x) {
+  return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), s * 0x55, 0xf, 0xf, true));
+}
+template <int kCtrl>
+__device__ __forceinline__ float quad_swap(float x) {
+  return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), kCtrl, 0xf, 0xf, true));
+}
+
+// Forward of one 4x4 block (of quadrant k) of a heavy tile or of a small launch.  The walk of a long list is one chain of dependent
+// entries, bound by the wave's own instruction issue, and its small surfels meet few blocks; here the four lanes of
+// a pixel evaluate four entries of the block's list at a time, the transmittance runs through them by quad-lane
+// broadcasts, and each lane adds two of the images' channels over the four: every operation and its order are those
+// of the tile's walk, bit for bit.
+template <bool kMask, int k>
+__device__ __forceinline__ void render_fwd_block(const RenderArgs& a, Stage& s, uint32_t b, int bx, int by) {
+  const int lv = (int)(b / (uint32_t)a.tiles);
+  const int v = a.cams.v0 + lv;
+  const int t = (int)(b % (uint32_t)a.tiles);
+  const DevCam& c = a.cams.c[lv];
+  const int W = c.W, H = c.H;
+  const int lane = threadIdx.x, part = lane & 3;
+  const int ox = t % a.tiles_x * kTile, oy = t / a.tiles_x * kTile;
+  const int px = ox + bx + ((lane >> 2) & 3), py = oy + by + (lane >> 4);
+  const uint32_t start = a.ranges[(int64_t)v * a.tiles + t], end = a.ranges[(int64_t)v * a.tiles + t + 1];
+  const int64_t vn = (int64_t)v * a.n;
+  const bool inside = px < W && py < H;
+  // the pixel of quadrant 0 whose terms the evaluation starts from
+  const float lx0 = (float)(px - ox - 8 * (k & 1)) + 0.5f, ly0 = (float)(py - oy - 8 * (k >> 1)) + 0.5f;
+
+  float T = inside ? 1.f : -1.f;  // as FwdState's, the same in the pixel's four lanes
+  float A0 = 0.f, A1 = 0.f;       // lane 0: r, g; 1: b, depth; 2: nx, ny; 3: nz
+  float Dm = 0.f;
+  uint32_t last = start, med = 0;  // one past the entry
+  uint32_t nid = start + lane < end ? a.ids[start + lane] : 0u;
+  StageIn in;
+  stage_load(in, a.rec, vn, a.n, nid, start + lane < end ? 1u << k : 0u);
+  nid = start + 64u + lane < end ? a.ids[start + 64u + lane] : 0u;
+  bool live = __ballot(T > 0.f) != 0;
+  for (uint32_t base = start; base < end && live; base += 64) {
+    const uint32_t idx = base + lane;
+    uint64_t todo = __ballot(stage_put<true>(s, lane, in, ox, oy, true, bx, by) != 0u);
+    stage_load(in, a.rec, vn, a.n, nid, idx + 64u < end ? 1u << k : 0u);
+    nid = idx + 128u < end ? a.ids[idx + 128u] : 0u;
+    __syncthreads();
+    uint64_t cq = 0;
+    while (todo != 0) {
+      int at[4];
+      bool has[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        has[q] = todo != 0;
+        at[q] = has[q] ? __builtin_ctzll(todo) : at[0];
+        todo &= todo - 1;
+      }
+      const int j = part == 0 ? at[0] : part == 1 ? at[1] : part == 2 ? at[2] : at[3];
+      const bool act = part == 0 || (part == 1 ? has[1] : part == 2 ? has[2] : has[3]);
+      const float4 q0 = s.q[j][0], q1 = s.q[j][1], q2 = s.q[j][2];
+      float2 ch[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) ch[q] = ((const float2*)&s.q[at[q]][3])[part];
+      LaneTerms lt;
+      lane_terms(lx0, ly0, q0, q1, q2, lt);
+      Px e;
+      eval_px<k>(lt, q2.y, e);
+      bool upd = act && T > 0.f && e.alpha >= kAlphaMin;
+      const uint64_t taken = __ballot(upd);
+      if (taken == 0) continue;
+      if (kMask) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          if (taken & (0x1111111111111111ull << q)) cq |= 1ull << at[q];
+      }
+      const float al = upd ? e.alpha : 0.f;
+      const float om = 1.f - al;
+      const float o0 = quad_lane<0>(om), o1 = quad_lane<1>(om), o2 = quad_lane<2>(om), o3 = quad_lane<3>(om);
+      const float T1 = T * o0, T2 = T1 * o1, T3 = T2 * o2, T4 = T3 * o3;
+      float Tf = part == 0 ? T : part == 1 ? T1 : part == 2 ? T2 : T3;  // in front of this lane's entry
+      if (__ballot(T > 0.f && T4 < kTmin) == 0) {
+        T = T4;
+      } else {
+        // some pixel stops within these entries: one after the other
+        float cur = T;
+        auto step = [&](int q, float o) {
+          const float Tn = cur * o;
+          const bool takes = cur > 0.f && o < 1.f, stops = Tn < kTmin;
+          if (part == q) {
+            Tf = cur;
+            upd = upd && takes && !stops;
+          }
+          cur = takes ? (stops ? -cur : Tn) : cur;
+        };
+        step(0, o0);
+        step(1, o1);
+        step(2, o2);
+        step(3, o3);
+        T = cur;
+        live = __ballot(T > 0.f) != 0;
+        if (!live) todo = 0;
+      }
+      const float wgt = upd ? al * Tf : 0.f;
+      const float zf = e.is3d ? q2.w * e.iw : q2.z;
+      auto add = [&](const float2& x, float w, float z) {
+        A0 = fmaf(w, x.x, A0);
+        A1 = fmaf(w, part == 1 ? z : x.y, A1);
+      };
+      add(ch[0], quad_lane<0>(wgt), quad_lane<0>(zf));
+      add(ch[1], quad_lane<1>(wgt), quad_lane<1>(zf));
+      add(ch[2], quad_lane<2>(wgt), quad_lane<2>(zf));
+      add(ch[3], quad_lane<3>(wgt), quad_lane<3>(zf));
+      const uint32_t next = base + (uint32_t)j + 1u;
+      const bool m = upd && Tf > 0.5f;
+      Dm = m ? zf : Dm;
+      med = m ? next : med;
+      last = upd ? next : last;
+    }
+    if (kMask && ((cq >> lane) & 1u))
+      atomicOr((uint32_t*)(a.img.qmask + (idx & ~3u)), (1u << k) << (8u * (idx & 3u)));
+    __syncthreads();
+  }
+  // the latest of the four lanes' entries
+  auto over = [&](auto ctrl) {
+    constexpr int kC = decltype(ctrl)::value;
+    const float od = quad_swap<kC>(Dm);
+    const uint32_t om = __float_as_uint(quad_swap<kC>(__uint_as_float(med)));
+    Dm = om > med ? od : Dm;
+    med = max(med, om);
+    last = max(last, __float_as_uint(quad_swap<kC>(__uint_as_float(last))));
+  };
+  over(std::integral_constant<int, 0xb1>{});  // lanes 1 0 3 2
+  over(std::integral_constant<int, 0x4e>{});  // lanes 2 3 0 1
+  if (!inside) return;
+  const int64_t HW = (int64_t)W * H;
+  const cgv2_image& im = a.img;
+  const int64_t p = (int64_t)py * W + px, vp = (int64_t)v * HW + p;
+  T = fabsf(T);
+  float* o = part < 2 ? im.rgb : im.normal;
+  if (o) {
+    o += (int64_t)v * 3 * HW + p + (part & 1 ? 2 * HW : 0);
+    o[0] = part < 2 ? fmaf(T, c.bg[part == 0 ? 0 : 2], A0) : A0;
+    if (!(part & 1)) o[HW] = part < 2 ? fmaf(T, c.bg[1], A1) : A1;
+  }
+  if (part == 1 && im.depth) im.depth[vp] = A1;
+  if (part != 0) return;
+  if (im.depth_med) im.depth_med[vp] = Dm;
+  if (im.alpha) im.alpha[vp] = 1.f - T;
+  if (im.T_final) im.T_final[vp] = T;
+  if (im.last) im.last[vp] = last;
+  if (im.med) im.med[vp] = med - 1u;
+}
+
 template <bool kCount, bool kMask, int kContrib>
 __global__ __launch_bounds__(64) void k_render_fwd(RenderArgs a) {
   __shared__ Stage s;
   uint32_t sub;
   const uint32_t b = tile_of_block(a, sub);
   if (*a.status != 0) return;
+  if constexpr (!kCount && kContrib == kNoContrib) {
+    if (sub & kBlockBit) {
+      const int bx = 4 * (int)(sub & 3u), by = (int)(sub & 12u);
+      switch ((bx >> 3) + 2 * (by >> 3)) {
+        case 0: render_fwd_block<kMask, 0>(a, s, b, bx, by); break;
+        case 1: render_fwd_block<kMask, 1>(a, s, b, bx, by); break;
+        case 2: render_fwd_block<kMask, 2>(a, s, b, bx, by); break;
+        default: render_fwd_block<kMask, 3>(a, s, b, bx, by); break;
+      }
+      return;
+    }
+  }
   switch (sub) {
     case 0x1u: render_fwd_tile<kCount, kMask, kContrib, 0x1u>(a, s, b); break;
     case 0x2u: render_fwd_tile<kCount, kMask, kContrib, 0x2u>(a, s, b); break;
@@ -885,7 +1065,7 @@ __global__ __launch_bounds__(256) void k_clear_split_qmask(RenderArgs a) {
 }  // namespace cgv2
 
 static void split_tiles(cgv2::RenderArgs& a, int64_t resident, int64_t fill_below) {
-  a.n_q = a.n_h = 0;
+  a.n_b = a.n_q = a.n_h = 0;
   if (!a.order) return;
   const int64_t all = (int64_t)a.cams.count * a.tiles;
   int64_t q = std::min<int64_t>(all / kSplitDiv, kSplitMax);
@@ -919,7 +1099,7 @@ static cgv2::RenderArgs make_args(const cgv2_proj& p, const cgv2_bins& b, const 
   a.counters = counters;
   a.cws = nullptr;
   a.gamma = 0.f;
-  a.n_q = a.n_h = 0;
+  a.n_b = a.n_q = a.n_h = 0;
   return a;
 }
 
@@ -930,13 +1110,29 @@ static void split_bwd(cgv2::RenderArgs& a, bool geom) {
   split_tiles(a, resident, resident * 3 / 4 + 1);
 }
 
+// Of the quadrant tiles, the heaviest run as blocks while the launch is small: a block tile issues up to twice the
+// instructions of four quadrants, but in sixteen chains a quarter to an eighth as long.  Forward, us, with
+// quadrants and with blocks: 64 tiles 43 -> 26, 260 tiles 65 -> 42 (1 M surfels 264 -> 162, 2 M visible ones 4,370 ->
+// 1,940), 475 tiles 89 -> 66, 1,200 tiles 172 -> 156 and 97 -> 98.  Bins sized for long lists (a mean capacity of
+// kLongLists a tile) have a few tiles many times the mean, whose chains then bound the launch: 1,200 tiles with
+// lists to 32,767 1,850 -> 1,030 with 8,192 waves, 1,853 with 5,120, 1,107 with 10,240.  From 2,048 tiles on the chip
+// is full without: blocks for the heaviest 1/64 cost 1,600x1,066 152 -> 170 and 3,840x2,160 1,116 -> 1,183.
+constexpr int64_t kLongLists = 3000, kBlockWaves = 5120, kBlockWavesLong = 8192;
+static void split_blocks(cgv2::RenderArgs& a, int64_t capacity) {
+  const int64_t all = (int64_t)a.cams.count * a.tiles;
+  const int64_t waves = capacity / std::max<int64_t>(all, 1) >= kLongLists ? kBlockWavesLong : kBlockWaves;
+  a.n_b = (uint32_t)std::min<int64_t>(std::max<int64_t>((waves - 4 * all) / 12, 0), a.n_q);
+  a.n_q -= a.n_b;
+}
+
 hipError_t cgv2_launch_render_fwd(const cgv2_proj& p, const cgv2_bins& b, const cgv2::CamPack& cams, int64_t n,
                                   int tiles_x, int tiles_y, const cgv2_image& img, hipStream_t st) {
   cgv2::RenderArgs a = make_args(p, b, cams, n, tiles_x, tiles_y, &img, nullptr);
   split_fwd(a);
-  const unsigned grid = (unsigned)((int64_t)cams.count * a.tiles + 3 * a.n_q + a.n_h);
-  if (img.qmask && a.n_q + a.n_h)
-    hipLaunchKernelGGL(cgv2::k_clear_split_qmask, dim3(a.n_q + a.n_h), dim3(256), 0, st, a);
+  split_blocks(a, b.capacity);
+  const unsigned grid = (unsigned)((int64_t)cams.count * a.tiles + 15 * a.n_b + 3 * a.n_q + a.n_h);
+  if (img.qmask && a.n_b + a.n_q + a.n_h)
+    hipLaunchKernelGGL(cgv2::k_clear_split_qmask, dim3(a.n_b + a.n_q + a.n_h), dim3(256), 0, st, a);
   if (img.qmask) hipLaunchKernelGGL((cgv2::k_render_fwd<false, true, cgv2::kNoContrib>), dim3(grid), dim3(64), 0, st, a);
   else hipLaunchKernelGGL((cgv2::k_render_fwd<false, false, cgv2::kNoContrib>), dim3(grid), dim3(64), 0, st, a);
   return hipGetLastError();
