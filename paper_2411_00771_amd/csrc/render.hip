@@ -38,8 +38,8 @@ struct RenderArgs {
   float* cws;   // contribution mode: [V][n] pairs (sum of alpha^gamma T^(1-gamma), pixel count)
   float gamma;
   const uint32_t* order;  // launch order of this view chunk (heaviest tiles first), or null
-  // the first n_b tiles of 'order' run as sixteen 4x4 blocks (the forward image only), the next n_q as four
-  // quadrant blocks, the next n_h as two halves
+  // the first n_b tiles of 'order' run as sixteen 4x4 blocks (none in the counting and contribution passes), the
+  // next n_q as four quadrant blocks, the next n_h as two halves
   uint32_t n_b, n_q, n_h;
 };
 
@@ -745,49 +745,44 @@ __device__ __forceinline__ void bwd_init(const BwdArgs& A, const DevCam& c, int 
   p.sS = Tf * bS;
 }
 
-// One pixel's share of the record gradients of a staged surfel.  Branch-free: a pixel that does not
-// take this surfel (entry at or past its 'last', or alpha below 1/255) adds zero and keeps its T.
+// What a pixel takes from a staged surfel, before its transmittance and sums come in.
+struct BwdTake {
+  float rom, ar, g, gs, zf;  // 1 / (1 - alpha), alpha / (1 - alpha), upstream . attributes (total, SSIM-only), depth
+  bool con;
+};
+
+template <bool kGeom>
+__device__ __forceinline__ void bwd_take(const Px& e, bool con, const float4& q2, const float4& q3, const float4& q4,
+                                         const BwdState& p, BwdTake& t) {
+  t.con = con;
+  const float al = con ? e.alpha : 0.f;
+  t.rom = __builtin_amdgcn_rcpf(1.f - al);
+  t.ar = al * t.rom;
+  t.g = fmaf(p.GC[0], q3.x, fmaf(p.GC[1], q3.y, p.GC[2] * q3.z));
+  t.gs = fmaf(p.GS[0], q3.x, fmaf(p.GS[1], q3.y, p.GS[2] * q3.z));
+  t.zf = 0.f;
+  if (kGeom) {
+    t.zf = e.is3d ? q2.w * e.iw : q2.z;
+    t.g = fmaf(p.GN[0], q4.x, t.g);
+    t.g = fmaf(p.GN[1], q4.y, t.g);
+    t.g = fmaf(p.GN[2], q4.z, t.g);
+    t.g = fmaf(p.GD2, t.zf, t.g);
+  }
+}
+
+// Its share of the record gradients: wgt = alpha T, nA and nS = 2 (1 - alpha) dL/dalpha of the total and the SSIM-only
+// upstream (what lies behind minus T in front times this fragment's attributes).
 // acc[G_OP] collects 2 d rho (the opacity gradient is -alpha_raw d rho / o, formed at the atomics);
 // acc[G_R..G_B] and the normal sums collect -2 times their gradients.
-template <int k, bool kGeom>
-__device__ __forceinline__ void bwd_px(const LaneTerms& lt, const float4& q0, const float4& q1, const float4& q2,
-                                       const float4& q3, const float4& q4, uint32_t e_idx, BwdState& p,
-                                       float (&acc)[kGradFields], bool& any) {
-  Px e;
-  eval_px<k>(lt, q2.y, e);
-  const bool con = e_idx < p.last && e.alpha >= kAlphaMin;
-  // for a quadrant without a contributing pixel every update below is the identity
-  if (__ballot(con) == 0) return;
-  any = true;  // wave-uniform: some pixel takes the entry
+template <bool kGeom>
+__device__ __forceinline__ void bwd_terms(const Px& e, const BwdTake& t, const float4& q0, const float4& q1,
+                                          const float4& q2, uint32_t e_idx, const BwdState& p, float wgt, float nA,
+                                          float nS, float (&acc)[kGradFields]) {
   const float a11 = q0.z, a12 = q0.w, a21 = q1.x, a22 = q1.y, w0 = q1.z, w1 = q1.w, w2 = q2.x;
-  const float zc = q2.z, zw = q2.w;
-  const float al = con ? e.alpha : 0.f;
-  const float rom = __builtin_amdgcn_rcpf(1.f - al);
-  const float ar = al * rom;  // alpha / (1 - alpha)
-  // upstream . (this fragment's attributes), for the total and the SSIM-only upstream
-  float g = fmaf(p.GC[0], q3.x, fmaf(p.GC[1], q3.y, p.GC[2] * q3.z));
-  const float gs = fmaf(p.GS[0], q3.x, fmaf(p.GS[1], q3.y, p.GS[2] * q3.z));
-  float zf = 0.f;
-  if (kGeom) {
-    zf = e.is3d ? zw * e.iw : zc;
-    g = fmaf(p.GN[0], q4.x, g);
-    g = fmaf(p.GN[1], q4.y, g);
-    g = fmaf(p.GN[2], q4.z, g);
-    g = fmaf(p.GD2, zf, g);
-  }
-  // Tn = the transmittance after this fragment (its last use is the step back to the one in front, so
-  // the step writes in place)
-  const float Tn = p.T;
-  // 2 (1 - alpha) dL/dalpha: what lies behind minus T in front times this fragment's attributes
-  const float nA = fmaf(-Tn, g, p.sA);
-  const float nS = fmaf(-Tn, gs, p.sS);
-  const float wgt = Tn * ar;  // alpha T_i
-  p.T = Tn * rom;             // T_i, in front of it
-  p.sA = fmaf(wgt, g, p.sA);
-  p.sS = fmaf(wgt, gs, p.sS);
+  const float zc = q2.z;
   // d alpha / d alpha_raw / (1 - alpha): the 0.99 clamp blocks the path to o and rho; below it alpha is
   // alpha_raw, and a pixel that does not take the entry has al = 0
-  const float rA = e.araw > kAlphaMax ? 0.f : ar;
+  const float rA = e.araw > kAlphaMax ? 0.f : t.ar;
   acc[G_R] = fmaf(p.GC[0], wgt, acc[G_R]);
   acc[G_G] = fmaf(p.GC[1], wgt, acc[G_G]);
   acc[G_B] = fmaf(p.GC[2], wgt, acc[G_B]);
@@ -796,7 +791,7 @@ __device__ __forceinline__ void bwd_px(const LaneTerms& lt, const float4& q0, co
     acc[G_NX] = fmaf(p.GN[0], wgt, acc[G_NX]);
     acc[G_NY] = fmaf(p.GN[1], wgt, acc[G_NY]);
     acc[G_NZ] = fmaf(p.GN[2], wgt, acc[G_NZ]);
-    dz = fmaf(p.GD, wgt, con && e_idx == p.med ? p.GM : 0.f);
+    dz = fmaf(p.GD, wgt, t.con && e_idx == p.med ? p.GM : 0.f);
   }
   // -2 d rho of either upstream
   const float ndr = rA * nA;
@@ -810,7 +805,7 @@ __device__ __forceinline__ void bwd_px(const LaneTerms& lt, const float4& q0, co
     const float u1 = e.P1 * iww, u2 = e.P2 * iww, uw = e.rho * iw;
     const float nP1 = ndr * u1, nP2 = ndr * u2;
     // the intersection depth z_c w0 / w also depends on w
-    const float dzw = kGeom ? dz * zf * iw : 0.f;
+    const float dzw = kGeom ? dz * t.zf * iw : 0.f;
     const float gw = kGeom ? fmaf(ndr, uw, -dzw) : ndr * uw;
     acc[G_A11] = fmaf(-nP1, e.xr, acc[G_A11]);
     acc[G_A12] = fmaf(-nP1, e.yr, acc[G_A12]);
@@ -835,6 +830,32 @@ __device__ __forceinline__ void bwd_px(const LaneTerms& lt, const float4& q0, co
   acc[G_CY] = fmaf(ndr, vy, acc[G_CY]);
   acc[G_SCX] = fmaf(nds, vx, acc[G_SCX]);
   acc[G_SCY] = fmaf(nds, vy, acc[G_SCY]);
+}
+
+// One pixel's share of the record gradients of a staged surfel.  Branch-free: a pixel that does not
+// take this surfel (entry at or past its 'last', or alpha below 1/255) adds zero and keeps its T.
+template <int k, bool kGeom>
+__device__ __forceinline__ void bwd_px(const LaneTerms& lt, const float4& q0, const float4& q1, const float4& q2,
+                                       const float4& q3, const float4& q4, uint32_t e_idx, BwdState& p,
+                                       float (&acc)[kGradFields], bool& any) {
+  Px e;
+  eval_px<k>(lt, q2.y, e);
+  const bool con = e_idx < p.last && e.alpha >= kAlphaMin;
+  // for a quadrant without a contributing pixel every update below is the identity
+  if (__ballot(con) == 0) return;
+  any = true;  // wave-uniform: some pixel takes the entry
+  BwdTake t;
+  bwd_take<kGeom>(e, con, q2, q3, q4, p, t);
+  // Tn = the transmittance after this fragment (its last use is the step back to the one in front, so
+  // the step writes in place)
+  const float Tn = p.T;
+  const float nA = fmaf(-Tn, t.g, p.sA);
+  const float nS = fmaf(-Tn, t.gs, p.sS);
+  const float wgt = Tn * t.ar;  // alpha T_i
+  p.T = Tn * t.rom;             // T_i, in front of it
+  p.sA = fmaf(wgt, t.g, p.sA);
+  p.sS = fmaf(wgt, t.gs, p.sS);
+  bwd_terms<kGeom>(e, t, q0, q1, q2, e_idx, p, wgt, nA, nS, acc);
 }
 
 // Factor that turns the reduced value of field 'slot' into its record gradient: the staged numerator
@@ -993,12 +1014,129 @@ __device__ __forceinline__ void render_bwd_tile(const BwdArgs& A, Stage& s, uint
   }
 }
 
+// Reverse pass of one 4x4 block (of quadrant k): as render_fwd_block, the four lanes of a pixel take four entries at a
+// time, from the back.  Each pixel's terms are those of the tile's walk bit for bit; the record gradients of the four
+// entries are summed over the block's pixels at once and leave in one atomic instruction.
+template <bool kGeom, int k>
+__device__ __forceinline__ void render_bwd_block(const BwdArgs& A, Stage& s, uint32_t b, int bx, int by) {
+  const RenderArgs& a = A.r;
+  const int lv = (int)(b / (uint32_t)a.tiles);
+  const int v = a.cams.v0 + lv;
+  const int t = (int)(b % (uint32_t)a.tiles);
+  const DevCam& c = a.cams.c[lv];
+  const int lane = threadIdx.x, part = lane & 3;
+  const int ox = t % a.tiles_x * kTile, oy = t / a.tiles_x * kTile;
+  const int px = ox + bx + ((lane >> 2) & 3), py = oy + by + (lane >> 4);
+  const uint32_t start = a.ranges[(int64_t)v * a.tiles + t], end = a.ranges[(int64_t)v * a.tiles + t + 1];
+  const int64_t vn = (int64_t)v * a.n;
+  float* rgv = A.rg.row + (int64_t)v * a.n * kGradRow;
+  float* rgn = A.rg.nrm + (int64_t)v * a.n * kGradNrm;
+  const float lx0 = (float)(px - ox - 8 * (k & 1)) + 0.5f, ly0 = (float)(py - oy - 8 * (k >> 1)) + 0.5f;
+  BwdState p;  // the same in the pixel's four lanes
+  bwd_init<kGeom>(A, c, v, px, py, start, end, p);
+  uint32_t hi = p.last;
+  for (int off = 4; off < 64; off <<= 1) hi = max(hi, __shfl_xor(hi, off));
+  hi = uniform(hi);
+  const int slot = reduce16_index(lane);
+  const float sc = slot_scale(slot);
+  auto wanted = [&](uint32_t idx, uint32_t top) -> uint32_t {
+    const uint32_t allow = idx < top ? 1u << k : 0u;
+    return allow && a.img.qmask ? a.img.qmask[idx] & allow : allow;
+  };
+  auto below = [&](uint32_t x) { return x - start > 64u ? x - 64u : start; };
+  uint32_t nlo = below(hi), nid, nqm;
+  StageIn in;
+  {
+    const uint32_t idx = nlo + lane, l2 = below(nlo);
+    stage_load(in, a.rec, vn, a.n, idx < hi ? a.ids[idx] : 0u, wanted(idx, hi));
+    nid = l2 + lane < nlo ? a.ids[l2 + lane] : 0u;
+    nqm = wanted(l2 + lane, nlo);
+  }
+  for (uint32_t top = hi; top > start;) {
+    const uint32_t lo = nlo;
+    uint64_t todo = __ballot(stage_put<true>(s, lane, in, ox, oy, !a.img.qmask, bx, by) != 0u);
+    nlo = below(lo);
+    stage_load(in, a.rec, vn, a.n, nid, nqm);
+    const uint32_t l2 = below(nlo);
+    nid = l2 + lane < nlo ? a.ids[l2 + lane] : 0u;
+    nqm = wanted(l2 + lane, nlo);
+    __syncthreads();
+    while (todo != 0) {
+      int at[4];
+      bool has[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        has[q] = todo != 0;
+        at[q] = has[q] ? 63 - __builtin_clzll(todo) : at[0];
+        if (has[q]) todo &= ~(1ull << at[q]);
+      }
+      const int j = part == 0 ? at[0] : part == 1 ? at[1] : part == 2 ? at[2] : at[3];
+      const bool act = part == 0 || (part == 1 ? has[1] : part == 2 ? has[2] : has[3]);
+      const uint32_t e_idx = lo + (uint32_t)j;
+      const float4 q0 = s.q[j][0], q1 = s.q[j][1], q2 = s.q[j][2], q3 = s.q[j][3], q4 = s.q[j][4];
+      LaneTerms lt;
+      lane_terms(lx0, ly0, q0, q1, q2, lt);
+      Px e;
+      eval_px<k>(lt, q2.y, e);
+      const bool con = act && e_idx < p.last && e.alpha >= kAlphaMin;
+      const uint64_t taken = __ballot(con);
+      if (taken == 0) continue;
+      BwdTake u;
+      bwd_take<kGeom>(e, con, q2, q3, q4, p, u);
+      // the transmittance behind each of the four entries, from the last one on
+      const float T1 = p.T * quad_lane<0>(u.rom), T2 = T1 * quad_lane<1>(u.rom), T3 = T2 * quad_lane<2>(u.rom);
+      const float Tn = part == 0 ? p.T : part == 1 ? T1 : part == 2 ? T2 : T3;
+      p.T = T3 * quad_lane<3>(u.rom);
+      const float wgt = Tn * u.ar;
+      const float w0 = quad_lane<0>(wgt), w1 = quad_lane<1>(wgt), w2 = quad_lane<2>(wgt), w3 = quad_lane<3>(wgt);
+      // an entry the pixel does not take leaves the sums as they are
+      auto sums = [&](float& sum, float g) {
+        const float s1 = fmaf(w0, quad_lane<0>(g), sum), s2 = fmaf(w1, quad_lane<1>(g), s1),
+                    s3 = fmaf(w2, quad_lane<2>(g), s2);
+        const float own = part == 0 ? sum : part == 1 ? s1 : part == 2 ? s2 : s3;
+        sum = fmaf(w3, quad_lane<3>(g), s3);
+        return own;
+      };
+      const float sA = sums(p.sA, u.g), sS = sums(p.sS, u.gs);
+      float acc[kGradFields];
+#pragma unroll
+      for (int f = 0; f < kGradFields; ++f) acc[f] = 0.f;
+      bwd_terms<kGeom>(e, u, q0, q1, q2, e_idx, p, wgt, fmaf(-Tn, u.g, sA), fmaf(-Tn, u.gs, sS), acc);
+      float red[16];
+#pragma unroll
+      for (int f = 0; f < 16; ++f) red[f] = acc[f];
+      const float tot = reduce16_scatter_quads(red);
+      const bool any = (taken & (0x1111111111111111ull << part)) != 0;  // some pixel takes this lane's entry
+      const int64_t id = (int64_t)__float_as_uint(q3.w);
+      if (any && (kGeom || slot != G_ZC))
+        atomicAdd(rgv + id * kGradRow + slot, tot * (slot == G_OP ? -0.5f * q4.w : sc));
+      if (kGeom) {
+        const float n0 = sum_quads(acc[G_NX]), n1 = sum_quads(acc[G_NY]), n2 = sum_quads(acc[G_NZ]);
+        if (any && lane < 12)
+          atomicAdd(rgn + id * kGradNrm + (lane >> 2), -0.5f * (lane < 4 ? n0 : lane < 8 ? n1 : n2));
+      }
+    }
+    __syncthreads();
+    top = lo;
+  }
+}
+
 template <bool kGeom>
 __global__ __launch_bounds__(64) void k_render_bwd(BwdArgs A) {
   __shared__ Stage s;
   uint32_t sub;
   const uint32_t b = tile_of_block(A.r, sub);
   if (*A.r.status != 0) return;
+  if (sub & kBlockBit) {
+    const int bx = 4 * (int)(sub & 3u), by = (int)(sub & 12u);
+    switch ((bx >> 3) + 2 * (by >> 3)) {
+      case 0: render_bwd_block<kGeom, 0>(A, s, b, bx, by); break;
+      case 1: render_bwd_block<kGeom, 1>(A, s, b, bx, by); break;
+      case 2: render_bwd_block<kGeom, 2>(A, s, b, bx, by); break;
+      default: render_bwd_block<kGeom, 3>(A, s, b, bx, by); break;
+    }
+    return;
+  }
   switch (sub) {
     case 0x1u: render_bwd_tile<kGeom, 0x1u>(A, s, b); break;
     case 0x2u: render_bwd_tile<kGeom, 0x2u>(A, s, b); break;
@@ -1111,17 +1249,27 @@ static void split_bwd(cgv2::RenderArgs& a, bool geom) {
 }
 
 // Of the quadrant tiles, the heaviest run as blocks while the launch is small: a block tile issues up to twice the
-// instructions of four quadrants, but in sixteen chains a quarter to an eighth as long.  Forward, us, with
-// quadrants and with blocks: 64 tiles 43 -> 26, 260 tiles 65 -> 42 (1 M surfels 264 -> 162, 2 M visible ones 4,370 ->
-// 1,940), 475 tiles 89 -> 66, 1,200 tiles 172 -> 156 and 97 -> 98.  Bins sized for long lists (a mean capacity of
-// kLongLists a tile) have a few tiles many times the mean, whose chains then bound the launch: 1,200 tiles with
-// lists to 32,767 1,850 -> 1,030 with 8,192 waves, 1,853 with 5,120, 1,107 with 10,240.  From 2,048 tiles on the chip
-// is full without: blocks for the heaviest 1/64 cost 1,600x1,066 152 -> 170 and 3,840x2,160 1,116 -> 1,183.
-constexpr int64_t kLongLists = 3000, kBlockWaves = 5120, kBlockWavesLong = 8192;
-static void split_blocks(cgv2::RenderArgs& a, int64_t capacity) {
+// instructions of four quadrants (in the reverse about as many: its reductions take four entries at once), but in
+// sixteen chains a quarter to an eighth as long.  With quadrants -> with blocks, forward / reverse / reverse with
+// geometry terms, us:
+//   64 tiles                             43 -> 26      63 -> 30      79 -> 34
+//   260 tiles                            65 -> 42      98 -> 47     128 -> 58
+//   260 tiles, lists to 67,521         4370 -> 1940  2855 -> 1290  3463 -> 1440
+//   475 tiles                            89 -> 66     130 -> 73     166 -> 98
+//   600 tiles                           100 -> 78     141 -> 88     186 -> 117   (26 % of them: 85, 127, 172)
+//   1,200 tiles (2 % of them)            97 -> 98     148 -> 146    184 -> 181   (all: reverse 133, but another
+//                                                                                scene 157 -> 193)
+//   1,200 tiles, lists to 32,767       1850 -> 1030  1690 -> 784   2100 -> 902   (forward with 282 tiles; 2 % of them:
+//                                                                                1,853; reverse with all, 282: 922, 1209)
+// Bins sized for long lists (a mean capacity of kLongLists a tile) have tiles many times the mean, whose chains then
+// bound the launch, so those take more blocks.  From 2,048 tiles on the chip is full without: blocks for the heaviest
+// 1/64 cost the forward 152 -> 170 at 6,700 tiles and 1,116 -> 1,183 at 32,400, for 1/8 the reverse 297 -> 375.
+constexpr int64_t kLongLists = 3000, kAllBlocks = 640, kBlockWaves = 5120;
+static void split_blocks(cgv2::RenderArgs& a, int64_t capacity, int64_t long_waves) {
   const int64_t all = (int64_t)a.cams.count * a.tiles;
-  const int64_t waves = capacity / std::max<int64_t>(all, 1) >= kLongLists ? kBlockWavesLong : kBlockWaves;
-  a.n_b = (uint32_t)std::min<int64_t>(std::max<int64_t>((waves - 4 * all) / 12, 0), a.n_q);
+  int64_t n = all;
+  if (all > kAllBlocks) n = ((capacity / all >= kLongLists ? long_waves : kBlockWaves) - 4 * all) / 12;
+  a.n_b = (uint32_t)std::min<int64_t>(std::max<int64_t>(n, 0), a.n_q);
   a.n_q -= a.n_b;
 }
 
@@ -1129,7 +1277,7 @@ hipError_t cgv2_launch_render_fwd(const cgv2_proj& p, const cgv2_bins& b, const 
                                   int tiles_x, int tiles_y, const cgv2_image& img, hipStream_t st) {
   cgv2::RenderArgs a = make_args(p, b, cams, n, tiles_x, tiles_y, &img, nullptr);
   split_fwd(a);
-  split_blocks(a, b.capacity);
+  split_blocks(a, b.capacity, 8192);
   const unsigned grid = (unsigned)((int64_t)cams.count * a.tiles + 15 * a.n_b + 3 * a.n_q + a.n_h);
   if (img.qmask && a.n_b + a.n_q + a.n_h)
     hipLaunchKernelGGL(cgv2::k_clear_split_qmask, dim3(a.n_b + a.n_q + a.n_h), dim3(256), 0, st, a);
@@ -1161,7 +1309,8 @@ hipError_t cgv2_launch_render_bwd(const cgv2_proj& p, const cgv2_bins& b, const 
   A.rg = rg;
   const bool geom = up.d_depth || up.d_depth_med || up.d_normal || up.d_alpha;
   split_bwd(A.r, geom);
-  const unsigned grid = (unsigned)((int64_t)cams.count * A.r.tiles + 3 * A.r.n_q + A.r.n_h);
+  split_blocks(A.r, b.capacity, 20480);
+  const unsigned grid = (unsigned)((int64_t)cams.count * A.r.tiles + 15 * A.r.n_b + 3 * A.r.n_q + A.r.n_h);
   if (geom) hipLaunchKernelGGL(cgv2::k_render_bwd<true>, dim3(grid), dim3(64), 0, st, A);
   else hipLaunchKernelGGL(cgv2::k_render_bwd<false>, dim3(grid), dim3(64), 0, st, A);
   return hipGetLastError();

@@ -11,13 +11,13 @@ pytestmark = pytest.mark.gpu
 NAMES = ("rgb", "depth", "depth_med", "normal", "alpha", "T_final", "last", "med")
 
 
-# tiles: one (ragged, and with blocks outside the image), all blocks up to 320, some from 321 to 1,279, and with bins
+# tiles: one (ragged, and with blocks outside the image), all blocks up to 640, some from 641 to 1,279, and with bins
 # sized for long lists up to 2,047; two views in one launch.  Opaque surfels stop pixels within four entries of one
 # another, faint ones fill the lists; a few surfels leave all but one of the four places empty.
 @pytest.mark.parametrize("W,H,views,capacity,n,opacity", [
     (5, 3, 1, 1 << 20, 4000, 2.0), (16, 16, 1, 1 << 20, 3, 0.0), (16, 16, 1, 1 << 20, 70000, -3.0),
     (320, 256, 1, 1 << 20, 6000, 6.0), (1712, 48, 1, 1 << 21, 6000, 0.0), (160, 256, 2, 1 << 20, 5000, -2.0),
-    (640, 510, 1, 1 << 21, 20000, 3.0), (656, 788, 1, 1 << 23, 20000, -1.0)])
+    (640, 256, 1, 1 << 20, 9000, 1.0), (1712, 96, 1, 1 << 20, 9000, 0.0), (640, 510, 1, 1 << 21, 20000, 3.0), (656, 788, 1, 1 << 23, 20000, -1.0)])
 def test_blocks_equal_whole_tiles(cuda, W, H, views, capacity, n, opacity):
     import torch
     from paper_2411_00771_amd import raster
