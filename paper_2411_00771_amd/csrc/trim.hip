@@ -6,7 +6,8 @@
 //   k_contrib_final   C_{n,k} = sum / count (0 for surfels without a blended pixel), the running sum
 //                     over the call's views (fixed order), |P_k|
 //   k_sel_*           exact k-th smallest of a non-negative float array: four 8-bit radix passes over
-//                     the float bits (per-workgroup histograms, one workgroup picks the digit)
+//                     the float bits (workgroup histograms added into a few copies of a global one, one
+//                     workgroup picks the digit and clears them for the next pass)
 //   k_trim_apply      mask = c <= bound, per-workgroup counts, reduced by one workgroup
 #include "cgv2r_device.h"
 #include "cgv2r_kernels.h"
@@ -50,7 +51,9 @@ __global__ __launch_bounds__(256) void k_contrib_final(const uint8_t* __restrict
 }
 
 // selection state: [0] prefix of the bits found so far, [1] mask of those bits, [2] rank still sought
-__global__ void k_sel_init(uint32_t* __restrict__ state, uint32_t k) {
+__global__ __launch_bounds__(256) void k_sel_init(uint32_t* __restrict__ state, uint32_t* __restrict__ hist, int copies,
+                                                  uint32_t k) {
+  for (int c = 0; c < copies; ++c) hist[c * 256 + threadIdx.x] = 0;
   if (threadIdx.x == 0) {
     state[0] = 0;
     state[1] = 0;
@@ -60,7 +63,7 @@ __global__ void k_sel_init(uint32_t* __restrict__ state, uint32_t k) {
 
 __global__ __launch_bounds__(kSelBlock) void k_sel_hist(const float* __restrict__ c, int64_t n,
                                                        const uint32_t* __restrict__ state, int shift,
-                                                       uint32_t* __restrict__ part) {
+                                                       uint32_t* __restrict__ hist, int copies) {
   __shared__ uint32_t h[256];
   h[threadIdx.x] = 0;
   __syncthreads();
@@ -70,58 +73,46 @@ __global__ __launch_bounds__(kSelBlock) void k_sel_hist(const float* __restrict_
     if ((key & mask) == prefix) atomicAdd(&h[(key >> shift) & 255u], 1u);
   }
   __syncthreads();
-  part[(int64_t)blockIdx.x * 256 + threadIdx.x] = h[threadIdx.x];
+  const uint32_t t = h[threadIdx.x];
+  if (t) atomicAdd(&hist[(int)(blockIdx.x % (unsigned)copies) * 256 + (int)threadIdx.x], t);
 }
 
-// One workgroup of kPickThreads: the per-workgroup histograms are summed by kPickThreads / 256 groups
-// of threads with kPickUnroll independent loads in flight each (the sum is latency-bound); a scan over
-// the 256 bins then finds the digit whose count range holds the rank sought.
-constexpr int kPickThreads = 1024;
-constexpr int kPickUnroll = 8;
+// One workgroup: sums and clears the copies; a scan over the 256 bins then finds the digit whose count range holds the
+// rank sought.  Latency bound: with a histogram row of every workgroup to sum (489 at 1 M surfels) it took 19 us,
+// now 4.  Eight copies keep the additions to one bin from one another's way (a same-address atomic takes 13 ns).
+constexpr int kSelCopies = 8;
+constexpr int kPickThreads = 256;
 
-__global__ __launch_bounds__(kPickThreads) void k_sel_pick(const uint32_t* __restrict__ part, int nblocks, int shift,
+__global__ __launch_bounds__(kPickThreads) void k_sel_pick(uint32_t* __restrict__ hist, int copies, int shift,
                                                           uint32_t* __restrict__ state) {
-  constexpr int kGroups = kPickThreads / 256;
-  __shared__ uint32_t tot[kGroups][256];
   __shared__ uint32_t wsum[4];
   const uint32_t k = state[2];  // read by every thread before any write below
-  const int bin = threadIdx.x & 255, grp = threadIdx.x >> 8;
-  uint32_t acc[kPickUnroll] = {};
-  int b = grp;
-  for (; b + (kPickUnroll - 1) * kGroups < nblocks; b += kPickUnroll * kGroups) {
+  uint32_t v[kSelCopies];
 #pragma unroll
-    for (int u = 0; u < kPickUnroll; ++u) acc[u] += part[(int64_t)(b + u * kGroups) * 256 + bin];
+  for (int q = 0; q < kSelCopies; ++q) v[q] = q < copies ? hist[q * 256 + threadIdx.x] : 0u;
+  uint32_t c = 0;
+#pragma unroll
+  for (int q = 0; q < kSelCopies; ++q) {
+    c += v[q];
+    if (q < copies) hist[q * 256 + threadIdx.x] = 0;
   }
-  for (; b < nblocks; b += kGroups) acc[0] += part[(int64_t)b * 256 + bin];
-  uint32_t t = 0;
-#pragma unroll
-  for (int u = 0; u < kPickUnroll; ++u) t += acc[u];
-  tot[grp][bin] = t;
-  __syncthreads();
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  uint32_t c = 0, x = 0;
-  if (threadIdx.x < 256) {
+  uint32_t x = c;
 #pragma unroll
-    for (int g = 0; g < kGroups; ++g) c += tot[g][threadIdx.x];
-    x = c;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-      const uint32_t y = __shfl_up(x, d, 64);
-      if (lane >= d) x += y;
-    }
-    if (lane == 63) wsum[w] = x;
+  for (int d = 1; d < 64; d <<= 1) {
+    const uint32_t y = __shfl_up(x, d, 64);
+    if (lane >= d) x += y;
   }
+  if (lane == 63) wsum[w] = x;
   __syncthreads();
-  if (threadIdx.x < 256) {
-    uint32_t off = 0;
-    for (int q = 0; q < w; ++q) off += wsum[q];
-    const uint32_t incl = off + x, below = incl - c;
-    // digit d: below(d) <= k < below(d) + count(d); the last digit also takes a rank past the total
-    if (below <= k && (k < incl || threadIdx.x == 255)) {
-      state[0] |= (uint32_t)threadIdx.x << shift;
-      state[1] |= 255u << shift;
-      state[2] = k - below;
-    }
+  uint32_t off = 0;
+  for (int q = 0; q < w; ++q) off += wsum[q];
+  const uint32_t incl = off + x, below = incl - c;
+  // digit d: below(d) <= k < below(d) + count(d); the last digit also takes a rank past the total
+  if (below <= k && (k < incl || threadIdx.x == 255)) {
+    state[0] |= (uint32_t)threadIdx.x << shift;
+    state[1] |= 255u << shift;
+    state[2] = k - below;
   }
 }
 
@@ -188,7 +179,7 @@ hipError_t cgv2_launch_contribution_final(const cgv2_proj& p, const cgv2::CamPac
 size_t cgv2_trim_ws_layout(int64_t n, size_t* off) {
   const int64_t nb = std::min<int64_t>(std::max<int64_t>((n + cgv2::kSelBlock * 8 - 1) / (cgv2::kSelBlock * 8), 1),
                                        cgv2::kSelMaxBlocks);
-  // off: [0] selection state (u32 x 4), [1] per-workgroup histograms (u32, nb x 256), [2] counts (u32, nb)
+  // off: [0] selection state (u32 x 4), [1] histograms (u32, room for nb x 256), [2] counts (u32, nb)
   off[0] = 0;
   off[1] = 256;
   off[2] = off[1] + ((4 * 256 * (size_t)nb + 255) & ~(size_t)255);
@@ -202,12 +193,14 @@ hipError_t cgv2_launch_trim(const float* c, int64_t n, uint32_t k, float* bound,
   const int nb = (int)std::min<int64_t>(std::max<int64_t>((n + cgv2::kSelBlock * 8 - 1) / (cgv2::kSelBlock * 8), 1),
                                         cgv2::kSelMaxBlocks);
   uint32_t* state = (uint32_t*)((char*)ws + off[0]);
-  uint32_t* part = (uint32_t*)((char*)ws + off[1]);
+  uint32_t* hist = (uint32_t*)((char*)ws + off[1]);
   uint32_t* cnt = (uint32_t*)((char*)ws + off[2]);
-  hipLaunchKernelGGL(cgv2::k_sel_init, dim3(1), dim3(64), 0, st, state, k);
+  const int copies = std::min(cgv2::kSelCopies, nb);
+  hipLaunchKernelGGL(cgv2::k_sel_init, dim3(1), dim3(256), 0, st, state, hist, copies, k);
   for (int shift = 24; shift >= 0; shift -= 8) {
-    hipLaunchKernelGGL(cgv2::k_sel_hist, dim3((unsigned)nb), dim3(cgv2::kSelBlock), 0, st, c, n, state, shift, part);
-    hipLaunchKernelGGL(cgv2::k_sel_pick, dim3(1), dim3(cgv2::kPickThreads), 0, st, part, nb, shift, state);
+    hipLaunchKernelGGL(cgv2::k_sel_hist, dim3((unsigned)nb), dim3(cgv2::kSelBlock), 0, st, c, n, state, shift, hist,
+                       copies);
+    hipLaunchKernelGGL(cgv2::k_sel_pick, dim3(1), dim3(cgv2::kPickThreads), 0, st, hist, copies, shift, state);
   }
   hipLaunchKernelGGL(cgv2::k_trim_apply, dim3((unsigned)nb), dim3(cgv2::kSelBlock), 0, st, c, n, state, mask, cnt);
   hipLaunchKernelGGL(cgv2::k_trim_count, dim3(1), dim3(cgv2::kSelBlock), 0, st, cnt, nb, state, bound, removed);
