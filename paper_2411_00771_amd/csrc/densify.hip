@@ -4,7 +4,7 @@
 // k_dgd_partial  per view, per block of 1,024 surfels: sums of |g_total| and |g_ssim| over the
 //                visible surfels, tree-reduced in FP64 in a fixed order
 // k_dgd_final    one workgroup per view reduces its block partials in a fixed order into
-//                scale_v = max(omega a_tot / a_ssim, 1) (deterministic)
+//                scale_v = max(omega a_tot / a_ssim, 1) (deterministic); few surfels: done by k_densify
 // k_densify      updates the per-surfel state and the masks; per-workgroup counter partials
 // k_count_final  one workgroup adds the partials to the counters (no same-address atomics)
 #include <atomic>
@@ -78,6 +78,11 @@ __global__ __launch_bounds__(kDBlock) void k_dgd_partial(const uint8_t* __restri
   if (blockIdx.x == 0 && v == 0 && threadIdx.x < 8) counters[threadIdx.x] = 0;
 }
 
+// The Eq. 2 factor of a view from its sums of |g_total| and |g_ssim|.
+__device__ __forceinline__ float view_scale(double total, double ssim, float omega) {
+  return (float)(ssim > 0 ? fmax((double)omega * total / ssim, 1.0) : 1.0);
+}
+
 // Latency bound: one workgroup per view, eight loads in flight (10 M surfels, 8 views: 240 us for all views in one
 // workgroup, 6 now).
 __global__ __launch_bounds__(kDBlock) void k_dgd_final(const double* __restrict__ partial, int nblocks, float omega,
@@ -102,8 +107,7 @@ __global__ __launch_bounds__(kDBlock) void k_dgd_final(const double* __restrict_
     __syncthreads();
   }
   if (threadIdx.x == 0) {
-    const double at = red[0][0], as = red[1][0];
-    const float sc = (float)(as > 0 ? fmax((double)omega * at / as, 1.0) : 1.0);
+    const float sc = view_scale(red[0][0], red[1][0], omega);
     scale_ws[v] = sc;
     if (scale_out) scale_out[v] = sc;
   }
@@ -118,12 +122,36 @@ struct DCounts {
 // Bound by the state's arrays and the sectors of the planar gradients of the visible surfels; the next view's flag
 // is in flight during a view, the counters come from ballots.  10 M surfels, 8 views: 395 us -> 333; 1 M, one view:
 // 10.1 -> 11.  More views' loads grouped cost registers and occupancy (two views 323 and 12.5, eight 436 and 22).
+// kFew: a set of at most kFewBlocks workgroups skips the two one-workgroup kernels around this one: every workgroup
+// sums the views' few partials itself (thread v for view v, in block order) and adds its counters to the global ones.
+// Launch bound, us of the call: 4,000 surfels 26 -> 17, 8,000 in 8 views 37 -> 20, 32,000 23 -> 21 (in 8 views 26 -> 23);
+// beyond, the partials' sums and the same-line atomics (4 ns each) cost what the launches do.
+constexpr int kFewBlocks = 128;
+constexpr int kMaxDViews = 64;  // views of a call (the entry points refuse more)
+
+template <bool kFew>
 __global__ __launch_bounds__(kDBlock) void k_densify(cgv2_surfels s, const uint8_t* __restrict__ flags,
                                                      const float* __restrict__ radius, const float* __restrict__ gt,
                                                      const float* __restrict__ gs, int V,
-                                                     const float* __restrict__ scale_ws, cgv2_densify_params prm,
-                                                     cgv2_densify_state st, uint32_t* __restrict__ cpart) {
+                                                     const float* __restrict__ scale_ws,
+                                                     const double* __restrict__ partial, int nbp,
+                                                     cgv2_densify_params prm, cgv2_densify_state st,
+                                                     uint32_t* __restrict__ cpart) {
   __shared__ DCounts cnt_s[kDBlock / 64];
+  __shared__ float scale_s[kFew ? kMaxDViews : 1];
+  if constexpr (kFew) {
+    const int v = threadIdx.x;
+    if (v < V) {
+      double at = 0, as = 0;
+      for (int k = 0; k < nbp; ++k) {
+        at += partial[2 * (v * nbp + k)];
+        as += partial[2 * (v * nbp + k) + 1];
+      }
+      scale_s[v] = view_scale(at, as, prm.omega);
+      if (blockIdx.x == 0 && st.scale) st.scale[v] = scale_s[v];
+    }
+    __syncthreads();
+  }
   const int64_t n = s.n;
   DCounts c = {0, 0, 0, 0, 0, 0};
   const int64_t i = (int64_t)blockIdx.x * kDBlock + threadIdx.x;
@@ -146,7 +174,7 @@ __global__ __launch_bounds__(kDBlock) void k_densify(cgv2_surfels s, const uint8
         const float* g2 = gs + (int64_t)v * 2 * n;
         ns = sqrtf(g2[i] * g2[i] + g2[n + i] * g2[n + i]);
       }
-      adgd = fmaf(scale_ws[v], ns, adgd);
+      adgd = fmaf(kFew ? scale_s[v] : scale_ws[v], ns, adgd);
       atot += nt;
       den += 1;
       mr = fmaxf(mr, radius[vi]);
@@ -181,7 +209,11 @@ __global__ __launch_bounds__(kDBlock) void k_densify(cgv2_surfels s, const uint8
     uint32_t t = 0;
 #pragma unroll
     for (int w = 0; w < kDBlock / 64; ++w) t += ((const uint32_t*)&cnt_s[w])[threadIdx.x];
-    cpart[(int64_t)blockIdx.x * kCounters + threadIdx.x] = t;
+    if (kFew) {
+      if (t) atomicAdd(&st.counters[threadIdx.x], t);
+    } else {
+      cpart[(int64_t)blockIdx.x * kCounters + threadIdx.x] = t;
+    }
   }
 }
 
@@ -236,12 +268,17 @@ hipError_t cgv2_launch_densify(const cgv2_surfels& s, const cgv2_proj& p, const 
   uint32_t* cpart = (uint32_t*)((char*)ws + off[1]);
   hipLaunchKernelGGL(cgv2::k_dgd_partial, dim3((unsigned)nbp, (unsigned)V), dim3(cgv2::kDBlock), 0, stream, p.flags,
                      g.g_view_total, g.g_view_ssim, n, partial, nbp, st.counters);
+  const int nbd = (int)((n + cgv2::kDBlock - 1) / cgv2::kDBlock);
+  if (n > 0 && nbd <= cgv2::kFewBlocks) {
+    hipLaunchKernelGGL(cgv2::k_densify<true>, dim3((unsigned)nbd), dim3(cgv2::kDBlock), 0, stream, s, p.flags, p.radius,
+                       g.g_view_total, g.g_view_ssim, V, scale_ws, partial, nbp, prm, st, cpart);
+    return hipGetLastError();
+  }
   hipLaunchKernelGGL(cgv2::k_dgd_final, dim3((unsigned)V), dim3(cgv2::kDBlock), 0, stream, partial, nbp, prm.omega,
                      scale_ws, st.scale);
   if (n > 0) {
-    const int nbd = (int)((n + cgv2::kDBlock - 1) / cgv2::kDBlock);
-    hipLaunchKernelGGL(cgv2::k_densify, dim3((unsigned)nbd), dim3(cgv2::kDBlock), 0, stream, s, p.flags, p.radius,
-                       g.g_view_total, g.g_view_ssim, V, scale_ws, prm, st, cpart);
+    hipLaunchKernelGGL(cgv2::k_densify<false>, dim3((unsigned)nbd), dim3(cgv2::kDBlock), 0, stream, s, p.flags,
+                       p.radius, g.g_view_total, g.g_view_ssim, V, scale_ws, partial, nbp, prm, st, cpart);
     hipLaunchKernelGGL(cgv2::k_count_final, dim3(1), dim3(cgv2::kCBlock), 0, stream, cpart, nbd, st.counters);
   }
   return hipGetLastError();

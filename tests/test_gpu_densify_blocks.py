@@ -1,4 +1,5 @@
-"""The view sums and counters of the densification statistics at the edges of their blocks (1,024 surfels a sum)."""
+"""The view sums and counters of the densification statistics at the edges of their blocks (1,024 surfels a sum) and of
+the short form (up to 32,768 surfels)."""
 import numpy as np
 import pytest
 
@@ -7,7 +8,8 @@ import oracle
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("n,V,density", [(1, 1, 1.0), (63, 2, 0.5), (1023, 1, 0.9), (1024, 3, 0.1), (1025, 2, 1.0),
+@pytest.mark.parametrize("n,V,density", [(1, 1, 1.0), (63, 2, 0.5), (1023, 1, 0.9), (1024, 3, 0.1),
+                                         (1025, 2, 1.0), (100, 64, 0.5), (32_768, 3, 0.2), (32_769, 2, 0.2),
                                          (1_050_000, 2, 0.04)])
 def test_block_edges_match_oracle(cuda, n, V, density):
     import torch
