@@ -356,9 +356,11 @@ constexpr uint32_t kChunkTiles = 4 * kGroup;
 constexpr uint32_t kFirstTiles = CGV2_FIRST_CHUNKS * kChunkTiles;
 // Atomics on one address complete every 13 ns, whichever XCD they come from: a tile of 32,767 entries (the
 // horizon of a 640x480 view of 5 M surfels) alone takes 0.43 ms.  Launches of few tiles, whose lists can be
-// that long, count into kSets counters per tile (workgroup b into set b % kSets).
+// that long, count into kSets counters per tile (workgroup b into set b % kSets), where the bins have room for
+// lists that can queue on one counter (kSetsSlots slots a tile: 0.8 us).
 constexpr int kSets = 8;
 constexpr int64_t kSetsMaxTiles = 4096;
+constexpr int64_t kSetsSlots = 64;
 
 // Small-rect runs pack a surfel's index within its run into the top 8 bits of an entry's rank (a tile lists
 // each of a view's n surfels at most once).
@@ -1151,10 +1153,17 @@ __global__ __launch_bounds__(kScanBlock) void k_tile_scan_order(uint32_t* __rest
 static int64_t scan_blocks(int64_t m) { return (m + cgv2::kScanChunk - 1) / cgv2::kScanChunk; }
 static int64_t surf_blocks(int64_t m) { return (m + cgv2::kSurfChunk - 1) / cgv2::kSurfChunk; }
 
-static int counter_sets(int64_t m) { return m <= cgv2::kSetsMaxTiles ? cgv2::kSets : 1; }
+static int counter_sets(int64_t m, int64_t capacity) {
+  return m <= cgv2::kSetsMaxTiles && capacity >= cgv2::kSetsSlots * m ? cgv2::kSets : 1;
+}
+// Counters that the workspace holds: of m tiles, and of any fewer (a workspace sized for an engine's largest image
+// serves its smaller ones too).
+static int64_t counter_room(int64_t m, int64_t capacity) {
+  return std::max(m, cgv2::kSets * std::min(std::min(m, cgv2::kSetsMaxTiles), capacity / cgv2::kSetsSlots));
+}
 
 size_t cgv2_binsort_ws_layout(int64_t capacity, int V, int tiles, int64_t n, size_t* off) {
-  // off: [0] tile counters (u32, m, kSets times for few tiles) followed by the sort-item and chunk-queue
+  // off: [0] tile counters (u32, counter_room) and, after those in use, the sort-item and chunk-queue
   //      counts, [1] chunk sums of the surfel scan (2 x u64 arrays), [2] chunks of the long lists (uint2), [3] scan totals
   //      (u64 x 2), [4] keys (u64, capacity), [5] staged entries (8 B, capacity), [6], [7], [11] per visible entry: staged count (u16), first slot (u32, capacity), depth (f32),
   //      [8] chunk sums of the tile scan (u64)
@@ -1164,13 +1173,14 @@ size_t cgv2_binsort_ws_layout(int64_t capacity, int V, int tiles, int64_t n, siz
   const int64_t vis = std::min(vn, capacity);  // most visible surfels that are staged
   size_t o = 0;
   auto take = [&](size_t bytes) { size_t r = o; o += (bytes + 255) & ~(size_t)255; return r; };
-  off[0] = take(4 * (size_t)(m * counter_sets(m) + 2));
+  off[0] = take(4 * (size_t)(counter_room(m, capacity) + 2));
   off[1] = take(16 * (size_t)(nsb + 1));
   off[2] = take(8 * (size_t)(capacity / (cgv2::kWaveSort / 2) + 1));
   off[3] = take(64);
   off[4] = take(8 * (size_t)capacity);
   off[5] = take(8 * (size_t)capacity);
-  off[6] = take(2 * (size_t)vis);
+  off[11] = take(6 * (size_t)vis);
+  off[6] = off[11] + 4 * (size_t)vis;
   off[7] = take(4 * (size_t)(capacity + 1));
   off[8] = take(8 * (size_t)(scan_blocks(m) + 1));
   // [9] per-chunk bucket counts of the launch order (one view chunk at a time)
@@ -1178,7 +1188,6 @@ size_t cgv2_binsort_ws_layout(int64_t capacity, int V, int tiles, int64_t n, siz
   off[9] = take(4 * (size_t)cgv2::kOrdBuckets * (size_t)((per + cgv2::kOrdChunk - 1) / cgv2::kOrdChunk + 1));
   // [10] the chunk queue of the large rects (see k_stage)
   off[10] = take(16 * (size_t)(capacity / cgv2::kChunkTiles + 1));
-  off[11] = take(4 * (size_t)vis);
   return o;
 }
 
@@ -1188,7 +1197,7 @@ hipError_t cgv2_launch_bin_sort(const cgv2_proj& p, int64_t n, int V, int tiles_
   const int tiles = tiles_x * tiles_y;
   const int64_t m = (int64_t)V * tiles;
   const int64_t vn = (int64_t)V * n;
-  const int sets = counter_sets(m);
+  const int sets = counter_sets(m, b.capacity);
   size_t off[kBinsortOffs];
   cgv2_binsort_ws_layout(b.capacity, V, tiles, n, off);
   char* w = (char*)ws;
