@@ -356,12 +356,13 @@ __device__ __noinline__ void loss_final(const double* __restrict__ partial, int6
 // strip alone (forward and reverse: 82 output rows, one strip per SIMD, 96 us at 1600x1066; 40 rows, two, 71;
 // 27 rows, three, 78; 45 rows, as before, 1.8 per SIMD, 80).  The cheapest height is taken, the largest of
 // equals (fewer halo rows read); small images take short strips (128x128: 50 -> 23 us).
+constexpr int kMinRows = 4;
 static cgv2::StripGrid strip_grid(int W, int H, int V) {
   constexpr int64_t kSimds = 1024;
   cgv2::StripGrid g;
   g.nx = (W + cgv2::kStripW - 1) / cgv2::kStripW;
   int64_t best = INT64_MAX;
-  for (int rows = 4; rows <= 128; ++rows) {
+  for (int rows = kMinRows; rows <= 128; ++rows) {
     const int ny = (H + rows - 1) / rows;
     const int64_t strips = (int64_t)g.nx * ny * 3 * V;
     const int64_t per = (strips + kSimds - 1) / kSimds;
@@ -375,11 +376,12 @@ static cgv2::StripGrid strip_grid(int W, int H, int V) {
 }
 
 size_t cgv2_loss_ws_layout(int W, int H, int V, size_t* off) {
-  const cgv2::StripGrid g = strip_grid(W, H, V);
+  // room for the most strips: a workspace sized for a larger image, whose strips may be taller, serves this one too
+  const int64_t nx = (W + cgv2::kStripW - 1) / cgv2::kStripW, ny = ((int64_t)H + kMinRows - 1) / kMinRows;
   size_t o = 0;
   auto take = [&](size_t bytes) { size_t r = o; o += (bytes + 255) & ~(size_t)255; return r; };
   off[0] = take(sizeof(float) * 9 * (size_t)W * H * V);     // partial maps [V][3][3][H][W]
-  off[1] = take(sizeof(double) * 2 * (size_t)((int64_t)g.nx * g.ny * 3 * V));  // per-wave sums
+  off[1] = take(sizeof(double) * 2 * (size_t)(nx * ny * 3 * V));  // per-wave sums
   return o;
 }
 

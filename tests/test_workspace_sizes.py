@@ -27,6 +27,15 @@ def test_bin_sort_workspace_random_pairs():
         assert need(capacity, v, fewer, 1000) <= need(capacity, v, tiles, 1000), (capacity, v, fewer, tiles)
 
 
+def test_loss_workspace_random_pairs():
+    need = _lib.lib().cgv2_loss_workspace
+    rng = random.Random(6)
+    for _ in range(60000):
+        w, h, v = int(2 ** rng.uniform(0, 12)), int(2 ** rng.uniform(0, 12)), rng.randrange(1, 9)
+        w2, h2, v2 = (max(1, x - rng.randrange(4)) for x in (w, h, v))
+        assert need(w2, h2, v2) <= need(w, h, v), (w, h, v, w2, h2, v2)
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("width,height", [(640, 480), (1024, 1008), (64, 48)])
 def test_smaller_image_on_a_larger_engine(cuda, width, height):
