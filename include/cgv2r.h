@@ -131,7 +131,9 @@ typedef struct {
  * ranges[v*tiles + t + 1]), ordered front to back by (float32 bits of z_c, id).  A surfel is listed in
  * the tiles of its rect where its alpha >= 1/255 region can reach a pixel sample: some point of the
  * tile's pixel-sample box, padded by 1/64 px, has min(rho_3d, rho_2d) <= k^2 (1 + 2e-3) + 2e-3 (every
- * pixel that can blend the surfel keeps it; Sec. 3.1 cutoff).
+ * pixel that can blend the surfel keeps it; Sec. 3.1 cutoff).  A surfel whose cutoff conic is no ellipse, or one
+ * too thin for a float32 evaluation (determinant of its quadratic part at most 1e-11 of the diagonal's product),
+ * is listed in every tile of its rect.
  * The staging holds one slot per tile of every rect: 'capacity' and *needed count those slots.
  * *status is set to 1 when they exceed 'capacity' (sticky: the library never clears it; the caller
  * zeroes it before the first call).  *needed receives the total number of rect slots of the call.

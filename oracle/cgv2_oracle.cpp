@@ -434,7 +434,7 @@ void cross(const double* a, const double* b, double* c) {
 }
 
 // x in [xl, xh], y in [yl, yh], centre-relative
-bool tile_reached(const double* M, double K, double xl, double xh, double yl, double yh) {
+bool tile_reached(const double* M, double K, double xl, double xh, double yl, double yh, double thin) {
   // screen-filter branch: rho2d = 2 |x - c|^2
   const double dx = xl > 0 ? xl : (xh < 0 ? xh : 0.0), dy = yl > 0 ? yl : (yh < 0 ? yh : 0.0);
   if (2 * (dx * dx + dy * dy) <= K) return true;
@@ -450,7 +450,7 @@ bool tile_reached(const double* M, double K, double xl, double xh, double yl, do
   const double Q00 = dot(c1, c1), Q01 = dot(c1, c2), Q11 = dot(c2, c2);
   const double B0 = dot(c1, pc), B1 = dot(c2, pc), D = dot(pc, pc);
   const double det = Q00 * Q11 - Q01 * Q01;
-  if (!(Q00 > 0 && Q11 > 0 && det > 0)) return true;
+  if (!(Q00 > 0 && Q11 > 0 && det > thin * Q00 * Q11)) return true;
   const double xs = -(Q11 * B0 - Q01 * B1) / det, ys = -(Q00 * B1 - Q01 * B0) / det;
   if (xs >= xl && xs <= xh && ys >= yl && ys <= yh) return true;
   auto q = [&](double x, double y) { return Q00 * x * x + 2 * Q01 * x * y + Q11 * y * y + 2 * B0 * x + 2 * B1 * y + D; };
@@ -461,12 +461,12 @@ bool tile_reached(const double* M, double K, double xl, double xh, double yl, do
   return best <= 0;
 }
 
-bool tile_reach_at(const double* M, double k2, int tx, int ty, double Kscale, double pad) {
+bool tile_reach_at(const double* M, double k2, int tx, int ty, double Kscale, double pad, double thin) {
   const double K = (k2 * (1 + 2e-3) + 2e-3) * Kscale;
   const double cx = M[2] / M[8], cy = M[5] / M[8];
   const double xl = kTile * tx + 0.5 - pad - cx, xh = kTile * tx + kTile - 0.5 + pad - cx;
   const double yl = kTile * ty + 0.5 - pad - cy, yh = kTile * ty + kTile - 0.5 + pad - cy;
-  return tile_reached(M, K, xl, xh, yl, yh);
+  return tile_reached(M, K, xl, xh, yl, yh, thin);
 }
 
 }  // namespace
@@ -562,9 +562,12 @@ int orc_project(int64_t n, int deg, const double* mean, const double* log_scale,
 //                    definite the set is an ellipse and q is convex: it meets the box iff its minimiser
 //                    lies in the box or q <= 0 at the minimum along one of the four edges.  Otherwise
 //                    (the cutoff ellipse on the surfel's plane reaches the camera plane) every tile of
-//                    the rect is kept.
+//                    the rect is kept, and likewise where the determinant of the quadratic part is at most
+//                    1e-11 of its diagonal's product (a long thin surfel seen edge-on: the FP32 evaluation
+//                    moves the ends of such an ellipse by more than the enlargement).
 // keep[j] / fragile[j] for the rect tiles of the visible surfels in order (surfel, then tile rows);
-// fragile marks decisions that change between K (1 -+ 1e-5) with the pad -+ 1e-3 px.
+// fragile marks decisions that change between K (1 -+ 1e-5) with the pad -+ 1e-3 px and the limit of thinness
+// 1e-11 halved and doubled (FP32 coefficients hold the determinant there to about a tenth).
 // ------------------------------------------------------------------------------------------
 
 int64_t orc_tile_reach(int64_t n, const double* M, const double* k2, const int32_t* tile_rect, uint8_t* keep,
@@ -575,17 +578,17 @@ int64_t orc_tile_reach(int64_t n, const double* M, const double* k2, const int32
     start[i + 1] = start[i] + (int64_t)std::max(0, r[2] - r[0]) * std::max(0, r[3] - r[1]);
   }
   if (!keep) return start[n];
-  const double pad = 1.0 / 64.0;
+  const double pad = 1.0 / 64.0, thin = 1e-11;
 #pragma omp parallel for schedule(dynamic, 256)
   for (int64_t i = 0; i < n; ++i) {
     const int32_t* r = tile_rect + 4 * i;
     int64_t j = start[i];
     for (int y = r[1]; y < r[3]; ++y)
       for (int x = r[0]; x < r[2]; ++x, ++j) {
-        keep[j] = tile_reach_at(M + 9 * i, k2[i], x, y, 1.0, pad);
+        keep[j] = tile_reach_at(M + 9 * i, k2[i], x, y, 1.0, pad, thin);
         if (fragile)
-          fragile[j] = tile_reach_at(M + 9 * i, k2[i], x, y, 1 + 1e-5, pad + 1e-3) !=
-                       tile_reach_at(M + 9 * i, k2[i], x, y, 1 - 1e-5, pad - 1e-3);
+          fragile[j] = tile_reach_at(M + 9 * i, k2[i], x, y, 1 + 1e-5, pad + 1e-3, 2 * thin) !=
+                       tile_reach_at(M + 9 * i, k2[i], x, y, 1 - 1e-5, pad - 1e-3, 0.5 * thin);
       }
   }
   return start[n];
