@@ -27,8 +27,8 @@ constexpr int kTaps = 2 * kR + 1;       // 11
 constexpr int kStripW = 64;             // output columns per wave (one per lane)
 constexpr int kRowW = kStripW + 2 * kR;
 constexpr float kC1 = 0.0001f, kC2 = 0.0009f;
-// The moments are taken about mid-grey: the variances do not change, and less cancels in them (the gradient's
-// error against float64 on images in [0, 1] is 3.5e-5, about zero 9.5e-5).
+// The moments of a strip are taken about mid-grey or about zero, whichever is nearer to the middle of its values:
+// the variances do not change, and least cancels in them (see strip_mid).
 constexpr float kMid = 0.5f;
 
 struct Win { float g[kTaps]; };
@@ -99,12 +99,48 @@ __device__ __forceinline__ void vsum(const float (&ring)[kTaps][N], const Win& w
   }
 }
 
+// The value that the strip's moments are taken about, from both images at four rows spread over its output rows.
+// What cancels grows with the square of the distance of the values from it.  Relative error of the SSIM gradient
+// against float64 on smooth images in [0, 1] / [0.45, 0.55] / [0, 0.2] / [0, 0.004] and a photograph-like one: about
+// mid-grey 3.3e-6 / 2.0e-5 / 1.3e-5 / 3.7e-5 and 3.6e-5, about zero 1.1e-5 / 2.8e-5 / 2.0e-6 / 3.1e-7 and 9.0e-5,
+// chosen per strip the smaller of the two in each.
+struct StripSample {
+  float x[4], y[4];
+};
+
+__device__ __forceinline__ void sample_load(StripSample& q, __amdgpu_buffer_rsrc_t rx, __amdgpu_buffer_rsrc_t ry,
+                                            int W, int H, int x0, int y0, int rows, int lane) {
+  const int col = min(x0 + lane, W - 1), last = min(rows, H - y0) - 1;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const uint32_t off = (uint32_t)((int64_t)(y0 + last * k / 3) * W + col) * 4u;
+    q.x[k] = load_or_zero(rx, off);
+    q.y[k] = load_or_zero(ry, off);
+  }
+}
+
+__device__ __forceinline__ float strip_mid(const StripSample& q) {
+  float lo = INFINITY, hi = -INFINITY;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    lo = fminf(lo, fminf(q.x[k], q.y[k]));
+    hi = fmaxf(hi, fmaxf(q.x[k], q.y[k]));
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    lo = fminf(lo, __shfl_xor(lo, o, 64));
+    hi = fmaxf(hi, __shfl_xor(hi, o, 64));
+  }
+  return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(lo + hi < kMid ? 0.f : kMid)));
+}
+
 // Rows are loaded kTaps ahead of their use: the queue slot of a row is then its ring slot (row % 11), fixed at
 // every position of the unrolled loop.  (Two rows ahead: a wave alone on its SIMD waits on every row.)
 struct FwdStrip {
   __amdgpu_buffer_rsrc_t rx, ry, rm;
   int W, H, x0, y0, lane, rows;  // rows: input rows of the strip
   int64_t HW;
+  float mid;                                         // of the moments
   float xa[kTaps], xb[kTaps], ya[kTaps], yb[kTaps];  // the next rows' own and halo columns
   float ring[kTaps][4];                              // horizontal sums of the last 11 input rows
   double m_sum, l1_sum;
@@ -125,12 +161,18 @@ __device__ __forceinline__ void fwd_load(FwdStrip& f, int rn) {
 template <int J>
 __device__ __forceinline__ void fwd_step(FwdStrip& f, float4* s, const Win& win, int r) {
   wave_lds_order();  // the previous row is no longer read
-  const float x = f.xa[J] - kMid, y = f.ya[J] - kMid;
+  const float x = f.xa[J] - f.mid, y = f.ya[J] - f.mid;
   s[f.lane] = make_float4(x, y, fmaf(x, x, y * y), x * y);
   if (f.lane < 2 * kR) {
-    const float u = f.xb[J] - kMid, v = f.yb[J] - kMid;
+    const float u = f.xb[J] - f.mid, v = f.yb[J] - f.mid;
     s[kStripW + f.lane] = make_float4(u, v, fmaf(u, u, v * v), u * v);
   }
+  // L1 of the row where it is one of the strip's outputs, from the raw values: lanes 5 to 63 loaded columns x0 to
+  // x0 + 58 with their own, lanes 0 to 4 the other five with the halo (both images read 0 outside)
+  float l1 = f.xa[J] - f.ya[J];
+  if (f.lane < kR) l1 = f.xb[J] - f.yb[J];
+  asm volatile("" : "+v"(l1));  // taken here: left to the scheduler, the kernel needs 184 registers instead of 162
+  f.l1_sum += r >= kR && r < f.rows - kR ? (double)fabsf(l1) : 0.0;
   wave_lds_order();
   fwd_load<J>(f, r + kTaps);  // the slot is free again
   float m0 = 0, m1 = 0, m2 = 0, m3 = 0;
@@ -142,16 +184,12 @@ __device__ __forceinline__ void fwd_step(FwdStrip& f, float4* s, const Win& win,
     m1 = fmaf(g, q.y, m1);
     m2 = fmaf(g, q.z, m2);
     m3 = fmaf(g, q.w, m3);
-    if (a == kR) {  // the lane's own column: its L1 term, where the row is one of the strip's outputs
-      const bool own = f.x0 + f.lane < f.W && r >= kR && r < f.rows - kR;
-      f.l1_sum += own ? (double)fabsf(q.x - q.y) : 0.0;
-    }
   }
   f.ring[J][0] = m0; f.ring[J][1] = m1; f.ring[J][2] = m2; f.ring[J][3] = m3;
   if (r < 2 * kR) return;
   float v[4];
   vsum<4, J>(f.ring, win, v);
-  const float sx = v[0], sy = v[1], mx = sx + kMid, my = sy + kMid;  // the means, shifted and true
+  const float sx = v[0], sy = v[1], mx = sx + f.mid, my = sy + f.mid;  // the means, shifted and true
   const int px = f.x0 + f.lane, py = f.y0 + r - 2 * kR;
   const bool in = px < f.W && py < f.H;
   const float A1 = fmaf(2.f * mx, my, kC1), A2 = fmaf(2.f, fmaf(-sx, sy, v[3]), kC2);
@@ -203,7 +241,10 @@ __global__ __launch_bounds__(64) void k_ssim_fwd(const float* __restrict__ img, 
   f.ry = plane_rsrc(tgt + vc * f.HW, f.HW);
   f.rm = plane_rsrc(maps + (int64_t)vc * 3 * f.HW, 3 * f.HW);
   f.m_sum = f.l1_sum = 0.0;
+  StripSample q;
+  sample_load(q, f.rx, f.ry, W, H, f.x0, f.y0, sg.rows, f.lane);
   fwd_fill<0>(f);
+  f.mid = strip_mid(q);
   fwd_rows(f, s, win);
   // per-wave sums in FP64, fixed order (butterfly)
   double m_sum = f.m_sum, l1_sum = f.l1_sum;
