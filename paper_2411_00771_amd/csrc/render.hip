@@ -38,42 +38,66 @@ struct RenderArgs {
   float* cws;   // contribution mode: [V][n] pairs (sum of alpha^gamma T^(1-gamma), pixel count)
   float gamma;
   const uint32_t* order;  // launch order of this view chunk (heaviest tiles first), or null
-  // the first n_b tiles of 'order' run as sixteen 4x4 blocks (none in the counting and contribution passes), the
-  // next n_q as four quadrant blocks, the next n_h as two halves
-  uint32_t n_b, n_q, n_h;
+  // the first n_b tiles of 'order' run as sixteen 4x4 blocks, the next n_m as sixteen blocks where the tile is long and
+  // as four quadrant blocks elsewhere (neither in the counting and contribution passes), the next n_q as four quadrant
+  // blocks, the next n_h as two halves
+  uint32_t n_b, n_m, n_q, n_h;
 };
 
 // Block -> (local view, tile) index and quadrant subset.  Without a launch order: the XCD-aware spatial
 // mapping, whole tiles.  With one (the bin_sort's heaviest-first order; bounded, so a stale order cannot
 // leave the launch), the n_b heaviest tiles run as sixteen blocks each (bit kBlockBit of sub, the block's
-// row-major number below it), the next n_q as four single-quadrant blocks, the next n_h as two halves
-// (top 0x3, bottom 0xc), the rest whole; the launch has 15 n_b + 3 n_q + n_h blocks more than tiles.
-constexpr uint32_t kBlockBit = 16u;
+// row-major number below it), the next n_m likewise with kMaybeBit (only the first four here), the next n_q as four
+// single-quadrant blocks, the next n_h as two halves (top 0x3, bottom 0xc), the rest whole; then come the other
+// twelve of each of the n_m, where the launch's work hides their dispatch if they find nothing to do.  The launch has
+// 15 n_b + 15 n_m + 3 n_q + n_h blocks more than tiles.
+constexpr uint32_t kBlockBit = 16u, kMaybeBit = 32u;
+constexpr uint32_t kLongFwd = 512, kLongFwdHalves = 5, kLongBwd = 256;  // see split_blocks
 __device__ __forceinline__ uint32_t tile_of_block(const RenderArgs& a, uint32_t& sub) {
-  const uint32_t tiles = gridDim.x - 15u * a.n_b - 3u * a.n_q - a.n_h;
+  const uint32_t tiles = gridDim.x - 15u * (a.n_b + a.n_m) - 3u * a.n_q - a.n_h;
   uint32_t bid = blockIdx.x;
   sub = 0xfu;
   if (!a.order) return xcd_remap(bid, tiles);
+  const uint32_t late = gridDim.x - 12u * a.n_m;
   uint32_t i;
   if (bid < 16u * a.n_b) {
     i = bid >> 4;
     sub = kBlockBit | (bid & 15u);
+  } else if (bid >= late) {
+    bid -= late;
+    const uint32_t k = bid / 12u;
+    i = a.n_b + k;
+    sub = kMaybeBit | kBlockBit | (4u + bid - 12u * k);
   } else {
     bid -= 16u * a.n_b;
-    if (bid < 4u * a.n_q) {
+    const uint32_t n4 = 4u * (a.n_m + a.n_q);
+    if (bid < n4) {
       i = bid >> 2;
-      sub = 1u << (bid & 3u);
-    } else if (bid < 4u * a.n_q + 2u * a.n_h) {
-      const uint32_t r = bid - 4u * a.n_q;
-      i = a.n_q + (r >> 1);
+      sub = i < a.n_m ? kMaybeBit | kBlockBit | (bid & 3u) : 1u << (bid & 3u);
+    } else if (bid < n4 + 2u * a.n_h) {
+      const uint32_t r = bid - n4;
+      i = a.n_m + a.n_q + (r >> 1);
       sub = (r & 1u) ? 0xcu : 0x3u;
     } else {
-      i = bid - 3u * a.n_q - a.n_h;
+      i = bid - 3u * (a.n_m + a.n_q) - a.n_h;
     }
     i += a.n_b;
   }
   const uint32_t b = a.order[i];
   return b < tiles ? b : tiles - 1u;
+}
+
+// Is tile b's list long: at least 'least' entries and 'halves' / 2 times the mean of the launch?
+__device__ __forceinline__ bool long_list(const RenderArgs& a, uint32_t b, uint32_t least, uint32_t halves) {
+  const uint32_t all = (uint32_t)a.cams.count * (uint32_t)a.tiles, *r = a.ranges + (int64_t)a.cams.v0 * a.tiles;
+  const uint32_t len = r[b + 1] - r[b];
+  return len >= least && 2ull * len * all >= (uint64_t)halves * (r[all] - r[0]);
+}
+
+// What a block of a kMaybeBit tile does: its block of a long tile, else one quadrant (the first four) or nothing (0).
+__device__ __forceinline__ uint32_t maybe_block(uint32_t sub, bool tile_is_long) {
+  if (tile_is_long) return sub & ~kMaybeBit;
+  return (sub & 15u) < 4u ? 1u << (sub & 3u) : 0u;
 }
 
 // LDS record, five float4 (the quadrant masks of the 64 staged entries travel as wave ballots):
@@ -672,6 +696,10 @@ __global__ __launch_bounds__(64) void k_render_fwd(RenderArgs a) {
   const uint32_t b = tile_of_block(a, sub);
   if (*a.status != 0) return;
   if constexpr (!kCount && kContrib == kNoContrib) {
+    if (sub & kMaybeBit) {
+      sub = maybe_block(sub, long_list(a, b, kLongFwd, kLongFwdHalves));
+      if (sub == 0u) return;
+    }
     if (sub & kBlockBit) {
       const int bx = 4 * (int)(sub & 3u), by = (int)(sub & 12u);
       switch ((bx >> 3) + 2 * (by >> 3)) {
@@ -1127,6 +1155,10 @@ __global__ __launch_bounds__(64) void k_render_bwd(BwdArgs A) {
   uint32_t sub;
   const uint32_t b = tile_of_block(A.r, sub);
   if (*A.r.status != 0) return;
+  if (sub & kMaybeBit) {
+    sub = maybe_block(sub, long_list(A.r, b, kLongBwd, 0u));
+    if (sub == 0u) return;
+  }
   if (sub & kBlockBit) {
     const int bx = 4 * (int)(sub & 3u), by = (int)(sub & 12u);
     switch ((bx >> 3) + 2 * (by >> 3)) {
@@ -1203,7 +1235,7 @@ __global__ __launch_bounds__(256) void k_clear_split_qmask(RenderArgs a) {
 }  // namespace cgv2
 
 static void split_tiles(cgv2::RenderArgs& a, int64_t resident, int64_t fill_below) {
-  a.n_b = a.n_q = a.n_h = 0;
+  a.n_b = a.n_m = a.n_q = a.n_h = 0;
   if (!a.order) return;
   const int64_t all = (int64_t)a.cams.count * a.tiles;
   int64_t q = std::min<int64_t>(all / kSplitDiv, kSplitMax);
@@ -1237,7 +1269,7 @@ static cgv2::RenderArgs make_args(const cgv2_proj& p, const cgv2_bins& b, const 
   a.counters = counters;
   a.cws = nullptr;
   a.gamma = 0.f;
-  a.n_b = a.n_q = a.n_h = 0;
+  a.n_b = a.n_m = a.n_q = a.n_h = 0;
   return a;
 }
 
@@ -1257,30 +1289,43 @@ static void split_bwd(cgv2::RenderArgs& a, bool geom) {
 //   260 tiles, lists to 67,521         4370 -> 1940  2855 -> 1290  3463 -> 1440
 //   475 tiles                            89 -> 66     130 -> 73     166 -> 98
 //   600 tiles                           100 -> 78     141 -> 88     186 -> 117   (26 % of them: 85, 127, 172)
-//   1,200 tiles (2 % of them)            97 -> 98     148 -> 146    184 -> 181   (all: reverse 133, but another
-//                                                                                scene 157 -> 193)
-//   1,200 tiles, lists to 32,767       1850 -> 1030  1690 -> 784   2100 -> 902   (forward with 282 tiles; 2 % of them:
-//                                                                                1,853; reverse with all, 282: 922, 1209)
-// Bins sized for long lists (a mean capacity of kLongLists a tile) have tiles many times the mean, whose chains then
-// bound the launch, so those take more blocks.  From 2,048 tiles on the chip is full without: blocks for the heaviest
-// 1/64 cost the forward 152 -> 170 at 6,700 tiles and 1,116 -> 1,183 at 32,400, for 1/8 the reverse 297 -> 375.
-constexpr int64_t kLongLists = 3000, kAllBlocks = 640, kBlockWaves = 5120;
-static void split_blocks(cgv2::RenderArgs& a, int64_t capacity, int64_t long_waves) {
+// Up to kAllBlocks tiles all of them do.  Beyond, the heaviest do as far as kBlockWaves waves go, and further ones, as
+// far as kMaybeWaves go, where the device finds their lists long (maybe_block): in the forward kLongFwd entries and
+// kLongFwdHalves / 2 times the mean, since blocks help only where single tiles' chains bound the launch, in the reverse
+// kLongBwd entries.  The twelve waves too many of a short tile come last in the launch, where they cost nothing (in
+// front of the others: reverse 196 -> 240 at 300 k opaque surfels).  Measured, first with an allowance by the bins'
+// capacity (fitted to the scene, then the engine's own default), then by the lists:
+//   1,200 tiles, 5 M surfels, lists to 16,504, mean 2,407  forward 850, 849 -> 704   reverse 532, 531 -> 544
+//                1 M, to 3,938, mean 675                           324, 270 -> 251           410, 257 -> 265
+//                300 k opaque, to 2,295, mean 996                  110, 139 -> 110           192, 196 -> 205
+//                1 M faint, to 2,971, mean 1,214                   333, 477 -> 333           537, 383 -> 389
+//                300 k, to 679, mean 163                            92, 118 ->  93           144, 133 -> 137
+//   1,900 tiles, 1 M opaque, to 6,078, mean 2,661                  167, 166 -> 168           331, 322 -> 250
+//                1 M, to 1,043, mean 224                           139, 142 -> 142           224, 272 -> 204
+//   3,600 tiles, 2 M, 1280x720                                     376 -> 361                517 -> 533
+// (the forward by kLongFwd alone: 110 -> 136 at 300 k opaque, 333 -> 398 at 1 M faint.)  At 6,700 tiles blocks for the
+// heaviest 1/64 cost the forward 152 -> 170, for 1/8 the reverse 297 -> 375.
+constexpr int64_t kAllBlocks = 640, kBlockWaves = 5120, kMaybeWavesFwd = 8192, kMaybeWavesBwd = 20480;
+static void split_blocks(cgv2::RenderArgs& a, int64_t maybe_waves) {
   const int64_t all = (int64_t)a.cams.count * a.tiles;
-  int64_t n = all;
-  if (all > kAllBlocks) n = ((capacity / all >= kLongLists ? long_waves : kBlockWaves) - 4 * all) / 12;
-  a.n_b = (uint32_t)std::min<int64_t>(std::max<int64_t>(n, 0), a.n_q);
-  a.n_q -= a.n_b;
+  auto tiles_of = [&](int64_t waves) {
+    return (uint32_t)std::min<int64_t>(std::max<int64_t>((waves - 4 * all) / 12, 0), a.n_q);
+  };
+  a.n_b = all > kAllBlocks ? tiles_of(kBlockWaves) : a.n_q;
+  a.n_m = all > kAllBlocks ? tiles_of(maybe_waves) - a.n_b : 0;
+  a.n_q -= a.n_b + a.n_m;
+}
+static unsigned launch_blocks(const cgv2::RenderArgs& a) {
+  return (unsigned)((int64_t)a.cams.count * a.tiles + 15 * (int64_t)(a.n_b + a.n_m) + 3 * a.n_q + a.n_h);
 }
 
 hipError_t cgv2_launch_render_fwd(const cgv2_proj& p, const cgv2_bins& b, const cgv2::CamPack& cams, int64_t n,
                                   int tiles_x, int tiles_y, const cgv2_image& img, hipStream_t st) {
   cgv2::RenderArgs a = make_args(p, b, cams, n, tiles_x, tiles_y, &img, nullptr);
   split_fwd(a);
-  split_blocks(a, b.capacity, 8192);
-  const unsigned grid = (unsigned)((int64_t)cams.count * a.tiles + 15 * a.n_b + 3 * a.n_q + a.n_h);
-  if (img.qmask && a.n_b + a.n_q + a.n_h)
-    hipLaunchKernelGGL(cgv2::k_clear_split_qmask, dim3(a.n_b + a.n_q + a.n_h), dim3(256), 0, st, a);
+  split_blocks(a, kMaybeWavesFwd);
+  const unsigned grid = launch_blocks(a), split = a.n_b + a.n_m + a.n_q + a.n_h;
+  if (img.qmask && split) hipLaunchKernelGGL(cgv2::k_clear_split_qmask, dim3(split), dim3(256), 0, st, a);
   if (img.qmask) hipLaunchKernelGGL((cgv2::k_render_fwd<false, true, cgv2::kNoContrib>), dim3(grid), dim3(64), 0, st, a);
   else hipLaunchKernelGGL((cgv2::k_render_fwd<false, false, cgv2::kNoContrib>), dim3(grid), dim3(64), 0, st, a);
   return hipGetLastError();
@@ -1290,7 +1335,7 @@ hipError_t cgv2_launch_render_count(const cgv2_proj& p, const cgv2_bins& b, cons
                                     int tiles_x, int tiles_y, unsigned long long* counters, hipStream_t st) {
   cgv2::RenderArgs a = make_args(p, b, cams, n, tiles_x, tiles_y, nullptr, counters);
   split_fwd(a);
-  const unsigned grid = (unsigned)((int64_t)cams.count * a.tiles + 3 * a.n_q + a.n_h);
+  const unsigned grid = launch_blocks(a);
   hipLaunchKernelGGL((cgv2::k_render_fwd<true, false, cgv2::kNoContrib>), dim3(grid), dim3(64), 0, st, a);
   return hipGetLastError();
 }
@@ -1309,8 +1354,8 @@ hipError_t cgv2_launch_render_bwd(const cgv2_proj& p, const cgv2_bins& b, const 
   A.rg = rg;
   const bool geom = up.d_depth || up.d_depth_med || up.d_normal || up.d_alpha;
   split_bwd(A.r, geom);
-  split_blocks(A.r, b.capacity, 20480);
-  const unsigned grid = (unsigned)((int64_t)cams.count * A.r.tiles + 15 * A.r.n_b + 3 * A.r.n_q + A.r.n_h);
+  split_blocks(A.r, kMaybeWavesBwd);
+  const unsigned grid = launch_blocks(A.r);
   if (geom) hipLaunchKernelGGL(cgv2::k_render_bwd<true>, dim3(grid), dim3(64), 0, st, A);
   else hipLaunchKernelGGL(cgv2::k_render_bwd<false>, dim3(grid), dim3(64), 0, st, A);
   return hipGetLastError();
@@ -1322,7 +1367,7 @@ hipError_t cgv2_launch_contribution(const cgv2_proj& p, const cgv2_bins& b, cons
   split_fwd(a);
   a.cws = cws;
   a.gamma = gamma;
-  const unsigned grid = (unsigned)((int64_t)cams.count * a.tiles + 3 * a.n_q + a.n_h);
+  const unsigned grid = launch_blocks(a);
   if (gamma == 0.5f)
     hipLaunchKernelGGL((cgv2::k_render_fwd<false, false, cgv2::kHalfGamma>), dim3(grid), dim3(64), 0, st, a);
   else
