@@ -9,6 +9,8 @@
 #include "cgv2r_device.h"
 #include "cgv2r_kernels.h"
 
+#include <type_traits>
+
 #include <algorithm>
 
 namespace cgv2 {
@@ -131,7 +133,6 @@ __device__ __forceinline__ void load_row(const float* p, float (&v)[N]) {
     for (int j = 0; j < N; ++j) v[j] = p[j];
   }
 }
-
 
 template <int N>
 __device__ __forceinline__ void store_row(float* p, const float (&v)[N]) {
@@ -647,16 +648,27 @@ __device__ __forceinline__ void sh_bwd(const float* __restrict__ in, const float
         const float y3 = 4 * j + 3 < K ? Y[4 * j + 3 < K ? 4 * j + 3 : 0] : 0.f;
         Yj[j] = (q & 2u) ? ((q & 1u) ? y3 : y2) : ((q & 1u) ? y1 : y0);
       }
-      // colour through SH: a channel clamped at zero passes nothing
+      // colour through SH: a channel clamped at zero passes nothing.  One chain of FMAs over the coefficients, as in
+      // the projection: a channel near zero is then clamped here exactly where the image was.
       float dc[3];
 #pragma unroll
       for (int ch = 0; ch < 3; ++ch) {
-        float raw = 0.f;
+        float raw = 0.5f;
+        auto link = [&](auto lane, int j0, int j1) {  // coefficients j0 .. j1 - 1 of a lane of the quad
+          float t = raw;
+          for (int j = j0; j < j1; ++j) t = fmaf(f[b][j][ch], Yj[j], t);
+          raw = dpp<decltype(lane)::value * 0x55>(t);
+        };
+        using std::integral_constant;
 #pragma unroll
-        for (int j = 0; j < J; ++j) raw = fmaf(f[b][j][ch], Yj[j], raw);
-        raw += dpp<0xB1>(raw);  // the quad's sum
-        raw += dpp<0x4E>(raw);
-        dc[ch] = 0.5f + raw < 0.f ? 0.f : p[3 + ch];
+        for (int j = 0; j < (kWide ? 1 : J); ++j) {
+          const int j0 = kWide ? 0 : j, j1 = kWide ? J : j + 1;
+          link(integral_constant<int, 0>{}, j0, j1);
+          if (kWide || 4 * j + 1 < K) link(integral_constant<int, 1>{}, j0, j1);
+          if (kWide || 4 * j + 2 < K) link(integral_constant<int, 2>{}, j0, j1);
+          if (kWide || 4 * j + 3 < K) link(integral_constant<int, 3>{}, j0, j1);
+        }
+        dc[ch] = raw < 0.f ? 0.f : p[3 + ch];
       }
       float gY[4 * J];
 #pragma unroll
