@@ -749,32 +749,60 @@ __device__ __forceinline__ void project_bwd_wave(const cgv2_surfels& s, const De
 // the parameter and gradient lines of neighbouring surfels, and of one surfel in several views, are still in
 // the caches (a visible surfel touches some 30 sectors of the planar arrays, of which 4 % of the floats are
 // used in one view), and the view-space gradients of a view (zero outside its list) are written once, in
-// order.  10 M surfels, 8 views: 2,700 us with a launch per view and the zeroing before -> 1,940; 4 M, 4
-// views: 477 -> 386; ranges of 1,024 and 256: 2,500 and 2,130 (before the float4 rows).
-constexpr int kRange = 512;
+// order.  The next view's flags are in flight during a view.  Where less than 1 in kSparse is visible, a wave takes
+// twice the surfels.  Against a launch per view and the zeroing before, us, by share visible (0.2, 1, 3, 10 %); in
+// brackets one range size and no loads ahead:
+//   10 M surfels, 8 views, random order   478 1,145 2,474 4,701 -> 588 900 1,509 3,113   (936 1,262 1,757 3,131)
+//                          sorted         308   485   812 1,792 -> 349 403   612 1,387   (574   625   761 1,440)
+//   2 M, 8 views, random                  151   259   400   875 -> 123 191   325   655
+//   2 M, 2 views, random                   36    56    96   229 ->  33  53    97   186
+//                 sorted                   31    36    49   111 ->  30  41    59   114   ( 36    46    65   123)
+//   10 M, 2 views, sorted                  80   126   217   484 -> 136 160   189   391   (171   204   245   448)
+constexpr int kRange = 512, kSparse = 128;
 
 template <int DEG>
 __global__ __launch_bounds__(64, 2) void k_project_bwd_views(cgv2_surfels s, CamPack cams,
-                                                            const uint8_t* __restrict__ flags, RecGrads rg,
+                                                            const uint8_t* __restrict__ flags,
+                                                            const uint32_t* __restrict__ vstart, RecGrads rg,
                                                             cgv2_grads gr) {
   __shared__ BwdLds lds;
-  __shared__ uint16_t list[kRange];
-  const int64_t n = s.n, i0 = (int64_t)blockIdx.x * kRange;
+  __shared__ uint16_t list[2 * kRange];
+  constexpr int kRows = kRange / 64;
+  const int64_t n = s.n;
+  const uint32_t seen = vstart[cams.v0 + cams.count] - vstart[cams.v0];
+  const int range = (int64_t)seen * kSparse < n * cams.count ? 2 * kRange : kRange;
+  const int64_t i0 = (int64_t)blockIdx.x * range;
+  if (i0 >= n) return;
   const unsigned long long lt = (1ull << threadIdx.x) - 1ull;
+  uint8_t f[kRows];
+  auto load_flags = [&](int lv, int k0) {
+#pragma unroll
+    for (int k = 0; k < kRows; ++k) {
+      const int64_t i = i0 + k0 + k * 64 + threadIdx.x;
+      f[k] = i < n ? flags[(int64_t)(cams.v0 + lv) * n + i] : (uint8_t)0;
+    }
+  };
+  load_flags(0, 0);
   for (int lv = 0; lv < cams.count; ++lv) {
     const int v = cams.v0 + lv;
     uint32_t count = 0;
-    for (int k = 0; k < kRange; k += 64) {
-      const int64_t i = i0 + k + threadIdx.x;
-      const bool vis = i < n && (flags[(int64_t)v * n + i] & CGV2_F_VISIBLE);
-      const unsigned long long b = __ballot(vis);
-      if (vis) list[count + __popcll(b & lt)] = (uint16_t)(k + threadIdx.x);
-      count += (uint32_t)__popcll(b);
-      if (i < n && !vis) {
-        const int64_t at = (int64_t)v * 2 * n + i;
-        if (gr.g_view_total) gr.g_view_total[at] = gr.g_view_total[at + n] = 0.f;
-        if (gr.g_view_ssim) gr.g_view_ssim[at] = gr.g_view_ssim[at + n] = 0.f;
+    for (int k0 = 0; k0 < range; k0 += kRange) {
+#pragma unroll
+      for (int k = 0; k < kRows; ++k) {
+        const int at = k0 + k * 64 + (int)threadIdx.x;
+        const int64_t i = i0 + at;
+        const bool vis = (f[k] & CGV2_F_VISIBLE) != 0;
+        const unsigned long long b = __ballot(vis);
+        if (vis) list[count + __popcll(b & lt)] = (uint16_t)at;
+        count += (uint32_t)__popcll(b);
+        if (i < n && !vis) {
+          const int64_t to = (int64_t)v * 2 * n + i;
+          if (gr.g_view_total) gr.g_view_total[to] = gr.g_view_total[to + n] = 0.f;
+          if (gr.g_view_ssim) gr.g_view_ssim[to] = gr.g_view_ssim[to + n] = 0.f;
+        }
       }
+      if (k0 + kRange < range) load_flags(lv, k0 + kRange);
+      else if (lv + 1 < cams.count) load_flags(lv + 1, 0);
     }
     __syncthreads();
     for (uint32_t base = 0; base < count; base += 64u) {
@@ -880,10 +908,10 @@ hipError_t cgv2_launch_project_bwd(const cgv2_surfels& s, const cgv2::CamPack& c
   if (cams.count > 1 && n >= kViewsMin) {
     const dim3 grid((unsigned)((n + cgv2::kRange - 1) / cgv2::kRange));
     switch (s.sh_degree) {
-      case 0: hipLaunchKernelGGL(cgv2::k_project_bwd_views<0>, grid, dim3(64), 0, st, s, cams, p.flags, rg, g); break;
-      case 1: hipLaunchKernelGGL(cgv2::k_project_bwd_views<1>, grid, dim3(64), 0, st, s, cams, p.flags, rg, g); break;
-      case 2: hipLaunchKernelGGL(cgv2::k_project_bwd_views<2>, grid, dim3(64), 0, st, s, cams, p.flags, rg, g); break;
-      default: hipLaunchKernelGGL(cgv2::k_project_bwd_views<3>, grid, dim3(64), 0, st, s, cams, p.flags, rg, g); break;
+      case 0: hipLaunchKernelGGL(cgv2::k_project_bwd_views<0>, grid, dim3(64), 0, st, s, cams, p.flags, p.visible_start, rg, g); break;
+      case 1: hipLaunchKernelGGL(cgv2::k_project_bwd_views<1>, grid, dim3(64), 0, st, s, cams, p.flags, p.visible_start, rg, g); break;
+      case 2: hipLaunchKernelGGL(cgv2::k_project_bwd_views<2>, grid, dim3(64), 0, st, s, cams, p.flags, p.visible_start, rg, g); break;
+      default: hipLaunchKernelGGL(cgv2::k_project_bwd_views<3>, grid, dim3(64), 0, st, s, cams, p.flags, p.visible_start, rg, g); break;
     }
     return hipGetLastError();
   }
