@@ -579,7 +579,11 @@ __device__ __forceinline__ void render_fwd_block(const RenderArgs& a, Stage& s, 
   bool live = __ballot(T > 0.f) != 0;
   for (uint32_t base = start; base < end && live; base += 64) {
     const uint32_t idx = base + lane;
-    uint64_t todo = __ballot(stage_put<true>(s, lane, in, ox, oy, true, bx, by) != 0u);
+    const bool here = stage_put<true>(s, lane, in, ox, oy, true, bx, by) != 0u;
+    uint64_t todo = __ballot(here);
+    // Entries of an infinite colour (colours are never negative or NaN) are taken alone: zero times it is not zero, so
+    // one that no pixel takes may not share in the others' sums.
+    const uint64_t inf = __ballot(here && !(in.r[3].y + in.r[3].z + in.r[3].w < INFINITY));
     stage_load(in, a.rec, vn, a.n, nid, idx + 64u < end ? 1u << k : 0u);
     nid = idx + 128u < end ? a.ids[idx + 128u] : 0u;
     __syncthreads();
@@ -587,12 +591,19 @@ __device__ __forceinline__ void render_fwd_block(const RenderArgs& a, Stage& s, 
     while (todo != 0) {
       int at[4];
       bool has[4];
+      uint64_t now = todo;
+      if (inf != 0) {
+        const uint64_t first = todo & (0ull - todo), next = todo & inf;
+        now = (first & inf) ? first : todo & ((next & (0ull - next)) - 1ull);
+      }
+      todo &= ~now;
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        has[q] = todo != 0;
-        at[q] = has[q] ? __builtin_ctzll(todo) : at[0];
-        todo &= todo - 1;
+        has[q] = now != 0;
+        at[q] = has[q] ? __builtin_ctzll(now) : at[0];
+        now &= now - 1;
       }
+      todo |= now;
       const int j = part == 0 ? at[0] : part == 1 ? at[1] : part == 2 ? at[2] : at[3];
       const bool act = part == 0 || (part == 1 ? has[1] : part == 2 ? has[2] : has[3]);
       const float4 q0 = s.q[j][0], q1 = s.q[j][1], q2 = s.q[j][2];
@@ -1111,6 +1122,8 @@ __device__ __forceinline__ void render_bwd_block(const BwdArgs& A, Stage& s, uin
       if (taken == 0) continue;
       BwdTake u;
       bwd_take<kGeom>(e, con, q2, q3, q4, p, u);
+      u.g = con ? u.g : 0.f;  // (of an entry that is not taken it may be infinite)
+      u.gs = con ? u.gs : 0.f;
       // the transmittance behind each of the four entries, from the last one on
       const float T1 = p.T * quad_lane<0>(u.rom), T2 = T1 * quad_lane<1>(u.rom), T3 = T2 * quad_lane<2>(u.rom);
       const float Tn = part == 0 ? p.T : part == 1 ? T1 : part == 2 ? T2 : T3;
