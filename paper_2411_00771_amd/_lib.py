@@ -207,28 +207,36 @@ def camera_struct(cam) -> Camera:
 
 def _fill_cameras(arr, cams):
     """camera_struct of every camera, field by field through a numpy view of the array."""
-    import operator
+    from itertools import chain
+    from operator import attrgetter, itemgetter
 
     import numpy as np
     n = len(cams)
     rows = np.frombuffer(arr, dtype=np.dtype(Camera))
     scalars = ("fx", "fy", "cx", "cy", "znear")
-    get = operator.attrgetter(*scalars)
-    values = np.array([get(c) for c in cams], np.float64)
+
+    # scalars one by one through float(), which refuses what has no number (None would become NaN in an array) and takes
+    # what an array does not (tensors that require gradients)
+    def floats(get, items, count):
+        return np.fromiter(map(float, chain.from_iterable(map(get, items))), np.float64, n * count).reshape(n, count)
+
+    values = floats(attrgetter(*scalars), cams, len(scalars))
+    bg = floats(itemgetter(0, 1, 2), map(attrgetter("bg"), cams), 3)
     with np.errstate(over="ignore", invalid="ignore"):
-        rows["width"] = [int(c.width) for c in cams]
-        rows["height"] = [int(c.height) for c in cams]
+        for f in ("width", "height"):  # wrapped to 32 bits, as a structure's field is
+            rows[f] = np.array([int(x) & 0xffffffff for x in map(attrgetter(f), cams)], np.uint32).view(np.int32)
         for k, f in enumerate(scalars):
             rows[f] = values[:, k]
-        for f, m in (("R", 9), ("t", 3), ("bg", 3)):
-            rows[f] = np.array([getattr(c, f) for c in cams], np.float64).reshape(n, m)
+        rows["bg"] = bg
+        for f, m in (("R", 9), ("t", 3)):
+            rows[f] = np.array(list(map(attrgetter(f), cams)), np.float64).reshape(n, m)
 
 
 def camera_array(cams):
     arr = (Camera * len(cams))()
-    # by fields from the size on where that is the faster (us: 2 cameras 11 and 11, 8 cameras 40 and 20, 958 cameras
-    # 4,900 and 1,150); cameras whose fields don't stack are taken one by one
-    if len(cams) >= 4:
+    # by fields from the size on where that is the faster (us: 4 cameras 28 and 35, 8 cameras 68 and 41, 958 cameras
+    # 4,590 and 1,060); cameras whose fields don't stack are taken one by one
+    if len(cams) >= 6:
         try:
             _fill_cameras(arr, cams)
             return arr
