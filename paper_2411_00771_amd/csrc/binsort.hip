@@ -7,19 +7,22 @@
 //                 of the visible ones into per-view lists, plus the capacity check
 //   k_stage       a workgroup per run of consecutive visible surfels: for each tile of a surfel's rect that
 //                 its alpha >= 1/255 region reaches (reach_cell over the tile's pixel samples), a returning
-//                 atomic on the tile's counter gives the entry's rank within the tile; the run's entries
-//                 (counter, rank, depth bits << 32 | id) are packed at the start of the run's rect slots
+//                 atomic on the tile's counter gives the entry's rank within the tile; the entry (counter, rank)
+//                 is packed, with large rects at the start of the surfel's rect slots, with small ones at the
+//                 start of the run's; each visible surfel's depth, number of entries and first slot go beside
 //   k_tile_scan_order   one workgroup up to kScanChunk tiles: exclusive prefix sum of the counters ->
 //                 ranges and each counter's first slot; for at most kMaxViews views also the launch order
 //                 (k_tile_sums / k_tile_apply and the multi-workgroup order kernels otherwise)
-//   k_place       a workgroup per run: keys[first slot of the counter + rank] = key (no atomics)
+//   k_place       a workgroup per run: keys[first slot of the counter + rank] = depth bits << 32 | id of the
+//                 entry's surfel (no atomics)
 //   k_sort_wave   one wave per tile: bitonic sort of lists up to kWaveSort entries in registers; a longer
 //                 list is cut into equal chunks of at most kWaveSort, one wave each
 //   k_merge       one workgroup per chunk: each key's place among the other chunks of its list (binary
 //                 searches in LDS) gives its slot
 // (depth bits, id) is unique within a tile, so the order in which the atomics hand out ranks does not
-// matter: the result is deterministic and bit-exact.  HBM traffic is about 16 B staged + 16 B read +
-// 8 B placed + 8 B read + 4 B written per listed entry, nothing per rect tile out of reach.
+// matter: the result is deterministic and bit-exact.  HBM traffic is about 8 B staged + 8 B read + 8 B placed +
+// 8 B read + 4 B written per listed entry and 10 B written and read per visible surfel, nothing per rect tile out
+// of reach.
 #include "cgv2r_device.h"
 #include "cgv2r_kernels.h"
 
@@ -1165,8 +1168,8 @@ static int64_t counter_room(int64_t m, int64_t capacity) {
 size_t cgv2_binsort_ws_layout(int64_t capacity, int V, int tiles, int64_t n, size_t* off) {
   // off: [0] tile counters (u32, counter_room) and, after those in use, the sort-item and chunk-queue
   //      counts, [1] chunk sums of the surfel scan (2 x u64 arrays), [2] chunks of the long lists (uint2), [3] scan totals
-  //      (u64 x 2), [4] keys (u64, capacity), [5] staged entries (8 B, capacity), [6], [7], [11] per visible entry: staged count (u16), first slot (u32, capacity), depth (f32),
-  //      [8] chunk sums of the tile scan (u64)
+  //      (u64 x 2), [4] keys (u64, capacity), [5] staged entries (8 B, capacity), [11], [6], [7] per visible
+  //      surfel: depth (f32), staged count (u16), first slot (u32, capacity), [8] chunk sums of the tile scan (u64)
   const int64_t m = (int64_t)V * tiles;
   const int64_t vn = (int64_t)V * n;
   const int64_t nsb = surf_blocks(vn > 0 ? vn : 1);

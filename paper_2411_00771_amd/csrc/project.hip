@@ -896,9 +896,9 @@ hipError_t cgv2_launch_zero_grads(const cgv2_grads& g, int64_t n, int sh_degree,
   return hipGetLastError();
 }
 
-// Several views of many surfels go through k_project_bwd_views; below kViewsMin a launch per view is as fast (us:
-// 4 M surfels, 2 views 240 -> 214 through the views; 1 M, 5 views 120 -> 122; 132 k, 8 views 73 -> 80) and the
-// range would no longer fill the chip.
+// Several views of many surfels go through k_project_bwd_views (its comment has both sides); below kViewsMin a launch
+// per view is as fast (us: 1 M surfels, 5 views 120 -> 122; 132 k, 8 views 73 -> 80) and the ranges would no longer
+// fill the chip.
 constexpr int64_t kViewsMin = 2000000;
 
 hipError_t cgv2_launch_project_bwd(const cgv2_surfels& s, const cgv2::CamPack& cams, const cgv2_proj& p,

@@ -9,7 +9,8 @@
 // and reducing the surfel's pixel rect to a 4-bit mask of the quadrants it reaches, less those its
 // alpha >= 1/255 region (an ellipse, plus the screen-filter disc) misses.  A quadrant outside the mask
 // is skipped wave-uniformly, as is a quadrant whose pixels have all stopped; within a quadrant the
-// evaluation is branch-free, and the homography terms of a lane's four pixels are one add apart.
+// evaluation is branch-free, and the homography terms of a lane's four pixels are one add apart.  A heavy tile, or
+// one of a small launch, runs as halves, quadrants or sixteen 4x4 blocks in waves of their own (tile_of_block).
 //
 // The reverse walks each pixel's list from its checkpointed 'last' entry downwards, recovers T by
 // division, sums the per-surfel gradients of its four pixels in registers, reduces them over the

@@ -11,8 +11,8 @@ pytestmark = pytest.mark.gpu
 NAMES = ("rgb", "depth", "depth_med", "normal", "alpha", "T_final", "last", "med")
 
 
-# tiles: one (ragged, and with blocks outside the image), all blocks up to 640, some from 641 to 1,279, and with bins
-# sized for long lists up to 2,047; two views in one launch.  Opaque surfels stop pixels within four entries of one
+# tiles: one (ragged, and with blocks outside the image), all blocks up to 640, the heaviest from 641 to 1,279, and above
+# that none, the lists being short (the long-tiles test has others); two views in one launch.  Opaque surfels stop pixels within four entries of one
 # another, faint ones fill the lists; a few surfels leave all but one of the four places empty.
 @pytest.mark.parametrize("W,H,views,capacity,n,opacity", [
     (5, 3, 1, 1 << 20, 4000, 2.0), (16, 16, 1, 1 << 20, 3, 0.0), (16, 16, 1, 1 << 20, 70000, -3.0),

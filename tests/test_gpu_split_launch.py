@@ -8,8 +8,9 @@ from tests.helpers import gpu_forward, grad_close
 pytestmark = pytest.mark.gpu
 
 
-# tiles: 1 (a lone quadrant-split tile), 42 (all quadrants), 1,281 (one tile past all quadrants), 2,560 / 2,601
-# (the last all-halves launch, the first without), 3,136 and 4,096 (past the reverse's and the forward's fill)
+# tiles: 1 and 42 (all of them blocks, in the contribution pass quadrants), 1,281 (one tile past all quadrants; the
+# lists are too short for blocks, so quadrants in both directions), 2,560 / 2,601 (the last all-halves launch, the
+# first without), 3,136 and 4,096 (past the reverse's and the forward's fill)
 @pytest.mark.parametrize("W,H,views", [(9, 11, 1), (101, 85, 1), (336, 976, 1), (1024, 640, 1), (816, 816, 1),
                                        (896, 896, 1), (512, 512, 4)])
 def test_split_changes_nothing(cuda, W, H, views):
